@@ -3,7 +3,9 @@
 // mean-squared error and Adam, evaluated in the LHMM loop with an ensemble
 // spread gate (include/lhmm.h, lhmm_sur_*).
 //
-// Every product is one NT GEMM  C[M x N] = A[M x K] * B[N x K]^T  on BF16
+// Ensembles whose layers fit a workgroup's LDS (MLP_MAX_NH, MLP_LDS_MAX) run
+// the fused kernels of lhmm_mlp.h.  Wider ones run layer by layer: every
+// product is one NT GEMM  C[M x N] = A[M x K] * B[N x K]^T  on BF16
 // operands with FP32 accumulation (v_mfma_f32_32x32x16_bf16), one wave per
 // 32 x 32 x NT output tile (NT = 4, 2 or 1 as N allows), batched over the
 // ensemble members (grid z).  Operand
@@ -27,19 +29,11 @@
 
 #include "lhmm.h"
 #include "lhmm_internal.h"
+#include "lhmm_mlp.h"
 
 namespace {
 
-typedef __bf16 bf16;
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
 constexpr int HIST = LHMM_SUR_HIST;  // gradient samples per feature vector
-
-__device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_grad_f(float z) {
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * expf(-0.5f * z * z);
-}
 
 enum Epi {
     EPI_F32 = 0,      // C -> f32 [M x N]
@@ -103,7 +97,6 @@ __global__ __launch_bounds__(64) void k_gemm_nt(Gemm g) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[j], acc[j], 0, 0, 0);
     const long cbase = z * g.sC, tbase = e * g.sCt;
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int col = n0 + 32 * j + (l & 31);
@@ -214,8 +207,6 @@ __global__ void k_loss_final(const float* __restrict__ part, int nparts, int B, 
 // every 16th, and adds its 16 partials in order; k_colsum_final adds the
 // COLSUM_SLICES slices in order.  Slicing the rows keeps ~16 dependent loads
 // per thread where one block per column tile would chain hundreds.
-constexpr int COLSUM_SLICES = 16;
-
 __global__ __launch_bounds__(1024) void k_colsum_part(const float* __restrict__ x, int rows, int cols, long stride,
                                                      float* __restrict__ part) {
     __shared__ float sh[16][64];
@@ -439,6 +430,11 @@ struct lhmm_sur {
     float *Z1, *Z2, *Y, *dYf, *dZ1f, *dZ2f, *part;
     float* part_k = nullptr;  // k-split partials of the weight gradients
     float* part_c = nullptr;  // row-slice partials of the bias gradients
+    // fused engines (lhmm_mlp.h): packed weights, packed activations and
+    // gradients of the last training step, and partials
+    bool fused = false;
+    bf16 *W1f = nullptr, *W2f = nullptr, *W3f = nullptr, *W2r = nullptr, *W3r = nullptr;
+    float *pb[3] = {}, *pw[3] = {};
 };
 
 namespace {
@@ -504,6 +500,88 @@ void colsum(lhmm_sur* s, const float* x, int rows, int cols, long stride, float*
 long szW1(const lhmm_sur* s) { return (long)s->nin_p * s->nh; }
 long szW2(const lhmm_sur* s) { return (long)s->nh * s->nh; }
 long szW3(const lhmm_sur* s) { return (long)s->nh * s->nout_p; }
+
+// --- fused engines -----------------------------------------------------------
+
+template <bool TRAIN>
+void launch_rows(lhmm_sur* s, const MlpArgs& a) {
+    const dim3 grid(a.Bp / 32, s->E);
+    const size_t lds = mlp_lds_bytes(s->nin_p, s->nh);
+    if (s->nh <= 32 * MLP_WAVES)
+        k_mlp_rows<TRAIN, 1><<<grid, 64 * MLP_WAVES, lds, s->stream>>>(a);
+    else
+        k_mlp_rows<TRAIN, 2><<<grid, 64 * MLP_WAVES, lds, s->stream>>>(a);
+}
+
+MlpArgs rows_args(const lhmm_sur* s, const float* X, int B) {
+    MlpArgs a{};
+    a.X = X;
+    a.B = B;
+    a.Bp = round_up(B, 32);
+    a.nin = s->nin; a.nin_p = s->nin_p; a.nh = s->nh; a.nout = s->nout;
+    a.W1f = s->W1f; a.W2f = s->W2f; a.W3f = s->W3f; a.W2r = s->W2r; a.W3r = s->W3r;
+    a.b1 = s->b1; a.b2 = s->b2; a.b3 = s->b3;
+    return a;
+}
+
+// chunks of the batch in the weight gradients (K = batch): KCHUNK rows each, one below 2 KCHUNK
+int dw_chunks(int Bp) { return Bp >= 2 * KCHUNK ? (Bp + KCHUNK - 1) / KCHUNK : 1; }
+
+// Adam on every tensor from the partials of a batch in `chunks` chunks and
+// `nparts` loss partials; with chunks = nparts = 0 and lr = 0 it only writes
+// the packed copies of the masters
+void launch_update(lhmm_sur* s, int B, int chunks, int nparts, float lr, float c1, float c2, float* loss) {
+    UpArgs u{};
+    u.m[0] = UpMat{s->W1, s->gW1, s->mW1, s->vW1, s->pw[0], s->W1f, nullptr, s->nin_p, s->nh, 0};
+    u.m[1] = UpMat{s->W2, s->gW2, s->mW2, s->vW2, s->pw[1], s->W2f, s->W2r, s->nh, s->nh, 0};
+    u.m[2] = UpMat{s->W3, s->gW3, s->mW3, s->vW3, s->pw[2], s->W3f, s->W3r, s->nh, s->nout_p, 0};
+    u.b[0] = UpVec{s->b1, s->gb1, s->mb1, s->vb1, s->pb[0], s->nh, 0};
+    u.b[1] = UpVec{s->b2, s->gb2, s->mb2, s->vb2, s->pb[1], s->nh, 0};
+    u.b[2] = UpVec{s->b3, s->gb3, s->mb3, s->vb3, s->pb[2], s->nout_p, 0};
+    int blk = 0;
+    for (UpMat& m : u.m) {
+        m.blk0 = blk;
+        blk += (int)(((long)s->E * (m.rows / 8) * m.cols + 255) / 256);
+    }
+    for (UpVec& b : u.b) {
+        b.blk0 = blk;
+        blk += (s->E * b.n + 255) / 256;
+    }
+    u.loss0 = blk;
+    if (loss) blk += s->E;
+    u.E = s->E; u.chunks = chunks; u.nparts = nparts; u.B = B; u.nout = s->nout;
+    u.lr = lr; u.c1 = c1; u.c2 = c2;
+    u.ploss = s->part;
+    u.loss = loss;
+    k_mlp_update<<<blk, 256, 0, s->stream>>>(u);
+}
+
+void launch_dw(lhmm_sur* s, int Bp, int chunks) {
+    DwArgs d{};
+    const int it = s->nin_p / 32, ht = s->nh / 32;
+    const long sh = (long)s->nh * Bp, sy = 32L * Bp;
+    d.m[0] = DwMat{s->Xt, s->dZ1t, 0, sh, it, ht, 0, s->pw[0]};
+    d.m[1] = DwMat{s->H1t, s->dZ2t, sh, sh, ht, ht, 0, s->pw[1]};
+    d.m[2] = DwMat{s->H2t, s->dYt, sh, sy, ht, 1, 0, s->pw[2]};
+    for (DwMat& m : d.m) {
+        m.u0 = d.units;
+        d.units += ((m.mt + 1) / 2) * ((m.ntl + 1) / 2);
+    }
+    int cs = 0;
+    d.b[0] = DwVec{s->dZ1f, s->pb[0], s->nh, 0};
+    d.b[1] = DwVec{s->dZ2f, s->pb[1], s->nh, 0};
+    d.b[2] = DwVec{s->dYf, s->pb[2], s->nout_p, 0};
+    for (DwVec& b : d.b) {
+        b.u0 = cs;
+        cs += COLSUM_SLICES * ((b.n + 63) / 64);
+    }
+    d.chunks = chunks;
+    d.KSB = Bp / 16;
+    d.kschunk = chunks > 1 ? KCHUNK / 16 : d.KSB;
+    k_mlp_dw<<<dim3(d.units * chunks + cs, s->E), 64, 0, s->stream>>>(d);
+}
+
+// --- layer-wise engines ------------------------------------------------------
 
 // Activations of a forward pass: padded BF16 inputs X [Bp x nin_p], per
 // member the BF16 hidden activations H1, H2 (member stride sh), their FP32
@@ -626,6 +704,15 @@ int lhmm_sur_create(const lhmm_sur_params* p, const float* weights, void* stream
     }
     const long E = s->E, w1 = szW1(s), w2 = szW2(s), w3 = szW3(s), nh = s->nh, no = s->nout_p;
     const long Bm = s->Bmax;
+    const size_t lds = mlp_lds_bytes(s->nin_p, s->nh);
+    s->fused = s->nh <= MLP_MAX_NH && lds <= MLP_LDS_MAX;
+    if (s->fused)
+        for (const void* k : {(const void*)&k_mlp_rows<false, 1>, (const void*)&k_mlp_rows<false, 2>,
+                              (const void*)&k_mlp_rows<true, 1>, (const void*)&k_mlp_rows<true, 2>})
+            if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MLP_LDS_MAX) != hipSuccess) {
+                delete s;
+                return lhmm_fail(LHMM_ERR_HIP, "fused layers: LDS of %zu bytes refused", lds);
+            }
     float** f32s[] = {&s->W1, &s->gW1, &s->mW1, &s->vW1};
     for (float** q : f32s) rc = rc ? rc : sur_alloc(s, q, E * w1);
     float** f32h[] = {&s->b1, &s->gb1, &s->mb1, &s->vb1, &s->b2, &s->gb2, &s->mb2, &s->vb2};
@@ -636,27 +723,44 @@ int lhmm_sur_create(const lhmm_sur_params* p, const float* weights, void* stream
     for (float** q : f32w3) rc = rc ? rc : sur_alloc(s, q, E * w3);
     float** f32b3[] = {&s->b3, &s->gb3, &s->mb3, &s->vb3};
     for (float** q : f32b3) rc = rc ? rc : sur_alloc(s, q, E * no);
-    bf16** wb[] = {&s->W1b, &s->W1t};
-    for (bf16** q : wb) rc = rc ? rc : sur_alloc(s, q, E * w1);
-    bf16** wb2[] = {&s->W2b, &s->W2t};
-    for (bf16** q : wb2) rc = rc ? rc : sur_alloc(s, q, E * w2);
-    bf16** wb3[] = {&s->W3b, &s->W3t};
-    for (bf16** q : wb3) rc = rc ? rc : sur_alloc(s, q, E * w3);
-    rc = rc ? rc : sur_alloc(s, &s->X, Bm * s->nin_p);
-    rc = rc ? rc : sur_alloc(s, &s->Xt, Bm * s->nin_p);
-    bf16** acts[] = {&s->H1, &s->H1t, &s->H2, &s->H2t, &s->dZ2, &s->dZ2t, &s->dZ1, &s->dZ1t};
-    for (bf16** q : acts) rc = rc ? rc : sur_alloc(s, q, E * Bm * nh);
-    float** actf[] = {&s->Z1, &s->Z2, &s->dZ1f, &s->dZ2f};
-    for (float** q : actf) rc = rc ? rc : sur_alloc(s, q, E * Bm * nh);
-    rc = rc ? rc : sur_alloc(s, &s->Y, E * Bm * no);
-    rc = rc ? rc : sur_alloc(s, &s->dYf, E * Bm * no);
-    rc = rc ? rc : sur_alloc(s, &s->dY, E * Bm * no);
-    rc = rc ? rc : sur_alloc(s, &s->dYt, E * Bm * no);
-    rc = rc ? rc : sur_alloc(s, &s->part, E * (Bm * no / 256 + 1));
-    rc = rc ? rc : sur_alloc(s, &s->part_c, (size_t)E * COLSUM_SLICES * std::max(nh, no));
-    if (Bm >= 2 * KCHUNK) {
-        const long mn = std::max(std::max(w1, w2), w3);
-        rc = rc ? rc : sur_alloc(s, &s->part_k, E * ((Bm + KCHUNK - 1) / KCHUNK) * mn);
+    if (s->fused) {
+        rc = rc ? rc : sur_alloc(s, &s->W1f, E * w1);
+        for (bf16** q : {&s->W2f, &s->W2r}) rc = rc ? rc : sur_alloc(s, q, E * w2);
+        for (bf16** q : {&s->W3f, &s->W3r}) rc = rc ? rc : sur_alloc(s, q, E * w3);
+        rc = rc ? rc : sur_alloc(s, &s->Xt, Bm * s->nin_p);
+        for (bf16** q : {&s->H1t, &s->H2t, &s->dZ2t, &s->dZ1t}) rc = rc ? rc : sur_alloc(s, q, E * Bm * nh);
+        rc = rc ? rc : sur_alloc(s, &s->dYt, E * Bm * no);
+        for (float** q : {&s->dZ2f, &s->dZ1f}) rc = rc ? rc : sur_alloc(s, q, E * Bm * nh);
+        rc = rc ? rc : sur_alloc(s, &s->dYf, E * Bm * no);
+        rc = rc ? rc : sur_alloc(s, &s->part, E * (Bm / 8));
+        const long sz[3] = {w1, w2, w3}, bz[3] = {nh, nh, no};
+        for (int k = 0; k < 3; ++k) {
+            rc = rc ? rc : sur_alloc(s, &s->pw[k], E * dw_chunks(Bm) * sz[k]);
+            rc = rc ? rc : sur_alloc(s, &s->pb[k], E * COLSUM_SLICES * bz[k]);
+        }
+    } else {
+        bf16** wb[] = {&s->W1b, &s->W1t};
+        for (bf16** q : wb) rc = rc ? rc : sur_alloc(s, q, E * w1);
+        bf16** wb2[] = {&s->W2b, &s->W2t};
+        for (bf16** q : wb2) rc = rc ? rc : sur_alloc(s, q, E * w2);
+        bf16** wb3[] = {&s->W3b, &s->W3t};
+        for (bf16** q : wb3) rc = rc ? rc : sur_alloc(s, q, E * w3);
+        rc = rc ? rc : sur_alloc(s, &s->X, Bm * s->nin_p);
+        rc = rc ? rc : sur_alloc(s, &s->Xt, Bm * s->nin_p);
+        bf16** acts[] = {&s->H1, &s->H1t, &s->H2, &s->H2t, &s->dZ2, &s->dZ2t, &s->dZ1, &s->dZ1t};
+        for (bf16** q : acts) rc = rc ? rc : sur_alloc(s, q, E * Bm * nh);
+        float** actf[] = {&s->Z1, &s->Z2, &s->dZ1f, &s->dZ2f};
+        for (float** q : actf) rc = rc ? rc : sur_alloc(s, q, E * Bm * nh);
+        rc = rc ? rc : sur_alloc(s, &s->Y, E * Bm * no);
+        rc = rc ? rc : sur_alloc(s, &s->dYf, E * Bm * no);
+        rc = rc ? rc : sur_alloc(s, &s->dY, E * Bm * no);
+        rc = rc ? rc : sur_alloc(s, &s->dYt, E * Bm * no);
+        rc = rc ? rc : sur_alloc(s, &s->part, E * (Bm * no / 256 + 1));
+        rc = rc ? rc : sur_alloc(s, &s->part_c, (size_t)E * COLSUM_SLICES * std::max(nh, no));
+        if (Bm >= 2 * KCHUNK) {
+            const long mn = std::max(std::max(w1, w2), w3);
+            rc = rc ? rc : sur_alloc(s, &s->part_k, E * ((Bm + KCHUNK - 1) / KCHUNK) * mn);
+        }
     }
     if (rc == LHMM_OK) rc = lhmm_sur_set_weights(s, weights);
     if (rc != LHMM_OK) {
@@ -703,13 +807,17 @@ int lhmm_sur_set_weights(lhmm_sur* s, const float* weights) {
     for (int k = 0; k < 18; ++k) LHMM_HIPCHK(hipMemset(zero[k], 0, (size_t)E * zs[k] * 4));
     // BF16 copies: an Adam step with zero learning rate and zero gradient
     // leaves the masters unchanged and writes both layouts
-    const int t = 256;
-    k_adam<<<(E * w1 + t - 1) / t, t, 0, s->stream>>>(s->W1, s->gW1, s->mW1, s->vW1, nin_p, nh, w1, E, 0.f, 1.f, 1.f,
-                                                     s->W1b, s->W1t);
-    k_adam<<<(E * w2 + t - 1) / t, t, 0, s->stream>>>(s->W2, s->gW2, s->mW2, s->vW2, nh, nh, w2, E, 0.f, 1.f, 1.f,
-                                                     s->W2b, s->W2t);
-    k_adam<<<(E * w3 + t - 1) / t, t, 0, s->stream>>>(s->W3, s->gW3, s->mW3, s->vW3, nh, no, w3, E, 0.f, 1.f, 1.f,
-                                                     s->W3b, s->W3t);
+    if (s->fused) {
+        launch_update(s, 1, 0, 0, 0.f, 1.f, 1.f, nullptr);
+    } else {
+        const int t = 256;
+        k_adam<<<(E * w1 + t - 1) / t, t, 0, s->stream>>>(s->W1, s->gW1, s->mW1, s->vW1, nin_p, nh, w1, E, 0.f, 1.f, 1.f,
+                                                         s->W1b, s->W1t);
+        k_adam<<<(E * w2 + t - 1) / t, t, 0, s->stream>>>(s->W2, s->gW2, s->mW2, s->vW2, nh, nh, w2, E, 0.f, 1.f, 1.f,
+                                                         s->W2b, s->W2t);
+        k_adam<<<(E * w3 + t - 1) / t, t, 0, s->stream>>>(s->W3, s->gW3, s->mW3, s->vW3, nh, no, w3, E, 0.f, 1.f, 1.f,
+                                                         s->W3b, s->W3t);
+    }
     LHMM_HIPCHK(hipGetLastError());
     LHMM_HIPCHK(hipStreamSynchronize(s->stream));
     s->step = 0;
@@ -779,6 +887,19 @@ int lhmm_sur_train_step(lhmm_sur* s, const float* X, const float* T, int32_t B, 
     if (!(lr >= 0.0f) || !std::isfinite(lr)) return lhmm_fail(LHMM_ERR_ARG, "bad learning rate");
     const int Bp = round_up(B, 32), E = s->E, nh = s->nh, no = s->nout_p;
     const long Bm = s->Bmax;
+    if (s->fused) {
+        MlpArgs a = rows_args(s, X, B);
+        a.T = T;
+        a.Xt = s->Xt; a.H1t = s->H1t; a.H2t = s->H2t; a.dYt = s->dYt; a.dZ2t = s->dZ2t; a.dZ1t = s->dZ1t;
+        a.dYf = s->dYf; a.dZ2f = s->dZ2f; a.dZ1f = s->dZ1f; a.ploss = s->part;
+        launch_rows<true>(s, a);
+        launch_dw(s, Bp, dw_chunks(Bp));
+        s->step += 1;
+        launch_update(s, B, dw_chunks(Bp), Bp / 8, lr, 1.0f - powf(0.9f, (float)s->step),
+                      1.0f - powf(0.999f, (float)s->step), loss);
+        LHMM_HIPCHK(hipGetLastError());
+        return LHMM_OK;
+    }
     int rc = load_inputs(s, X, B, Bp, s->X, s->Xt);
     if (rc != LHMM_OK) return rc;
     forward(s, Bp, engine_act(s, true));
@@ -853,6 +974,13 @@ int lhmm_sur_forward(lhmm_sur* s, const float* X, int32_t B, float* Y) {
     lhmm_clear_error();
     if (!s || !X || !Y) return lhmm_fail(LHMM_ERR_ARG, "null argument");
     if (B < 1 || B > s->Bmax) return lhmm_fail(LHMM_ERR_ARG, "batch %d outside 1..%d", B, s->Bmax);
+    if (s->fused) {
+        MlpArgs a = rows_args(s, X, B);
+        a.Y = Y;
+        launch_rows<false>(s, a);
+        LHMM_HIPCHK(hipGetLastError());
+        return LHMM_OK;
+    }
     const int Bp = round_up(B, 32);
     int rc = load_inputs(s, X, B, Bp, s->X, nullptr);
     if (rc != LHMM_OK) return rc;
@@ -877,6 +1005,13 @@ int lhmm_sur_forward_static(lhmm_sur* s, const float* X, int32_t B, float* Y) {
     LHMM_HIPCHK(hipGetDevice(&dev));
     if (dev != s->device) return lhmm_fail(LHMM_ERR_ARG, "call with the engine's device %d current (got %d)", s->device, dev);
     if (dev < 0 || dev >= MAX_DEVICES) return lhmm_fail(LHMM_ERR_ARG, "device %d beyond the %d supported", dev, MAX_DEVICES);
+    if (s->fused) {  // keeps its activations in LDS: the scratch is not touched
+        MlpArgs a = rows_args(s, X, B);
+        a.Y = Y;
+        launch_rows<false>(s, a);
+        LHMM_HIPCHK(hipGetLastError());
+        return LHMM_OK;
+    }
     unsigned char* base = nullptr;
     {
         // the scratch's device address, looked up once per device (with that device current)
