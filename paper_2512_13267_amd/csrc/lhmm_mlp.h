@@ -62,29 +62,33 @@ inline size_t mlp_lds_bytes(int nin_p, int nh) {
     return sizeof(bf16) * 32 * ((size_t)(nin_p + MLP_PAD) + 2 * (size_t)(nh + MLP_PAD) + 32 + MLP_PAD);
 }
 
-// Fragments in flight per wave: a product of 16 k-steps waits for L2 twice
-// instead of at every step.
-constexpr int MLP_PF = 8;
+// Weight fragments in flight per wave, so that a product of 16 k-steps does
+// not wait for L2 at every step.  Inference: 4 (14.3 us for 217 rows, 8 take
+// 15.5: the registers hold fewer waves).  Training keeps GELU' in registers
+// and has two workgroups per CU either way: 8 (64 us for 5 x 4096 rows, 4 take 67).
+constexpr int mlp_pf(bool train) { return train ? 8 : 4; }
 
-__device__ __forceinline__ void mlp_preload(bf16x8 (&b)[MLP_PF], const bf16* w, int KS, int l) {
+template <int PF>
+__device__ __forceinline__ void mlp_preload(bf16x8 (&b)[PF], const bf16* w, int KS, int l) {
     const bf16x8* p = (const bf16x8*)w + l;
 #pragma unroll
-    for (int i = 0; i < MLP_PF; ++i) b[i] = p[min(i, KS - 1) * 64];
+    for (int i = 0; i < PF; ++i) b[i] = p[min(i, KS - 1) * 64];
 }
 
 // acc += A W^T for one 32-column tile: A rows in LDS (row stride lda), the
-// tile's packed fragments at w, the first MLP_PF of them in b already.
-__device__ __forceinline__ void mlp_tile(floatx16& acc, bf16x8 (&b)[MLP_PF], const bf16* As, int lda, const bf16* w,
+// tile's packed fragments at w, the first PF of them in b already.
+template <int PF>
+__device__ __forceinline__ void mlp_tile(floatx16& acc, bf16x8 (&b)[PF], const bf16* As, int lda, const bf16* w,
                                          int KS, int l) {
     const bf16x8* p = (const bf16x8*)w + l;
     const bf16* a = As + (l & 31) * lda + 8 * (l >> 5);
-    for (int k0 = 0; k0 < KS; k0 += MLP_PF) {
+    for (int k0 = 0; k0 < KS; k0 += PF) {
 #pragma unroll
-        for (int i = 0; i < MLP_PF; ++i) {
+        for (int i = 0; i < PF; ++i) {
             if (k0 + i < KS) {
                 const bf16x8 av = *(const bf16x8*)(a + 16 * (k0 + i));
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b[i], acc, 0, 0, 0);
-                if (k0 + MLP_PF + i < KS) b[i] = p[(k0 + MLP_PF + i) * 64];
+                if (k0 + PF + i < KS) b[i] = p[(k0 + PF + i) * 64];
             }
         }
     }
@@ -96,11 +100,14 @@ __device__ __forceinline__ void mlp_store_t(bf16* base, int t, int KSB, int R0, 
     *(bf16x4*)(base + ((size_t)t * KSB + R0 / 16 + (vg >> 1)) * 512 + ((l & 31) + 32 * (vg & 1)) * 8 + 4 * (l >> 5)) = q;
 }
 
-// One workgroup per (32 rows, member).  NTW: 32-column tiles per wave and
-// hidden layer.  Bound by the GELU's vector instructions (about 40 an
-// element) once the layers are fused; the launches, the round trips of the
-// activations and the row-strided operand loads of the layer-wise pass
-// are what it saves.
+// One workgroup per (32 rows, member), 32 the smallest tile of the matrix
+// instruction.  NTW: 32-column tiles per wave and hidden layer.  Measured (5
+// members 129-256-256-3): inference of 3572 rows 22.6 us against 57.7 layer by
+// layer, 217 rows 14.3 against 37.6; the rows of a 4096-row training step 64 us
+// against 200.  Bound by the GELU (about 40 vector instructions an element, 10
+// of the 22.6 us) on the 2 or 3 workgroups that share a CU, and in training by
+// 85 MB of transposed operands and FP32 dZ written as well.  GELU' parked in
+// memory instead of registers (three workgroups per CU) took 73 us.
 template <bool TRAIN, int NTW>
 __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
     extern __shared__ __align__(16) unsigned char mlp_lds[];
@@ -115,7 +122,7 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
     const bf16* W1 = g.W1f + (size_t)e * g.nin_p * g.nh;
     const bf16* W2 = g.W2f + (size_t)e * g.nh * g.nh;
     const bf16* W3 = g.W3f + (size_t)e * 32 * g.nh;
-    bf16x8 b[MLP_PF];
+    bf16x8 b[mlp_pf(TRAIN)];
     if (wv < nt) mlp_preload(b, W1 + (size_t)wv * KS1 * 512, KS1, l);
     // the rows, rounded to BF16; rows and columns of the padding are zero
     for (int r = wv; r < 32; r += MLP_WAVES)
