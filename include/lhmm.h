@@ -210,24 +210,21 @@ int lhmm_micro_step_subset(lhmm_micro* m, const double* gradL, int32_t n_steps, 
  *   busy_lanes:  the search also stops, and rounds also continue, while at
  *                least this many of a wave's 64 lanes hold a neighbour
  *                (1 .. 64; 65 turns the rule off);
- *   bin_threads: threads of the per-box binning workgroup (256, 512, 1024);
+ *   bin_threads: threads of a binning workgroup (256, 512, 1024);
  *   graph_chunk: micro steps per captured HIP graph (1 .. 1000);
  *   prune:       1 skips stencil cells that lie provably beyond the cutoff
  *                (the accepted pairs and their order are unchanged), 0
  *                scans the full 27-cell stencil;
- *   fuse_bin:    1 runs the cell step and the half kick and drift inside the
- *                per-box binning workgroup (two launches fewer per step;
- *                lhmm_micro_time then reports their time under binning);
- *   groups:      1 .. 4: with fused binning, a captured step splits the
+ *   fuse_bin:    1 makes the next step's half kick and drift at the end of the
+ *                force pass and its cell beside the binning, particles staying
+ *                in cell order through a chunk of steps; 0 makes them in a
+ *                launch of their own, from and back to index order every step;
+ *   groups:      1 .. 4: with fuse_bin 1, a captured chunk splits the
  *                boxes by particle count into this many groups (the largest
  *                boxes, two thirds of the particles, in the last), each
- *                binned and force-evaluated on its own stream, so that the
- *                force pass of small boxes runs while large boxes are still
- *                being binned (1: one stream);
- *   bin_split:   0, or 256 .. 4096: with groups > 1 the group of the largest
- *                boxes is binned by several workgroups per box, over chunks
- *                of this many particles (count, scan and scatter passes), so
- *                that one box's sort is not held by one compute unit. */
+ *                on its own stream (1: one stream; small launches use one);
+ *   bin_split:   0, or 256 .. 4096: particles per binning workgroup aimed at
+ *                (0 and values above 1024 aim at 1024). */
 typedef struct {
     int32_t queue_depth;
     int32_t drain;
@@ -241,8 +238,7 @@ typedef struct {
 } lhmm_micro_config;
 
 /* Set / read the launch parameters (defaults: depth 16, drain 12; busy rule
- * off; 1024 binning threads; fused binning; two box groups; no split
- * binning (measured slower); 50-step graphs; no pruning: with
+ * off; 512 binning threads; fused steps; two box groups; 50-step graphs; no pruning: with
  * cells barely wider than the cutoff it skips little and costs more).  Set waits for the
  * engine and drops its captured graphs.  Errors: ARG. */
 int lhmm_micro_set_config(lhmm_micro* m, const lhmm_micro_config* cfg);
@@ -331,17 +327,18 @@ int lhmm_micro_prepare(lhmm_micro* m, int32_t n_steps);
 int lhmm_micro_flags(lhmm_micro* m, uint32_t* flags_out, int32_t clear);
 
 /* Kernels of one micro step, in launch order (indices of lhmm_micro_time). */
-#define LHMM_K_CELL 0       /* cell deformation, reduction, grid (per box)   */
-#define LHMM_K_KICK_DRIFT 1 /* half kick, drift, wrap, cell index            */
-#define LHMM_K_BIN 2        /* counting sort by cell (per box)               */
-#define LHMM_K_FORCES 3     /* DPD pair forces, FENE bonds, virial           */
+#define LHMM_K_CELL 0       /* cell deformation (inside the others: 0)       */
+#define LHMM_K_KICK_DRIFT 1 /* first step of a chunk: cell, half kick, drift */
+#define LHMM_K_BIN 2        /* counting sort by cell; the next step's cell   */
+#define LHMM_K_FORCES 3     /* DPD pair forces, FENE bonds, virial, kicks,   */
+                            /* the next step's drift                         */
 #define LHMM_K_KICK2 4      /* second half kick (inside the force kernel: 0) */
-#define LHMM_K_STRESS 5     /* per-box stress of the step, accumulation      */
+#define LHMM_K_STRESS 5     /* stresses of a window of steps (up to 50)      */
 #define LHMM_N_KERNELS 6
 
 /* Advance like lhmm_micro_step (same kernels, grids and state update) but
  * launch eagerly with a HIP event pair around every kernel on the engine's
- * stream, and return each kernel's mean duration in milliseconds.
+ * stream, and return each kernel's duration in milliseconds per step.
  *   gradL: DEVICE pointer n_boxes x 9; avg_ms: host LHMM_N_KERNELS doubles;
  *   stress_out: DEVICE pointer n_boxes x 6 (may be NULL).
  * Synchronous.  Errors: ARG, STATE, HIP. */

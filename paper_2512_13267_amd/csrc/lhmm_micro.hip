@@ -1,28 +1,31 @@
 // lhmm_micro.hip -- gfx950 kernels and runtime of the batched micro-DPD
 // engine behind include/lhmm.h.
 //
-// One step of every box (velocity-Verlet of the micro-scale equation of
-// motion, Eq. motion, in a periodic cell deformed by the box's velocity
-// gradient; Appendix "Detailed Coupling Protocol", Step 3) is three launches
-// over a flattened index of all boxes (five with unfused binning):
-//   k_bin_box      one workgroup per box: the cell step (FP64: mid-step
-//                  cell inverse, deformation h <- exp(L dt) h,
-//                  Lagrange-Gauss reduction of the in-plane basis, cell
-//                  grid, width guard), the half kick c += dt/2 (F/m - L c)
-//                  and drift of the fractional coordinates with the
-//                  mid-step cell (remap by the reduction, wrap, cell index),
-//                  then a counting sort of the particles by cell in LDS with
-//                  each cell sorted by id so every sum has a fixed order
-//                  (k_cell_step and k_kick_drift run the first two parts as
-//                  separate launches when binning is not fused);
+// A step of every box (velocity-Verlet of the micro-scale equation of motion,
+// Eq. motion, in a periodic cell deformed by the box's velocity gradient;
+// Appendix "Detailed Coupling Protocol", Step 3) is two launches over a
+// flattened index of all boxes:
+//   k_bin          a counting sort of the particles by cell, a workgroup per
+//                  slab of a box's cell columns, each cell in index order so
+//                  every sum has a fixed order; beside it the next step's cell
+//                  (FP64: mid-step cell inverse, deformation h <- exp(L dt) h,
+//                  Lagrange-Gauss reduction of the in-plane basis, cell grid,
+//                  width guard);
 //   k_forces       per particle: conservative + dissipative + random pair
 //                  forces (Eqs. conservative, dissipative, random) over the
 //                  neighbour cells, FENE springs (Eq. fene_force), the
-//                  second half kick with the final force, and the block's
-//                  virial and kinetic partial sums in FP64;
-//   k_box_stress   one wave per box: virial stress of the step (Eqs.
-//                  IKtotal, kinetic_stress, potential_stress with a uniform
-//                  weight over the cell), accumulated over the call.
+//                  second half kick with the final force, the block's virial
+//                  and kinetic partial sums in FP64, and the next step's half
+//                  kick c += dt/2 (F/m - L c) and drift of the fractional
+//                  coordinates with the mid-step cell (remap by the reduction,
+//                  wrap, cell index), written in cell order for the next
+//                  binning.  k_forces_wide does the same with sixteen lanes
+//                  per particle, for launches too small to fill the chip.
+// Steps come in chunks (captured in HIP graphs): k_begin_chunk takes the
+// particles from their arrays in index order through the first half kick and
+// drift, the last step's force pass puts them back, and k_flush reduces the
+// window's partial sums to the boxes' stresses (Eqs. IKtotal, kinetic_stress,
+// potential_stress with a uniform weight over the cell).
 // A box may instead be a micro-domain with boundary regions (Sec.
 // "Macro-to-Micro Coupling", Tab. 2): its cell stays fixed, the particles of
 // the boundary-condition ring relax toward the imposed field v' = G r' of
@@ -32,8 +35,7 @@
 // virial weighted by the fraction of its segment inside the core).
 // The per-particle kernels run over work blocks of BS particles; a block
 // never straddles two boxes, so per-box quantities are uniform in a block
-// and reductions stay deterministic.  The step loop is captured in HIP
-// graphs.  Particle state is single or double precision (template
+// and reductions stay deterministic.  Particle state is single or double precision (template
 // parameter); cells, gradients and stress sums are always double.
 #include <hip/hip_runtime.h>
 
@@ -54,10 +56,11 @@
 namespace {
 
 constexpr int BS = 256;                 // particles per work block
-constexpr int BIN_THREADS_MAX = 1024;   // largest binning workgroup (256, 512 or 1024 threads)
-constexpr int MAX_CELLS_PER_BOX = 17424;  // binning LDS: cell starts and three per-column offsets (136 KiB)
+constexpr int MAX_CELLS_PER_BOX = 17424;
 constexpr int GRAPH_CHUNK = 50;         // default steps per captured graph
 constexpr int MAX_GROUPS = 4;           // overlapped box groups of a captured step
+constexpr int MAX_WINDOW = 50;          // steps whose partial sums are kept before a flush
+constexpr size_t PART_BYTES = size_t(64) << 20;  // their memory, where more than one step would take more
 constexpr int ACC = 36;                 // per-box stress sums: kinetic, pair, FENE, C, D, R (6 each)
 
 thread_local std::string g_err;
@@ -82,16 +85,17 @@ struct BoxInfo {
     int off;       // first particle (global index)
     int n;         // particles
     int n_beads;   // n_chains * chain_len
-    int cell_off;  // first slot in cell_start (cap + 1 slots per box)
     int cell_cap;  // cell capacity
     int gcell_off; // first slot in gcell_start (2 cap + 1 slots per box)
     int zsub;      // cells per cutoff along z (1 or 2): the z range of a stencil row is 2 zsub + 1 cells
     int blk_off;   // first work block
     int nblk;      // work blocks
+    int slab_off;  // first slab of the binning
+    int nslab;     // slabs
     unsigned rng_id;  // box word of the random-force counter
 };
 
-struct BoxDyn {  // per-box FP64 state, rewritten every step
+struct BoxDyn {  // per-box FP64 state, rewritten every step; two slots (see Step)
     double h[9];
     double L[9];
     double E[9];
@@ -111,20 +115,32 @@ struct BoxDyn {  // per-box FP64 state, rewritten every step
 struct Ctx {
     int n_total, n_boxes, n_blocks, chain_len;
     const BoxInfo* box;
-    BoxDyn* dyn;
+    BoxDyn* dyn;  // 2 x n_boxes: slot 0 holds the state between chunks
     unsigned* flags;
     const int* blk_box;
     const int* blk_first;
+    const int* slab_box;
     // selection: when sel is set, per-box kernels run over the n_sel boxes
-    // sel[0..n_sel) and per-block kernels over the work blocks blk_list[..]
+    // sel[0..n_sel), per-block kernels over the work blocks blk_list[..] (those
+    // of sel[q] from blk0[q] on) and the binning over the slabs slab_list[..]
     const int* sel;
+    const int* blk0;
     const int* blk_list;
+    const int* slab_list;
     int n_sel;
     void* s;  // SoA: component k of particle i at [k * n_total + i]
     void* c;
     void* f;
-    int* pcell;
-    int* cell_start;
+    // inside a chunk: records (s, index) by index for the bonds (every
+    // particle's at the first step, the beads' later) and in the last cell
+    // order, two slots each (one read, one written by a force pass); (c, cell)
+    // and the cell alone in the source order of the next binning; each
+    // cell-order position's source position
+    void* sid[2];
+    void* sord[2];
+    void* cord;
+    int* key;
+    int* perm;
     // per box, cell-sorted pairs of records: (x, y, z, local index), r = h s,
     // then (cx, cy, cz, local index), 2 x 4 reals per particle (one scattered
     // 32-byte store in the binning, one 32-byte segment per neighbour in the
@@ -139,11 +155,14 @@ struct Ctx {
     // 1 below, 2 above), r = h s; padded by four records.
     int* gcell_start;
     void* srec;
-    double* part_vir;   // n_blocks x pv_stride: pair virial, FENE virial (+ C, D, R parts)
-    int pv_stride;      // 12, or 30 when the conservative, dissipative and random parts are kept
+    // partial sums of the window's steps: part_step per step, nv per work block
+    // (or per sixteen particles: k_forces_wide) in the launch's order: pair
+    // virial 6, FENE virial 6, ordered pairs, kinetic 6 (+ C, D, R virials)
+    double* part;
+    size_t part_step;
+    int nv;             // 19, or 37 when the conservative, dissipative and random parts are kept
+    double* vol;        // n_boxes per step of the window
     double vir_scale;   // 1 when each pair is evaluated once, 1/2 when twice
-    double* part_kin;   // n_blocks x 6
-    unsigned* part_pairs;  // n_blocks: ordered pairs within the cutoff
     double* acc;        // n_boxes x ACC: kinetic, pair, FENE, C, D, R stress sums
     unsigned long long* acc_pairs;  // n_boxes
     unsigned long long* tot_pairs;  // n_boxes, every step since the engine was created
@@ -151,6 +170,19 @@ struct Ctx {
     double a, gamma, sigma, rdt, dt, mass, inv_mass, rc, rc2, H, inv_R02;
     double ou_damp, ou_amp;  // ring relaxation over half a step: exp(-zeta dt/2), sqrt(kBT/m (1 - exp(-zeta dt)))
     unsigned key0, key1;
+};
+
+// One step's launches inside a chunk.  A step's cell is in dyn slot `slot`, the
+// next one's in the other; its own positions come from sid[slot] (first) or
+// sord[slot], its bond partners' from sid[slot].
+struct Step {
+    int slot;
+    int first;  // first step of the chunk
+    int more;   // another step of the chunk follows
+    int kick;   // 0: forces only (no second half kick)
+    int w;      // place in the window of partial sums
+    int k;      // this step's random-force counter is *C.step + k
+    int part0;  // first work block of the launch in the partial sums
 };
 
 // ---------------------------------------------------------------------------
@@ -430,25 +462,50 @@ __host__ __device__ inline int reduce_planar(double* h, int* U) {
 // Reductions
 // ---------------------------------------------------------------------------
 
-// Sum NV doubles over the workgroup (BS threads); thread 0 returns the sums.
+// One level of a wave reduction of N values per lane: lanes o apart add, and
+// each keeps half of the values (the lane with the bit set the upper half).
+// idx and n follow which values a lane still holds.
+template <int N>
+__device__ __forceinline__ void halve(double (&v)[N], int o, bool up, int& idx, int& n, double (&out)[(N + 1) / 2]) {
+    constexpr int M = (N + 1) / 2;
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        const double hi = k + M < N ? v[k + M] : 0.0;
+        const double send = up ? v[k] : hi, keep = up ? hi : v[k];
+        out[k] = keep + __shfl_xor(send, o, 64);
+    }
+    if (up) {
+        idx += M;
+        n -= M;
+    } else {
+        n = min(n, M);
+    }
+}
+
+// Sums of NV doubles over the workgroup (BS threads) to out[0 .. NV).  Lanes
+// 32, 16, .. 1 apart are added in that order and the waves after them in
+// order; each level halves the values a lane carries on, which takes about
+// 22 exchanges instead of 6 NV for the same sums.
 template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double* sh /* NV * (BS/64) */) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k)
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+__device__ __forceinline__ void block_sum(double (&v)[NV], double* sh /* NV * (BS/64) */, double* out) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) sh[wv * NV + k] = v[k];
+    int idx = 0, n = NV;
+    constexpr int N1 = (NV + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2, N4 = (N3 + 1) / 2, N5 = (N4 + 1) / 2,
+                  N6 = (N5 + 1) / 2;
+    double a1[N1], a2[N2], a3[N3], a4[N4], a5[N5], a6[N6];
+    halve<NV>(v, 32, lane & 32, idx, n, a1);
+    halve<N1>(a1, 16, lane & 16, idx, n, a2);
+    halve<N2>(a2, 8, lane & 8, idx, n, a3);
+    halve<N3>(a3, 4, lane & 4, idx, n, a4);
+    halve<N4>(a4, 2, lane & 2, idx, n, a5);
+    halve<N5>(a5, 1, lane & 1, idx, n, a6);
+    static_assert(N6 == 1, "one value per lane at the end");
+    if (n > 0) sh[wv * NV + idx] = a6[0];
     __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            double t = 0.0;
-            for (int w = 0; w < BS / 64; ++w) t += sh[w * NV + k];
-            v[k] = t;
-        }
+    if ((int)threadIdx.x < NV) {
+        double t = 0.0;
+        for (int w = 0; w < BS / 64; ++w) t += sh[w * NV + threadIdx.x];
+        out[threadIdx.x] = t;
     }
 }
 
@@ -466,105 +523,102 @@ __device__ __forceinline__ int xcd_local_work(int b, int n) {
     return x * per + min(x, rem) + l;
 }
 
-// Per call: take each box's gradient (device array n_boxes x 9), validate,
-// and form exp(L dt), exp(L dt/2).
-__global__ void k_setup_call(Ctx C, const double* __restrict__ gradL) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= C.n_boxes) return;
-    BoxDyn& D = C.dyn[b];
-    double L[9];
-    for (int k = 0; k < 9; ++k) L[k] = gradL[9 * b + k];
-    if (!gradient_ok(L)) {
-        for (int k = 0; k < 9; ++k) L[k] = 0.0;
-        C.flags[b] |= LHMM_FLAG_ARG;
-    }
-    if (D.hc > 0.0) {  // boundary regions: the gradient drives the ring, the cell stays fixed
-        D.G[0] = L[0]; D.G[1] = L[1]; D.G[2] = L[3]; D.G[3] = L[4];
-        for (int k = 0; k < 9; ++k) L[k] = 0.0;
-    }
-    for (int k = 0; k < 9; ++k) D.L[k] = L[k];
-    expm_planar(L, C.dt, D.E);
-    expm_planar(L, 0.5 * C.dt, D.Eh);
-}
+// Per call.  The first n_mean workgroups remove their box's mean peculiar
+// velocity (every box, or every selected one): the pair forces cancel, so the
+// mean obeys d<c>/dt = -L <c>; a flow that compresses the box amplifies it,
+// and the rounding of the two-sided single-precision pair forces seeds it.
+// The micro-domain moves with its macro particle, so its mean is zero.  The
+// remaining workgroups, a thread per box, take the box's gradient (device
+// array n_boxes x 9), validate it, form exp(L dt) and exp(L dt/2), and clear
+// the call's sums.  One launch: the two parts touch different data.
+constexpr int CALL_THREADS = 1024;
 
-// Remove each box's mean peculiar velocity (one workgroup per box, or per
-// selected box).  The pair forces cancel, so the mean obeys
-// d<c>/dt = -L <c>: a flow that compresses the box amplifies it, and the
-// rounding of the two-sided single-precision pair forces seeds it.  The
-// micro-domain moves with its macro particle, so its mean is zero.
 template <typename real>
-__global__ __launch_bounds__(256) void k_remove_mean(Ctx C) {
-    const int b = C.sel ? C.sel[blockIdx.x] : blockIdx.x;
+__global__ __launch_bounds__(CALL_THREADS) void k_begin_call(Ctx C, const double* __restrict__ gradL, int n_mean) {
+    if ((int)blockIdx.x >= n_mean) {
+        const int b = (blockIdx.x - n_mean) * 64 + threadIdx.x / 16, sub = threadIdx.x % 16;
+        if (b >= C.n_boxes) return;
+        for (int q = sub; q < ACC; q += 16) C.acc[ACC * (size_t)b + q] = 0.0;
+        if (sub != 0) return;
+        C.acc_pairs[b] = 0ull;
+        BoxDyn& D = C.dyn[b];
+        double L[9];
+        for (int k = 0; k < 9; ++k) L[k] = gradL[9 * (size_t)b + k];
+        if (!gradient_ok(L)) {
+            for (int k = 0; k < 9; ++k) L[k] = 0.0;
+            C.flags[b] |= LHMM_FLAG_ARG;
+        }
+        if (D.hc > 0.0) {  // boundary regions: the gradient drives the ring, the cell stays fixed
+            D.G[0] = L[0]; D.G[1] = L[1]; D.G[2] = L[3]; D.G[3] = L[4];
+            for (int k = 0; k < 9; ++k) L[k] = 0.0;
+        }
+        for (int k = 0; k < 9; ++k) D.L[k] = L[k];
+        expm_planar(L, C.dt, D.E);
+        expm_planar(L, 0.5 * C.dt, D.Eh);
+        return;
+    }
+    const int b = C.sel ? C.sel[blockIdx.x] : (int)blockIdx.x;
     const BoxInfo B = C.box[b];
     const int N = C.n_total;
-    real* c = (real*)C.c;
-    __shared__ double red[3][256];
+    real* c = (real*)C.c + B.off;
+    __shared__ double red[3][CALL_THREADS / 64];
+    // thread t adds particles t, t + 1024, ... in that order, four particles'
+    // loads in flight; then a fixed tree over the wave and the waves in order
     double acc[3] = {0.0, 0.0, 0.0};
-    // thread t adds particles t, t + 256, ... in that order; four particles'
-    // loads are issued before their additions
-    const real* cb = c + B.off;
     int i = threadIdx.x;
-    for (; i + 3 * 256 < B.n; i += 4 * 256) {
+    for (; i + 3 * CALL_THREADS < B.n; i += 4 * CALL_THREADS) {
         real v[4][3];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) v[u][k] = cb[(long)k * N + i + u * 256];
+            for (int k = 0; k < 3; ++k) v[u][k] = c[(long)k * N + i + u * CALL_THREADS];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int k = 0; k < 3; ++k) acc[k] += (double)v[u][k];
     }
-    for (; i < B.n; i += 256)
-        for (int k = 0; k < 3; ++k) acc[k] += (double)cb[(long)k * N + i];
-    for (int k = 0; k < 3; ++k) red[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
-        __syncthreads();
+    for (; i < B.n; i += CALL_THREADS)
+        for (int k = 0; k < 3; ++k) acc[k] += (double)c[(long)k * N + i];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc[k] += __shfl_xor(acc[k], o, 64);
+        if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = acc[k];
     }
-    const real mean[3] = {(real)(red[0][0] / B.n), (real)(red[1][0] / B.n), (real)(red[2][0] / B.n)};
-    real* cw = c + B.off;
+    __syncthreads();
+    real mean[3];
+    for (int k = 0; k < 3; ++k) {
+        double t = 0.0;
+        for (int w = 0; w < CALL_THREADS / 64; ++w) t += red[k][w];
+        mean[k] = (real)(t / B.n);
+    }
 #pragma unroll 4
-    for (int j = threadIdx.x; j < B.n; j += 256)
-        for (int k = 0; k < 3; ++k) cw[(long)k * N + j] -= mean[k];
+    for (int j = threadIdx.x; j < B.n; j += CALL_THREADS)
+        for (int k = 0; k < 3; ++k) c[(long)k * N + j] -= mean[k];
 }
 
-__global__ void k_zero_acc(Ctx C) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < ACC * C.n_boxes) C.acc[t] = 0.0;
-    if (t < C.n_boxes) C.acc_pairs[t] = 0ull;
-}
-
-// One thread per box.  advance = 1: mid-step inverse, deformation and
-// reduction of this step; advance = 0: grid for the current cell only.
-__device__ void cell_step_box(const Ctx& C, int b, int advance);
-
-__global__ void k_cell_step(Ctx C, int advance) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= (C.sel ? C.n_sel : C.n_boxes)) return;
-    cell_step_box(C, C.sel ? C.sel[q] : q, advance);
-}
-
-__device__ void cell_step_box(const Ctx& C, int b, int advance) {
-    BoxDyn& D = C.dyn[b];
+// One box's cell from S to D (which may not alias).  advance = 1: mid-step
+// inverse, deformation and reduction of a step; advance = 0: grid of the
+// current cell only.  raise: the caller raises the box's cell flags (one
+// caller per box and step).
+__device__ void cell_step_box(const Ctx& C, int b, const BoxDyn& S, BoxDyn& D, int advance, bool raise) {
+    D = S;
     double h[9];
-    for (int k = 0; k < 9; ++k) h[k] = D.h[k];
+    for (int k = 0; k < 9; ++k) h[k] = S.h[k];
     int U[4] = {1, 0, 0, 1};
     int changed = 0;
     if (advance) {
         double hm[9];
-        m3_mul(D.Eh, h, hm);
+        m3_mul(S.Eh, h, hm);
         m3_inv(hm, D.hmi);
-        m3_mul(D.E, h, h);
+        m3_mul(S.E, h, h);
         changed = reduce_planar(h, U);
         for (int k = 0; k < 9; ++k) D.h[k] = h[k];
     }
     for (int k = 0; k < 4; ++k) D.U[k] = U[k];
     D.changed = changed;
     // the stress is averaged over the core of a boundary-region box
-    D.vol = D.hc > 0.0 ? 4.0 * D.hc * D.hc * h[8] : fabs(m3_det(h));
+    D.vol = S.hc > 0.0 ? 4.0 * S.hc * S.hc * h[8] : fabs(m3_det(h));
     double w[3];
     m3_widths(h, w);
     int nc[3];
@@ -586,8 +640,10 @@ __device__ void cell_step_box(const Ctx& C, int b, int advance) {
         }
         nc[a] -= 1;
     }
-    if (narrow) C.flags[b] |= LHMM_FLAG_CELL;
-    if (!(fmin(fmin(w[0], w[1]), w[2]) >= LHMM_THIN_WIDTH * C.rc)) C.flags[b] |= LHMM_FLAG_THIN;
+    if (raise) {
+        if (narrow) C.flags[b] |= LHMM_FLAG_CELL;
+        if (!(fmin(fmin(w[0], w[1]), w[2]) >= LHMM_THIN_WIDTH * C.rc)) C.flags[b] |= LHMM_FLAG_THIN;
+    }
     D.nc[0] = nc[0]; D.nc[1] = nc[1]; D.nc[2] = nc[2];
 }
 
@@ -630,9 +686,9 @@ __device__ __forceinline__ void ring_relax(real x, real y, real hc, real hb, con
     philox4x32_10(x0, x1, x2, x3, k0, k1);
     real n0, n1;
     box_muller2<real>(x0, x1, n0, n1);
-    const real u0 = G[0] * x + G[1] * y, u1 = G[2] * x + G[3] * y;
-    c0 = u0 + (c0 - u0) * damp + amp * n0;
-    c1 = u1 + (c1 - u1) * damp + amp * n1;
+    const real u0 = fma(G[0], x, G[1] * y), u1 = fma(G[2], x, G[3] * y);
+    c0 = fma(amp, n0, fma(c0 - u0, damp, u0));
+    c1 = fma(amp, n1, fma(c1 - u1, damp, u1));
 }
 
 // A box's step constants for the half kick and drift, read once into
@@ -646,7 +702,7 @@ struct KickDrift {
     bool afbc;
     real hc, hb, G[4], h00, h01, h10, h11, damp, amp;
     unsigned step, box, k0, k1;
-    __device__ explicit KickDrift(const Ctx& C, const BoxDyn& D, unsigned box_rng = 0) {
+    __device__ explicit KickDrift(const Ctx& C, const BoxDyn& D, unsigned box_rng, unsigned step_made) {
         hdt = (real)(0.5 * C.dt);
         im = (real)C.inv_mass;
         dt = (real)C.dt;
@@ -660,68 +716,98 @@ struct KickDrift {
         for (int k = 0; k < 4; ++k) G[k] = (real)D.G[k];
         h00 = (real)D.h[0]; h01 = (real)D.h[1]; h10 = (real)D.h[3]; h11 = (real)D.h[4];
         damp = (real)C.ou_damp; amp = (real)C.ou_amp;
-        step = (unsigned)(*C.step + 1ull);  // the step being made
+        step = step_made;
         box = box_rng; k0 = C.key0; k1 = C.key1;
     }
 };
 
-// Half kick c += dt/2 (F/m - L c), drift of the fractional coordinate with
-// the mid-step cell, remap after a reduction, wrap (in registers).
+// Half kick c += dt/2 (F/m - L c); in-plane L: (L c)_z = 0.
 template <typename real>
+__device__ __forceinline__ void half_kick(real hdt, real im, real L0, real L1, real L3, real L4, real f0, real f1,
+                                          real f2, real& c0, real& c1, real& c2) {
+    const real lc0 = fma(L0, c0, L1 * c1), lc1 = fma(L3, c0, L4 * c1);
+    c0 = fma(hdt, fma(f0, im, -lc0), c0);
+    c1 = fma(hdt, fma(f1, im, -lc1), c1);
+    c2 = fma(hdt, f2 * im, c2);
+}
+
+// Half kick, drift of the fractional coordinate with
+// the mid-step cell, remap after a reduction, wrap (in registers).  AF:
+// the box may have boundary regions.  The integration's roundings are fixed by
+// explicit fmas (here, in half_kick and in bond_forces): the launches that make
+// a step, fused or not, then agree to the bit.
+template <typename real, bool AF>
 __device__ __forceinline__ void kick_drift(const KickDrift<real>& K, real (&sv)[3], real (&cv)[3], const real (&fv)[3],
                                            int id) {
-    // in-plane L: (L c)_z = 0
-    const real lc0 = K.L0 * cv[0] + K.L1 * cv[1], lc1 = K.L3 * cv[0] + K.L4 * cv[1];
-    cv[0] += K.hdt * (fv[0] * K.im - lc0);
-    cv[1] += K.hdt * (fv[1] * K.im - lc1);
-    cv[2] += K.hdt * (fv[2] * K.im);
-    if (K.afbc) {
-        const real x = K.h00 * (sv[0] - (real)0.5) + K.h01 * (sv[1] - (real)0.5);
-        const real y = K.h10 * (sv[0] - (real)0.5) + K.h11 * (sv[1] - (real)0.5);
+    half_kick<real>(K.hdt, K.im, K.L0, K.L1, K.L3, K.L4, fv[0], fv[1], fv[2], cv[0], cv[1], cv[2]);
+    if (AF && K.afbc) {
+        const real x = fma(K.h00, sv[0] - (real)0.5, K.h01 * (sv[1] - (real)0.5));
+        const real y = fma(K.h10, sv[0] - (real)0.5, K.h11 * (sv[1] - (real)0.5));
         ring_relax<real>(x, y, K.hc, K.hb, K.G, K.damp, K.amp, (unsigned)id, 0u, K.step, K.box, K.k0, K.k1, cv[0], cv[1]);
     }
-    real s0 = sv[0] + K.dt * (K.M[0] * cv[0] + K.M[1] * cv[1] + K.M[2] * cv[2]);
-    real s1 = sv[1] + K.dt * (K.M[3] * cv[0] + K.M[4] * cv[1] + K.M[5] * cv[2]);
-    const real s2 = sv[2] + K.dt * (K.M[6] * cv[0] + K.M[7] * cv[1] + K.M[8] * cv[2]);
+    auto row = [&](int k) { return fma(K.M[k + 2], cv[2], fma(K.M[k + 1], cv[1], K.M[k] * cv[0])); };
+    real s0 = fma(K.dt, row(0), sv[0]);
+    real s1 = fma(K.dt, row(3), sv[1]);
+    const real s2 = fma(K.dt, row(6), sv[2]);
     if (K.changed) {  // s <- U^{-1} s in the plane, U^{-1} = [[u11, -u01], [-u10, u00]]
         const real x = s0, y = s1;
-        s0 = (real)K.U[3] * x - (real)K.U[1] * y;
-        s1 = -(real)K.U[2] * x + (real)K.U[0] * y;
+        s0 = fma((real)K.U[3], x, -((real)K.U[1] * y));
+        s1 = fma((real)K.U[0], y, -((real)K.U[2] * x));
     }
     sv[0] = wrap01(s0); sv[1] = wrap01(s1); sv[2] = wrap01(s2);
 }
 
-// Half kick and drift of particle i (advance = 1) and its cell; returns the
-// cell (stored to pcell when store_cell is set).
+// Position r = h s of a fractional coordinate in the in-plane cell, with a
+// fixed rounding sequence (the binning and the force kernel must agree to
+// the bit: a particle finds itself at distance exactly zero).
 template <typename real>
-__device__ __forceinline__ int kick_drift_particle(const Ctx& C, const KickDrift<real>& K, int i, int local, int advance,
-                                                   bool store_cell = true) {
-    const int N = C.n_total;
-    real* s = (real*)C.s;
-    real* c = (real*)C.c;
-    const real* f = (const real*)C.f;
-    real sv[3] = {s[i], s[N + i], s[2 * N + i]};
-    if (advance) {
-        real cv[3] = {c[i], c[N + i], c[2 * N + i]};
-        const real fv[3] = {f[i], f[N + i], f[2 * N + i]};
-        kick_drift<real>(K, sv, cv, fv, local);
-        c[i] = cv[0]; c[N + i] = cv[1]; c[2 * N + i] = cv[2];
-        s[i] = sv[0]; s[N + i] = sv[1]; s[2 * N + i] = sv[2];
-    }
-    const int cell = cell_of(sv[0], sv[1], sv[2], K.nc);
-    if (store_cell) C.pcell[i] = cell;
-    return cell;
+__device__ __forceinline__ void cell_position(real s0, real s1, real s2, real h00, real h01, real h10, real h11,
+                                              real h22, real& x, real& y, real& z) {
+    x = fma(h01, s1, h00 * s0);
+    y = fma(h11, s1, h10 * s0);
+    z = h22 * s2;
 }
 
+// First launch of a chunk of steps, per work block: the box's cell step from
+// slot 0 to slot 1 (by the block's first thread; the box's first block stores
+// it), then, from the arrays in index order, the first step's half kick and
+// drift (advance = 1) and every particle's records by index: (s, index) in
+// sid[1], (c, cell) in cord, and its cell in key.
 template <typename real>
-__global__ __launch_bounds__(BS) void k_kick_drift(Ctx C, int advance) {
+__global__ __launch_bounds__(BS) void k_begin_chunk(Ctx C, int koff, int advance) {
+    using R = Rec<real>;
+    __shared__ BoxDyn D;
     const int blk = C.blk_list ? C.blk_list[blockIdx.x] : (int)blockIdx.x;
     const int b = C.blk_box[blk];
     const BoxInfo B = C.box[b];
-    const int i = C.blk_first[blk] + (int)threadIdx.x;
-    if (i >= B.off + B.n) return;
-    const KickDrift<real> K(C, C.dyn[b], B.rng_id);
-    kick_drift_particle<real>(C, K, i, i - B.off, advance);
+    const bool first = blk == B.blk_off;
+    const int i = C.blk_first[blk] + (int)threadIdx.x, N = C.n_total;
+    const bool act = i < B.off + B.n;
+    const real* s = (const real*)C.s;
+    const real* c = (const real*)C.c;
+    const real* f = (const real*)C.f;
+    real sv[3] = {0, 0, 0}, cv[3] = {0, 0, 0}, fv[3] = {0, 0, 0};
+    if (act)
+        for (int a = 0; a < 3; ++a) {
+            sv[a] = s[(size_t)a * N + i];
+            cv[a] = c[(size_t)a * N + i];
+            fv[a] = f[(size_t)a * N + i];
+        }
+    if (threadIdx.x == 0) cell_step_box(C, b, C.dyn[b], D, advance, first);
+    __syncthreads();
+    if (first)
+        for (int q = threadIdx.x; q < (int)(sizeof(BoxDyn) / sizeof(int)); q += BS)
+            ((int*)&C.dyn[(size_t)C.n_boxes + b])[q] = ((const int*)&D)[q];
+    if (!act) return;
+    const int local = i - B.off;
+    if (advance) {
+        const KickDrift<real> K(C, D, B.rng_id, (unsigned)(*C.step + (unsigned long long)koff + 1ull));
+        kick_drift<real, true>(K, sv, cv, fv, local);
+    }
+    const int cell = cell_of(sv[0], sv[1], sv[2], D.nc);
+    ((typename R::T*)C.sid[1])[i] = R::make(sv[0], sv[1], sv[2], local);
+    ((typename R::T*)C.cord)[i] = R::make(cv[0], cv[1], cv[2], cell);
+    C.key[i] = cell;
 }
 
 // Exclusive scan over k in [0, n) of val(k) by a workgroup of BT threads:
@@ -757,51 +843,114 @@ __device__ __forceinline__ void block_scan(int n, int* wsum /* BT / 64 */, Val v
     if (threadIdx.x == 0) out(n, total);
 }
 
-// Position r = h s of a fractional coordinate in the in-plane cell, with a
-// fixed rounding sequence (the binning and the force kernel must agree to
-// the bit: a particle finds itself at distance exactly zero).
-template <typename real>
-__device__ __forceinline__ void cell_position(real s0, real s1, real s2, real h00, real h01, real h10, real h11,
-                                              real h22, real& x, real& y, real& z) {
-    x = fma(h01, s1, h00 * s0);
-    y = fma(h11, s1, h10 * s0);
-    z = h22 * s2;
-}
+// Binning: a counting sort of every box's particles by cell, each cell in
+// index order so that all later sums have a fixed order.  A box is cut into
+// slabs of consecutive cell columns (about SLAB_TARGET particles each), one
+// workgroup per slab and no exchange between them: every workgroup reads the
+// cells of all its box's particles (4 bytes each), counting those in earlier
+// slabs (its base position, and the z images stored before it in the search
+// layout) and, per cell, those in its own; then it ranks and moves its own
+// particles only.  The source records are in the last step's cell order (in
+// index order at a chunk's first step), so a wave's loads and stores fall on
+// neighbouring records.  Written per particle: (x, y, z, index), (c, index) in
+// cell order, the source position in perm, and (x, y, z, cell-order position)
+// in the search layout, once more for the images of the bottom and top cells.
+//
+// One workgroup per box (the earlier form) took 19 us for 3000 particles,
+// 67 us for a batch with boxes of 1.5k to 12k and 160 us for 23k, which did
+// not fit its LDS; the largest box set the time.  See the table of the design
+// notes for the present times.
+//
+// A slab holding more than SLAB_CAP particles (a very uneven density) orders
+// its cells in global memory instead; the result is the same.
+//
+// The first n_cell workgroups, a thread per box, make the next step's cell
+// (slot of this step -> the other slot) and note this step's volume.
+constexpr int SLAB_TARGET = 1024;  // particles per slab
+constexpr int SLAB_CAP = 2048;     // particles a slab can order in LDS
+constexpr int SLAB_CELLS = 4096;   // a box has at least cells / SLAB_CELLS slabs
 
-// From the cell counts cnt[0 .. ncell) of box b (LDS): the cell starts
-// (cell_start and cnt[k] <- start of cell k, cnt[ncell] <- n), then the
-// search layout's starts (gcell_start) and every column's offsets from cell
-// order to its three segments of the search layout (col_off: the column's
-// cells, lo_off: the image of its top zsub cells below it, hi_off: the image
-// of its bottom zsub cells above it).  Ends with a barrier.
-template <int BT>
-__device__ void search_layout(const Ctx& C, const BoxInfo& B, const BoxDyn& D, int ncell, int* cnt, int* col_off,
-                              int* lo_off, int* hi_off, int* wsum) {
-    int* start = C.cell_start + B.cell_off;
-    int* gstart = C.gcell_start + B.gcell_off;
-    block_scan<BT>(ncell, wsum, [&](int k) { return cnt[k]; }, [&](int k, int excl) {
-        start[k] = excl;
-        cnt[k] = excl;
-    });
-    __syncthreads();
+template <typename real, int T>
+__global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_cells, int lds_cols) {
+    using R = Rec<real>;
+    using V4 = typename R::T;
+    constexpr int PER = SLAB_CAP / T;
+    extern __shared__ int lds[];
+    __shared__ int wsum[T / 64];
+    __shared__ int base[3];  // particles and images before the slab, images in it
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < n_cell) {
+        const int q = blockIdx.x * T + tid;
+        if (q >= (C.sel ? C.n_sel : C.n_boxes)) return;
+        const int b = C.sel ? C.sel[q] : q;
+        const BoxDyn& S = C.dyn[(size_t)A.slot * C.n_boxes + b];
+        C.vol[(size_t)A.w * C.n_boxes + b] = S.vol;
+        if (A.more) cell_step_box(C, b, S, C.dyn[(size_t)(A.slot ^ 1) * C.n_boxes + b], 1, true);
+        return;
+    }
+    int* cnt = lds;                  // counts, starts, then ends of the slab's cells
+    int* col_off = cnt + lds_cells;  // offsets from cell order to the search layout: the column's cells,
+    int* lo_off = col_off + lds_cols;  // the image of its top cells below it,
+    int* hi_off = lo_off + lds_cols;   // the image of its bottom cells above it
+    int* ent = hi_off + lds_cols;    // SLAB_CAP: source positions by slot
+    int* lid = ent + SLAB_CAP;       // SLAB_CAP: particle indices by slot
+    int slab = xcd_local_work(blockIdx.x - n_cell, gridDim.x - n_cell);
+    if (C.slab_list) slab = C.slab_list[slab];
+    const int b = C.slab_box[slab];
+    const BoxInfo B = C.box[b];
+    const BoxDyn& D = C.dyn[(size_t)A.slot * C.n_boxes + b];
     const int n2 = D.nc[2], zs = B.zsub, gn2 = n2 + 2 * zs, ncol = D.nc[0] * D.nc[1];
-    const float inv_gn2 = 1.0f / (float)gn2;
+    const int q = slab - B.slab_off;
+    const int c0 = (int)((long long)q * ncol / B.nslab), c1 = (int)((long long)(q + 1) * ncol / B.nslab);
+    const int nc = c1 - c0, s0 = c0 * n2, s1 = c1 * n2, ncell = nc * n2;
+    if (nc == 0) return;  // fewer columns than slabs
+    for (int k = tid; k < ncell; k += T) cnt[k] = 0;
+    if (tid < 3) base[tid] = 0;
+    __syncthreads();
+    const float inv_n2 = 1.0f / (float)n2;
+    const int* key = C.key + B.off;
+    int before = 0, img = 0;
+#pragma unroll 4
+    for (int k = tid; k < B.n; k += T) {
+        const int cell = key[k];
+        if (cell < s0) {
+            const int z = cell - div_small(cell, inv_n2) * n2;
+            before += 1;
+            img += (z < zs ? 1 : 0) + (z >= n2 - zs ? 1 : 0);
+        } else if (cell < s1) {
+            atomicAdd(&cnt[cell - s0], 1);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        before += __shfl_xor(before, o, 64);
+        img += __shfl_xor(img, o, 64);
+    }
+    if ((tid & 63) == 0) {
+        atomicAdd(&base[0], before);
+        atomicAdd(&base[1], img);
+    }
+    __syncthreads();
+    before = base[0];
+    img = base[1];
+    block_scan<T>(ncell, wsum, [&](int k) { return cnt[k]; }, [&](int k, int excl) { cnt[k] = excl; });
+    __syncthreads();
+    const int total = cnt[ncell];
     // images before each column (its top and bottom zsub cells' particles
-    // appear once more), scanned over columns
-    __shared__ int n_images;
-    block_scan<BT>(
-        ncol, wsum,
+    // appear once more), scanned over the slab's columns
+    block_scan<T>(
+        nc, wsum,
         [&](int col) {
             const int k = col * n2;
             return (cnt[k + n2] - cnt[k + n2 - zs]) + (cnt[k + zs] - cnt[k]);
         },
         [&](int col, int excl) {
-            if (col == ncol) {
-                n_images = excl;
+            if (col == nc) {
+                base[2] = excl;
                 return;
             }
             const int k = col * n2;
-            const int first = cnt[k] + excl, top = cnt[k + n2] - cnt[k + n2 - zs];
+            const int first = cnt[k] + img + excl, top = cnt[k + n2] - cnt[k + n2 - zs];
             lo_off[col] = first - cnt[k + n2 - zs];
             col_off[col] = first + top - cnt[k];
             hi_off[col] = first + top + (cnt[k + n2] - cnt[k]) - cnt[k];
@@ -809,380 +958,98 @@ __device__ void search_layout(const Ctx& C, const BoxInfo& B, const BoxDyn& D, i
     __syncthreads();
     // starts of the search-layout cells: a segment's offset plus the start
     // of the cell it repeats
-    for (int g = threadIdx.x; g < ncol * gn2; g += BT) {
+    int* gstart = C.gcell_start + B.gcell_off + c0 * gn2;
+    const float inv_gn2 = 1.0f / (float)gn2;
+    for (int g = tid; g < nc * gn2; g += T) {
         const int col = div_small(g, inv_gn2), zg = g - col * gn2, k = col * n2;
-        gstart[g] = zg < zs ? lo_off[col] + cnt[k + n2 - zs + zg]
-                            : (zg < zs + n2 ? col_off[col] + cnt[k + zg - zs] : hi_off[col] + cnt[k + zg - zs - n2]);
+        gstart[g] = before + (zg < zs ? lo_off[col] + cnt[k + n2 - zs + zg]
+                                      : (zg < zs + n2 ? col_off[col] + cnt[k + zg - zs] : hi_off[col] + cnt[k + zg - zs - n2]));
     }
-    if (threadIdx.x == 0) gstart[ncol * gn2] = B.n + n_images;
-    __threadfence_block();
+    if (tid == 0 && c1 == ncol) gstart[nc * gn2] = before + total + img + base[2];
     __syncthreads();
-}
-
-// One workgroup per box: counting sort by cell in LDS, writing each
-// particle's velocity record (velocity, local index) in cell order, sorted by
-// index inside every cell so all later sums have a fixed order, and its
-// position record (position, cell-order position) in the search layout: the
-// same order per cell, plus the z images of bottom and top cells.
-// LDS (dynamic): lds_cells cell counters / starts, three arrays of
-// lds_cols column offsets (from cell order to the search layout:
-// the column's cells, the image of its top cell, the image of its bottom
-// cell), then room for lds_parts ints.  A box with at most lds_parts
-// particles is scattered as entries into LDS, each thread ranks its own
-// particles inside their cells and stores their records; a larger box
-// scatters records to global scratch and sorts them there.  Both give the
-// same records in the same order.
-//
-// fuse >= 0: the workgroup first runs the box's cell step and the half kick
-// and drift of its particles (advance = fuse), counting cells as it goes;
-// fuse < 0: k_cell_step and k_kick_drift have run.
-template <typename real, int BIN_THREADS>
-__global__ __launch_bounds__(BIN_THREADS) void k_bin_box(Ctx C, int lds_cells, int lds_cols, int lds_parts, int fuse) {
-    using R = Rec<real>;
-    extern __shared__ int lds[];
-    int* cnt = lds;
-    int* col_off = lds + lds_cells;
-    int* lo_off = col_off + lds_cols;
-    int* hi_off = lo_off + lds_cols;
-    int* lidx = hi_off + lds_cols;
-    __shared__ int wsum[BIN_THREADS / 64];
-    const int b = C.sel ? C.sel[blockIdx.x] : (int)blockIdx.x;
-    const BoxInfo B = C.box[b];
-    if (fuse >= 0) {
-        if (threadIdx.x == 0) cell_step_box(C, b, fuse);
-        __threadfence_block();
-        __syncthreads();
-    }
-    const BoxDyn& D = C.dyn[b];
-    const int ncell = D.nc[0] * D.nc[1] * D.nc[2];
-    for (int k = threadIdx.x; k < ncell; k += BIN_THREADS) cnt[k] = 0;
-    __syncthreads();
-    const int* pc = C.pcell + B.off;
-    // cells of this thread's particles k = threadIdx.x + j BIN_THREADS, kept
-    // for the scatter when the box fits the LDS path
-    constexpr int KEEP = 16384 / BIN_THREADS;
-    int mycell[KEEP];
-    const bool keep = B.n <= lds_parts && B.n <= KEEP * BIN_THREADS;
-    if (fuse >= 0) {
-        const KickDrift<real> K(C, D, B.rng_id);
-        real* s = (real*)C.s;
-        real* c = (real*)C.c;
-        const real* f = (const real*)C.f;
-        const int N = C.n_total;
-        // four particles per thread and pass: all their loads issued before
-        // any store, so the loads stay in flight together
-#pragma unroll
-        for (int j0 = 0; j0 < KEEP; j0 += 4) {
-            if ((int)threadIdx.x + j0 * BIN_THREADS >= B.n) break;
-            int cell[4];
-            real sv[4][3], cv[4][3], fv[4][3];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = (int)threadIdx.x + (j0 + u) * BIN_THREADS;
-                const int i = B.off + (k < B.n ? k : 0);
-                for (int a = 0; a < 3; ++a) {
-                    sv[u][a] = s[a * N + i];
-                    cv[u][a] = c[a * N + i];
-                    fv[u][a] = f[a * N + i];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = (int)threadIdx.x + (j0 + u) * BIN_THREADS;
-                const int i = B.off + k;
-                cell[u] = -1;
-                if (k < B.n) {
-                    if (fuse) {
-                        kick_drift<real>(K, sv[u], cv[u], fv[u], k);
-                        for (int a = 0; a < 3; ++a) {
-                            c[a * N + i] = cv[u][a];
-                            s[a * N + i] = sv[u][a];
-                        }
-                    }
-                    cell[u] = cell_of(sv[u][0], sv[u][1], sv[u][2], K.nc);
-                    if (!keep) C.pcell[i] = cell[u];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                mycell[j0 + u] = cell[u];
-                if (cell[u] >= 0) atomicAdd(&cnt[cell[u]], 1);
-            }
+    const bool fits = total <= SLAB_CAP;
+    int* perm = C.perm + B.off;
+#pragma unroll 4
+    for (int k = tid; k < B.n; k += T) {
+        const int cell = key[k];
+        if (cell >= s0 && cell < s1) {
+            const int slot = atomicAdd(&cnt[cell - s0], 1);
+            if (fits)
+                ent[slot] = k;
+            else
+                perm[before + slot] = k;
         }
-        for (int k = (int)threadIdx.x + KEEP * BIN_THREADS; k < B.n; k += BIN_THREADS)
-            atomicAdd(&cnt[kick_drift_particle<real>(C, K, B.off + k, k, fuse)], 1);
-        __threadfence_block();
-    } else {
-#pragma unroll
-        for (int j0 = 0; j0 < KEEP; j0 += 4) {
-            if ((int)threadIdx.x + j0 * BIN_THREADS >= B.n) break;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = (int)threadIdx.x + (j0 + u) * BIN_THREADS;
-                mycell[j0 + u] = k < B.n ? pc[k] : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (mycell[j0 + u] >= 0) atomicAdd(&cnt[mycell[j0 + u]], 1);
-        }
-        for (int k = (int)threadIdx.x + KEEP * BIN_THREADS; k < B.n; k += BIN_THREADS) atomicAdd(&cnt[pc[k]], 1);
     }
+    if (!fits) __threadfence_block();
     __syncthreads();
-    search_layout<BIN_THREADS>(C, B, D, ncell, cnt, col_off, lo_off, hi_off, wsum);
-    const int* start = C.cell_start + B.cell_off;
-    const int n2 = D.nc[2], zs = B.zsub;
-    typename R::T* pv = (typename R::T*)C.cell_pv + 2 * (size_t)B.off;
-    typename R::T* srec = (typename R::T*)C.srec + 2 * B.off;
-    const real* s = (const real*)C.s;
-    const real* c = (const real*)C.c;
-    const int N = C.n_total;
+    // cnt[k] now ends cell k
+    const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
+    const V4* srcC = (const V4*)C.cord + B.off;
+    V4* pv = (V4*)C.cell_pv + 2 * (size_t)B.off;
+    V4* srec = (V4*)C.srec + 2 * (size_t)B.off;
     const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4];
     const real h22 = (real)D.h[8];
-    // the position record of cell-order position q (cell `cell`) in its
-    // search-layout slot and, for the zsub bottom or top cells, its image's slot
-    const float inv_n2 = 1.0f / (float)n2;
-    auto write_search = [&](int q, int cell, real x, real y, real z) {
+    // particle `src` (records S, V) to cell-order position p (local to the slab)
+    auto store = [&](int p, int src, const V4& S, const V4& V, int cell) {
+        real x, y, z;
+        cell_position<real>(S.x, S.y, S.z, h00, h01, h10, h11, h22, x, y, z);
+        const int id = R::id(S), g = before + p;
+        pv[2 * g] = R::make(x, y, z, id);
+        pv[2 * g + 1] = R::make(V.x, V.y, V.z, id);
+        perm[g] = src;
         const int col = div_small(cell, inv_n2), zc = cell - col * n2;
-        srec[q + col_off[col]] = R::make(x, y, z, q << 5);
-        if (zc >= n2 - zs) srec[q + lo_off[col]] = R::make(x, y, z - h22, (q << 5) | 9);
-        if (zc < zs) srec[q + hi_off[col]] = R::make(x, y, z + h22, (q << 5) | 18);
+        V4* o = srec + before;
+        o[p + col_off[col]] = R::make(x, y, z, g << 5);
+        if (zc >= n2 - zs) o[p + lo_off[col]] = R::make(x, y, z - h22, (g << 5) | 9);
+        if (zc < zs) o[p + hi_off[col]] = R::make(x, y, z + h22, (g << 5) | 18);
     };
-    if (keep) {
-        // LDS entries: cell << 14 | local index (cells < 2^14, particles < 2^14)
-        int slot[KEEP];
+    if (fits) {
+        V4 S[PER], V[PER];
+        int src[PER];
 #pragma unroll
-        for (int j = 0; j < KEEP; ++j) {
-            const int k = (int)threadIdx.x + j * BIN_THREADS;
-            slot[j] = k < B.n ? atomicAdd(&cnt[mycell[j]], 1) : -1;
+        for (int u = 0; u < PER; ++u) {
+            const int slot = tid + u * T;
+            src[u] = slot < total ? ent[slot] : -1;
+            if (src[u] >= 0) {
+                S[u] = srcS[src[u]];
+                V[u] = srcC[src[u]];
+            }
         }
 #pragma unroll
-        for (int j = 0; j < KEEP; ++j)
-            if (slot[j] >= 0) lidx[slot[j]] = (mycell[j] << 14) | ((int)threadIdx.x + j * BIN_THREADS);
+        for (int u = 0; u < PER; ++u)
+            if (src[u] >= 0) lid[tid + u * T] = R::id(S[u]);
         __syncthreads();
-        // cnt[k] now ends cell k: a particle's cell-order position is its
-        // cell's start plus the number of its cell's entries with a smaller
-        // index (a few each), so every cell is in index order
+        // a particle's position is its cell's start plus the number of its
+        // cell's entries with a smaller index (a few each)
 #pragma unroll
-        for (int j = 0; j < KEEP; ++j) {
-            if (slot[j] < 0) continue;
-            const int cell = mycell[j], key = (cell << 14) | ((int)threadIdx.x + j * BIN_THREADS);
-            const int q0 = cell == 0 ? 0 : cnt[cell - 1], q1 = cnt[cell];
+        for (int u = 0; u < PER; ++u) {
+            if (src[u] < 0) continue;
+            const int cell = R::id(V[u]) - s0, id = R::id(S[u]);
+            const int p0 = cell == 0 ? 0 : cnt[cell - 1], p1 = cnt[cell];
             int rank = 0;
-            for (int q = q0; q < q1; ++q) rank += lidx[q] < key;
-            slot[j] = q0 + rank;
-        }
-        // the thread's own particles, four per pass with their (coalesced)
-        // loads in flight together, each record stored to its slot
-#pragma unroll
-        for (int j0 = 0; j0 < KEEP; j0 += 4) {
-            if ((int)threadIdx.x + j0 * BIN_THREADS >= B.n) break;
-            real v[4][6];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = (int)threadIdx.x + (j0 + u) * BIN_THREADS;
-                const int g = B.off + (k < B.n ? k : 0);
-                v[u][0] = s[g]; v[u][1] = s[N + g]; v[u][2] = s[2 * N + g];
-                v[u][3] = c[g]; v[u][4] = c[N + g]; v[u][5] = c[2 * N + g];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = (int)threadIdx.x + (j0 + u) * BIN_THREADS;
-                if (k < B.n) {
-                    const int q = slot[j0 + u];
-                    real x, y, z;
-                    cell_position<real>(v[u][0], v[u][1], v[u][2], h00, h01, h10, h11, h22, x, y, z);
-                    pv[2 * q] = R::make(x, y, z, k);
-                    pv[2 * q + 1] = R::make(v[u][3], v[u][4], v[u][5], k);
-                    write_search(q, mycell[j0 + u], x, y, z);
-                }
-            }
+            for (int p = p0; p < p1; ++p) rank += lid[p] < id;
+            store(p0 + rank, src[u], S[u], V[u], cell);
         }
         return;
     }
-    for (int k = threadIdx.x; k < B.n; k += BIN_THREADS) {
-        const int pos = atomicAdd(&cnt[pc[k]], 1);
-        const int g = B.off + k;
-        real x, y, z;
-        cell_position<real>(s[g], s[N + g], s[2 * N + g], h00, h01, h10, h11, h22, x, y, z);
-        pv[2 * pos] = R::make(x, y, z, k);
-    }
-    __threadfence_block();
-    __syncthreads();
-    for (int k = threadIdx.x; k < ncell; k += BIN_THREADS) {
-        const int q0 = start[k], q1 = start[k + 1];
-        for (int q = q0 + 1; q < q1; ++q) {  // insertion sort by index, a few entries
-            const typename R::T v = pv[2 * q];
-            const int key = R::id(v);
-            int r = q - 1;
-            while (r >= q0 && R::id(pv[2 * r]) > key) {
-                pv[2 * (r + 1)] = pv[2 * r];
+    for (int k = tid; k < ncell; k += T) {
+        const int p0 = before + (k == 0 ? 0 : cnt[k - 1]), p1 = before + cnt[k];
+        for (int p = p0 + 1; p < p1; ++p) {  // insertion sort by index
+            const int v = perm[p], id = R::id(srcS[v]);
+            int r = p - 1;
+            while (r >= p0 && R::id(srcS[perm[r]]) > id) {
+                perm[r + 1] = perm[r];
                 --r;
             }
-            pv[2 * (r + 1)] = v;
+            perm[r + 1] = v;
         }
     }
     __threadfence_block();
     __syncthreads();
-    for (int q = threadIdx.x; q < B.n; q += BIN_THREADS) {
-        const typename R::T v = pv[2 * q];
-        const int k = R::id(v), g = B.off + k;
-        pv[2 * q + 1] = R::make(c[g], c[N + g], c[2 * N + g], k);
-        write_search(q, pc[k], v.x, v.y, v.z);
-    }
-}
-
-// Binning of large boxes over several workgroups each.  The selected boxes
-// (C.sel) are cut into chunks of `chunk` consecutive particles; per step:
-//   k_cell_step (one thread per box), then
-//   k_bin_count   (one workgroup per chunk): half kick and drift of the
-//                 chunk's particles, their cells (pcell), the chunk's cell
-//                 counts (cnt, one row of `cap` ints per chunk);
-//   k_bin_scan    (one workgroup per box): the box's cell starts and search
-//                 layout from the summed counts, each chunk's first position
-//                 in every cell (off: the cell's start plus the counts of the
-//                 box's earlier chunks) and the column offsets (col);
-//   k_bin_scatter (one workgroup per chunk): each particle's position is its
-//                 chunk's offset in its cell plus the number of the chunk's
-//                 particles in that cell with a smaller index, so every cell
-//                 is in index order as in k_bin_box, and the records are
-//                 stored as k_bin_box stores them.
-// The results equal k_bin_box's bit for bit.
-struct SplitArgs {
-    const int* box_chunk0;  // n_sel + 1: first chunk of each selected box
-    const int* chunk_boxj;  // n_chunks: the selected box (index into C.sel) of each chunk
-    int* cnt;               // n_chunks x cap: the chunk's particles per cell
-    int* off;               // n_chunks x cap: the chunk's first position in each cell
-    int* col;               // n_sel x 3 colcap: col_off, lo_off, hi_off per column
-    int chunk, cap, colcap;
-};
-
-constexpr int SPLIT_BT = 1024;  // threads per workgroup of the split binning
-constexpr int SPLIT_PER = 4;    // particles per thread and chunk at most (chunk <= 4096)
-
-template <typename real>
-__global__ __launch_bounds__(SPLIT_BT) void k_bin_count(Ctx C, SplitArgs S) {
-    extern __shared__ int lds[];
-    int* cnt = lds;
-    const int k = blockIdx.x, j = S.chunk_boxj[k], b = C.sel[j];
-    const BoxInfo B = C.box[b];
-    const BoxDyn& D = C.dyn[b];
-    const int first = (k - S.box_chunk0[j]) * S.chunk, last = min(first + S.chunk, B.n);
-    const int ncell = D.nc[0] * D.nc[1] * D.nc[2];
-    for (int q = threadIdx.x; q < ncell; q += SPLIT_BT) cnt[q] = 0;
-    __syncthreads();
-    const KickDrift<real> K(C, D, B.rng_id);
-    for (int q = first + (int)threadIdx.x; q < last; q += SPLIT_BT)
-        atomicAdd(&cnt[kick_drift_particle<real>(C, K, B.off + q, q, 1)], 1);
-    __syncthreads();
-    int* out = S.cnt + (size_t)k * S.cap;
-    for (int q = threadIdx.x; q < ncell; q += SPLIT_BT) out[q] = cnt[q];
-}
-
-__global__ __launch_bounds__(SPLIT_BT) void k_bin_scan(Ctx C, SplitArgs S, int lds_cells, int lds_cols) {
-    extern __shared__ int lds[];
-    int* cnt = lds;
-    int* col_off = lds + lds_cells;
-    int* lo_off = col_off + lds_cols;
-    int* hi_off = lo_off + lds_cols;
-    __shared__ int wsum[SPLIT_BT / 64];
-    const int j = blockIdx.x, b = C.sel[j];
-    const BoxInfo B = C.box[b];
-    const BoxDyn& D = C.dyn[b];
-    const int ncell = D.nc[0] * D.nc[1] * D.nc[2];
-    const int k0 = S.box_chunk0[j], k1 = S.box_chunk0[j + 1];
-    for (int q = threadIdx.x; q < ncell; q += SPLIT_BT) {
-        int t = 0;
-        for (int k = k0; k < k1; ++k) t += S.cnt[(size_t)k * S.cap + q];
-        cnt[q] = t;
-    }
-    __syncthreads();
-    search_layout<SPLIT_BT>(C, B, D, ncell, cnt, col_off, lo_off, hi_off, wsum);
-    for (int q = threadIdx.x; q < ncell; q += SPLIT_BT) {
-        int run = cnt[q];
-        for (int k = k0; k < k1; ++k) {
-            S.off[(size_t)k * S.cap + q] = run;
-            run += S.cnt[(size_t)k * S.cap + q];
-        }
-    }
-    const int ncol = D.nc[0] * D.nc[1];
-    int* col = S.col + (size_t)j * 3 * S.colcap;
-    for (int q = threadIdx.x; q < ncol; q += SPLIT_BT) {
-        col[q] = col_off[q];
-        col[S.colcap + q] = lo_off[q];
-        col[2 * S.colcap + q] = hi_off[q];
-    }
-}
-
-template <typename real>
-__global__ __launch_bounds__(SPLIT_BT) void k_bin_scatter(Ctx C, SplitArgs S) {
-    using R = Rec<real>;
-    extern __shared__ int lds[];
-    int* lst = lds;          // cap: the chunk's local cell starts, then ends
-    int* ent = lds + S.cap;  // chunk: local indices in local cell order
-    __shared__ int wsum[SPLIT_BT / 64];
-    const int k = blockIdx.x, j = S.chunk_boxj[k], b = C.sel[j];
-    const BoxInfo B = C.box[b];
-    const BoxDyn& D = C.dyn[b];
-    const int first = (k - S.box_chunk0[j]) * S.chunk, last = min(first + S.chunk, B.n);
-    const int ncell = D.nc[0] * D.nc[1] * D.nc[2];
-    const int* ccnt = S.cnt + (size_t)k * S.cap;
-    const int* coff = S.off + (size_t)k * S.cap;
-    block_scan<SPLIT_BT>(ncell, wsum, [&](int q) { return ccnt[q]; }, [&](int q, int excl) {
-        if (q < ncell) lst[q] = excl;
-    });
-    __syncthreads();
-    const int* pc = C.pcell + B.off;
-    int mycell[SPLIT_PER], slot[SPLIT_PER];
-#pragma unroll
-    for (int u = 0; u < SPLIT_PER; ++u) {
-        const int q = first + (int)threadIdx.x + u * SPLIT_BT;
-        mycell[u] = q < last ? pc[q] : -1;
-        slot[u] = q < last ? atomicAdd(&lst[mycell[u]], 1) : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < SPLIT_PER; ++u)
-        if (slot[u] >= 0) ent[slot[u]] = first + (int)threadIdx.x + u * SPLIT_BT;
-    __syncthreads();
-    // lst[c] now ends the chunk's entries of cell c
-#pragma unroll
-    for (int u = 0; u < SPLIT_PER; ++u) {
-        if (slot[u] < 0) continue;
-        const int c = mycell[u], me = first + (int)threadIdx.x + u * SPLIT_BT;
-        const int e1 = lst[c], e0 = e1 - ccnt[c];
-        int rank = 0;
-        for (int e = e0; e < e1; ++e) rank += ent[e] < me;
-        slot[u] = coff[c] + rank;
-    }
-    typename R::T* pv = (typename R::T*)C.cell_pv + 2 * (size_t)B.off;
-    typename R::T* srec = (typename R::T*)C.srec + 2 * B.off;
-    const real* s = (const real*)C.s;
-    const real* cv = (const real*)C.c;
-    const int N = C.n_total;
-    const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4];
-    const real h22 = (real)D.h[8];
-    const int n2 = D.nc[2], zs = B.zsub;
-    const float inv_n2 = 1.0f / (float)n2;
-    const int* col = S.col + (size_t)j * 3 * S.colcap;
-    real v[SPLIT_PER][6];
-#pragma unroll
-    for (int u = 0; u < SPLIT_PER; ++u) {
-        const int q = first + (int)threadIdx.x + u * SPLIT_BT;
-        const int g = B.off + (q < last ? q : first);
-        v[u][0] = s[g]; v[u][1] = s[N + g]; v[u][2] = s[2 * N + g];
-        v[u][3] = cv[g]; v[u][4] = cv[N + g]; v[u][5] = cv[2 * N + g];
-    }
-#pragma unroll
-    for (int u = 0; u < SPLIT_PER; ++u) {
-        if (slot[u] < 0) continue;
-        const int q = first + (int)threadIdx.x + u * SPLIT_BT, pos = slot[u];
-        real x, y, z;
-        cell_position<real>(v[u][0], v[u][1], v[u][2], h00, h01, h10, h11, h22, x, y, z);
-        pv[2 * pos] = R::make(x, y, z, q);
-        pv[2 * pos + 1] = R::make(v[u][3], v[u][4], v[u][5], q);
-        const int cc = div_small(mycell[u], inv_n2), zc = mycell[u] - cc * n2;
-        srec[pos + col[cc]] = R::make(x, y, z, pos << 5);
-        if (zc >= n2 - zs) srec[pos + col[S.colcap + cc]] = R::make(x, y, z - h22, (pos << 5) | 9);
-        if (zc < zs) srec[pos + col[2 * S.colcap + cc]] = R::make(x, y, z + h22, (pos << 5) | 18);
+    for (int p = tid; p < total; p += T) {
+        const int src = perm[before + p];
+        const V4 V = srcC[src];
+        store(p, src, srcS[src], V, R::id(V) - s0);
     }
 }
 
@@ -1263,9 +1130,133 @@ __device__ __forceinline__ real core_fraction(real ax, real ay, real ex, real ey
 // weighted by the fraction of its segment inside the core, and the second
 // half kick relaxes the ring toward the imposed field; the core's kinetic
 // sums use the velocity relative to that field.
+
+// One ordered pair: separation d, unit vector e, magnitude of the force on i
+// along e, force g; wR, ev, th are its factors.
+template <typename real>
+struct PairOut {
+    real ex, ey, ez, mag, gx, gy, gz, wR, ev, th;
+};
+
+// The part of pair_force below the separation (dx, dy, dz): v the relative
+// velocity without the streaming difference L d.
+template <typename real>
+struct PairConst {
+    real a, gam, sig, irc, L00, L01, L10, L11;
+    unsigned step, box, k0, k1;
+};
+
+template <typename real>
+__device__ __forceinline__ PairOut<real> pair_force(const PairConst<real>& P, real dx, real dy, real dz, real ci0,
+                                                    real ci1, real ci2, real cj0, real cj1, real cj2, unsigned id_i,
+                                                    unsigned id_j) {
+    PairOut<real> o;
+    const real r2 = fma(dz, dz, fma(dx, dx, dy * dy));  // fixed association
+    const real ir = inv_sqrt(r2);
+    const real r = r2 * ir;
+    o.ex = dx * ir; o.ey = dy * ir; o.ez = dz * ir;
+    o.wR = (real)1 - r * P.irc;
+    const real vx = ci0 - cj0 + P.L00 * dx + P.L01 * dy;
+    const real vy = ci1 - cj1 + P.L10 * dx + P.L11 * dy;
+    const real vz = ci2 - cj2;
+    o.ev = o.ex * vx + o.ey * vy + o.ez * vz;
+    o.th = pair_theta<real>(id_i, id_j, P.step, P.box, P.k0, P.k1);
+    o.mag = o.wR * (P.a - P.gam * o.wR * o.ev + P.sig * o.th);
+    o.gx = o.mag * o.ex; o.gy = o.mag * o.ey; o.gz = o.mag * o.ez;
+    return o;
+}
+
+// FENE springs of a bead to its chain neighbours: their forces added to f,
+// each bond's virial once (by its lower bead) to wf; S: (s, index) by index of
+// the box.  wgt(dx, dy): weight of a bond's virial.
+template <typename real, class Wgt>
+__device__ __forceinline__ void bond_forces(const Ctx& C, int b, int id, const typename Rec<real>::T* S, real h00,
+                                            real h01, real h10, real h11, real h22, real& fx, real& fy, real& fz,
+                                            real (&wf)[6], Wgt wgt) {
+    const typename Rec<real>::T si = S[id];
+    const int bead = id % C.chain_len;
+    const real Hf = (real)C.H, iR02 = (real)C.inv_R02;
+    for (int side = 0; side < 2; ++side) {
+        if (side == 0 && bead == 0) continue;
+        if (side == 1 && bead == C.chain_len - 1) continue;
+        const typename Rec<real>::T sj = S[side == 0 ? id - 1 : id + 1];
+        real ds0 = si.x - sj.x, ds1 = si.y - sj.y, ds2 = si.z - sj.z;
+        ds0 -= rint(ds0); ds1 -= rint(ds1); ds2 -= rint(ds2);
+        const real dx = fma(h00, ds0, h01 * ds1), dy = fma(h10, ds0, h11 * ds1), dz = h22 * ds2;
+        real den = fma(-fma(dz, dz, fma(dx, dx, dy * dy)), iR02, (real)1);
+        if (den <= (real)0) atomicOr(&C.flags[b], LHMM_FLAG_BOND);
+        if (den < (real)0.01) den = (real)0.01;
+        const real k = -Hf / den;
+        fx = fma(k, dx, fx); fy = fma(k, dy, fy); fz = fma(k, dz, fz);
+        if (side == 1) {
+            const real gx = k * dx, gy = k * dy, gz = k * dz;
+            const real w = wgt(dx, dy);
+            const real dxw = dx * w, dyw = dy * w, dzw = dz * w;
+            wf[0] = fma(dxw, gx, wf[0]); wf[1] = fma(dyw, gy, wf[1]); wf[2] = fma(dzw, gz, wf[2]);
+            wf[3] = fma(dxw, gy, wf[3]); wf[4] = fma(dxw, gz, wf[4]); wf[5] = fma(dyw, gz, wf[5]);
+        }
+    }
+}
+
+// The end of a particle's step: second half kick of the velocity-Verlet step,
+// c += dt/2 (F/m - L c), with its final force; the kinetic sums m c c in
+// kin; then either the next step's half kick and drift with that step's cell
+// Dn, written at its cell-order position (and by index for a bead), or, after
+// the chunk's last step, position, velocity and force in index order.
+template <typename real, bool AF>
+__device__ __forceinline__ void end_step(const Ctx& C, const Step& A, const BoxInfo& B, const BoxDyn& D,
+                                         const BoxDyn& Dn, int pos, int id, real s0, real s1, real s2, real c0,
+                                         real c1, real c2, real fx, real fy, real fz, real L00, real L01, real L10,
+                                         real L11, unsigned stepc, bool store, double (&kin)[6]) {
+    using R = Rec<real>;
+    using V4 = typename R::T;
+    const bool afbc = AF && D.hc > 0.0;
+    const int N = C.n_total, i = B.off + id;
+    const real hdt = (real)(0.5 * C.dt), im = (real)C.inv_mass;
+    half_kick<real>(hdt, im, L00, L01, L10, L11, fx, fy, fz, c0, c1, c2);
+    bool in_core = true;
+    real u0 = (real)0, u1 = (real)0;  // imposed field at the particle (boundary regions)
+    if (afbc) {
+        const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4], hcr = (real)D.hc;
+        const real x = fma(h00, s0 - (real)0.5, h01 * (s1 - (real)0.5));
+        const real y = fma(h10, s0 - (real)0.5, h11 * (s1 - (real)0.5));
+        const real G[4] = {(real)D.G[0], (real)D.G[1], (real)D.G[2], (real)D.G[3]};
+        ring_relax<real>(x, y, hcr, (real)D.hb, G, (real)C.ou_damp, (real)C.ou_amp, (unsigned)id, 1u, stepc, B.rng_id,
+                         C.key0, C.key1, c0, c1);
+        in_core = fmax(fabs(x), fabs(y)) < hcr;
+        u0 = fma(G[0], x, G[1] * y);
+        u1 = fma(G[2], x, G[3] * y);
+    }
+    if (in_core) {
+        const double mm = C.mass, x = (double)(c0 - u0), y = (double)(c1 - u1), z = (double)c2;
+        kin[0] = mm * x * x; kin[1] = mm * y * y; kin[2] = mm * z * z;
+        kin[3] = mm * x * y; kin[4] = mm * x * z; kin[5] = mm * y * z;
+    }
+    if (!store) return;
+    if (!A.more) {
+        real* s = (real*)C.s;
+        real* c = (real*)C.c;
+        real* f = (real*)C.f;
+        s[i] = s0; s[(size_t)N + i] = s1; s[2 * (size_t)N + i] = s2;
+        c[i] = c0; c[(size_t)N + i] = c1; c[2 * (size_t)N + i] = c2;
+        f[i] = fx; f[(size_t)N + i] = fy; f[2 * (size_t)N + i] = fz;
+        return;
+    }
+    real sv[3] = {s0, s1, s2}, cv[3] = {c0, c1, c2};
+    const real fv[3] = {fx, fy, fz};
+    const KickDrift<real> K(C, Dn, B.rng_id, stepc + 1u);
+    kick_drift<real, AF>(K, sv, cv, fv, id);
+    const int cell = cell_of(sv[0], sv[1], sv[2], K.nc), ns = A.slot ^ 1;
+    const V4 rec = R::make(sv[0], sv[1], sv[2], id);
+    ((V4*)C.sord[ns])[B.off + pos] = rec;
+    ((V4*)C.cord)[B.off + pos] = R::make(cv[0], cv[1], cv[2], cell);
+    C.key[B.off + pos] = cell;
+    if (id < B.n_beads) ((V4*)C.sid[ns])[i] = rec;
+}
+
 template <typename real, int QD, bool PRUNE, bool COMP = false, bool AF = false>
 __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4 : (PRUNE ? 5 : 6)) : 1) void k_forces(
-    Ctx C, int step_offset, int drain, int busy, int kick) {
+    Ctx C, Step A, int drain, int busy) {
     constexpr bool prune = PRUNE;
     constexpr int NV = COMP ? 37 : 19;  // block partial sums
     using R = Rec<real>;
@@ -1280,12 +1271,11 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
     // image_shift, and 0, -h22 or +h22 along z
     __shared__ real shift_tab[32][4];
 
-    int blk = xcd_local_work(blockIdx.x, gridDim.x);
-    if (C.blk_list) blk = C.blk_list[blk];
+    const int work = xcd_local_work(blockIdx.x, gridDim.x);
+    const int blk = C.blk_list ? C.blk_list[work] : work;
     const int b = C.blk_box[blk];
     const BoxInfo B = C.box[b];
-    const BoxDyn& D = C.dyn[b];
-    const int N = C.n_total;
+    const BoxDyn& D = C.dyn[(size_t)A.slot * C.n_boxes + b];
     const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
     const int p0 = C.blk_first[blk] - B.off;  // first cell-order position of the block
     const int pos = p0 + t;
@@ -1293,8 +1283,7 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
     const V4* pv = (const V4*)C.cell_pv + 2 * (size_t)B.off;
     const char* sbase = (const char*)((const V4*)C.srec + 2 * B.off);
     const __amdgpu_buffer_rsrc_t srsrc = rec_rsrc(sbase);
-    const real* s = (const real*)C.s;
-    real* f = (real*)C.f;
+    const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
 
     // in-plane cell and gradient
     const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4];
@@ -1306,13 +1295,14 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
     __syncthreads();
     real ri0 = 0, ri1 = 0, ri2 = 0, ci0 = 0, ci1 = 0, ci2 = 0;
     real own_s0 = 0, own_s1 = 0, own_s2 = 0;
-    int own_id = 0;
+    int own_id = 0, src = 0;
     if (act) {
         const V4 u = pv[2 * pos + 1];
         ci0 = u.x; ci1 = u.y; ci2 = u.z;
         own_id = R::id(u);
-        const int g = B.off + own_id;
-        own_s0 = s[g]; own_s1 = s[N + g]; own_s2 = s[2 * N + g];
+        src = C.perm[B.off + pos];
+        const V4 S = srcS[src];
+        own_s0 = S.x; own_s1 = S.y; own_s2 = S.z;
         cell_position<real>(own_s0, own_s1, own_s2, h00, h01, h10, h11, h22, ri0, ri1, ri2);
     }
     const real L00 = (real)D.L[0], L01 = (real)D.L[1], L10 = (real)D.L[3], L11 = (real)D.L[4];
@@ -1323,9 +1313,10 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
     const int n0 = D.nc[0], n1 = D.nc[1], n2 = D.nc[2], zs = B.zsub;
     const real dzc = h22 / (real)n2;  // cell height
     auto sqr = [](real x) { return x * x; };
-    const unsigned stepc = (unsigned)(*C.step + (unsigned long long)step_offset);
-    const real a = (real)C.a, gam = (real)C.gamma, sig = (real)(C.sigma * C.rdt);
-    const real rc2 = (real)C.rc2, irc = (real)(1.0 / C.rc);
+    const unsigned stepc = (unsigned)(*C.step + (unsigned long long)A.k);
+    const PairConst<real> P{(real)C.a, (real)C.gamma, (real)(C.sigma * C.rdt), (real)(1.0 / C.rc), L00, L01, L10, L11,
+                            stepc, B.rng_id, C.key0, C.key1};
+    const real rc2 = (real)C.rc2;
     const int* gstart = C.gcell_start + B.gcell_off;
 
     int k0 = 0, k1 = 0, k2 = 0;
@@ -1341,8 +1332,7 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
     real gl0 = 0, gh0 = 0, gl1 = 0, gh1 = 0, zl = 0, zh = 0;
     const real rcp2 = prune ? (real)(1.002 * C.rc2) : (real)0;
     if (act && prune) {
-        const int gi = B.off + own_id;
-        const real s0 = s[gi], s1 = s[N + gi], s2 = s[2 * N + gi];
+        const real s0 = own_s0, s1 = own_s1, s2 = own_s2;
         const real area = fabs(h00 * h11 - h01 * h10);
         const real w0 = area / sqrt(h01 * h01 + h11 * h11), w1 = area / sqrt(h00 * h00 + h10 * h10);
         const real f0 = s0 * (real)n0 - (real)k0, f1 = s1 * (real)n1 - (real)k1, f2 = s2 * (real)n2 - (real)k2;
@@ -1380,18 +1370,9 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
             // binning's z - h22, z + h22
             const real zj = pj.z + shift_tab[code][2];
             const real dx = (ri0 - sx) - pj.x, dy = (ri1 - sy) - pj.y, dz = ri2 - zj;
-            const real r2 = fma(dz, dz, fma(dx, dx, dy * dy));  // fixed association
-            const real ir = inv_sqrt(r2);
-            const real r = r2 * ir;
-            const real ex = dx * ir, ey = dy * ir, ez = dz * ir;
-            const real wR = (real)1 - r * irc;
-            const real vx = ci0 - cj.x + L00 * dx + L01 * dy;
-            const real vy = ci1 - cj.y + L10 * dx + L11 * dy;
-            const real vz = ci2 - cj.z;
-            const real ev = ex * vx + ey * vy + ez * vz;
-            const real th = pair_theta<real>((unsigned)own_id, (unsigned)R::id(cj), stepc, B.rng_id, C.key0, C.key1);
-            const real mag = wR * (a - gam * wR * ev + sig * th);
-            const real gx = mag * ex, gy = mag * ey, gz = mag * ez;
+            const PairOut<real> o = pair_force<real>(P, dx, dy, dz, ci0, ci1, ci2, cj.x, cj.y, cj.z, (unsigned)own_id,
+                                                     (unsigned)R::id(cj));
+            const real ex = o.ex, ey = o.ey, ez = o.ez, gx = o.gx, gy = o.gy, gz = o.gz;
             fx += gx; fy += gy; fz += gz;
             // a boundary-region box weighs the pair by its segment's share of the core
             const real wgt = afbc ? core_fraction<real>(ri0 - cx, ri1 - cy, -dx, -dy, hcr) : (real)1;
@@ -1400,7 +1381,7 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
             w[3] += dxw * gy; w[4] += dxw * gz; w[5] += dyw * gz;
             if constexpr (COMP) {
                 // d (x) e times each force's magnitude
-                const real mc = wR * a, md = -(wR * gam * wR * ev), mr = wR * sig * th;
+                const real mc = o.wR * P.a, md = -(o.wR * P.gam * o.wR * o.ev), mr = o.wR * P.sig * o.th;
                 const real de[6] = {dxw * ex, dyw * ey, dzw * ez, dxw * ey, dxw * ez, dyw * ez};
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
@@ -1503,36 +1484,9 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
     }
 
     real wf[6] = {0, 0, 0, 0, 0, 0};
-    if (act) {
-        const int i = B.off + own_id;
-        // FENE springs to the chain neighbours
-        if (own_id < B.n_beads) {
-            const real si0 = s[i], si1 = s[N + i], si2 = s[2 * N + i];
-            const int bead = own_id % C.chain_len;
-            const real Hf = (real)C.H, iR02 = (real)C.inv_R02;
-            for (int side = 0; side < 2; ++side) {
-                if (side == 0 && bead == 0) continue;
-                if (side == 1 && bead == C.chain_len - 1) continue;
-                const int j = side == 0 ? i - 1 : i + 1;
-                real ds0 = si0 - s[j], ds1 = si1 - s[N + j], ds2 = si2 - s[2 * N + j];
-                ds0 -= rint(ds0); ds1 -= rint(ds1); ds2 -= rint(ds2);
-                const real dx = h00 * ds0 + h01 * ds1, dy = h10 * ds0 + h11 * ds1, dz = h22 * ds2;
-                real den = (real)1 - (dx * dx + dy * dy + dz * dz) * iR02;
-                if (den <= (real)0) atomicOr(&C.flags[b], LHMM_FLAG_BOND);
-                if (den < (real)0.01) den = (real)0.01;
-                const real k = -Hf / den;
-                const real gx = k * dx, gy = k * dy, gz = k * dz;
-                fx += gx; fy += gy; fz += gz;
-                if (side == 1) {  // each bond's virial once, by its lower bead
-                    const real wgt = afbc ? core_fraction<real>(ri0 - cx, ri1 - cy, -dx, -dy, hcr) : (real)1;
-                    const real dxw = AF ? dx * wgt : dx, dyw = AF ? dy * wgt : dy, dzw = AF ? dz * wgt : dz;
-                    wf[0] += dxw * gx; wf[1] += dyw * gy; wf[2] += dzw * gz;
-                    wf[3] += dxw * gy; wf[4] += dxw * gz; wf[5] += dyw * gz;
-                }
-            }
-        }
-        f[i] = fx; f[N + i] = fy; f[2 * N + i] = fz;
-    }
+    if (act && own_id < B.n_beads)
+        bond_forces<real>(C, b, own_id, (const V4*)C.sid[A.slot] + B.off, h00, h01, h10, h11, h22, fx, fy, fz, wf,
+                          [&](real dx, real dy) { return afbc ? core_fraction<real>(ri0 - cx, ri1 - cy, -dx, -dy, hcr) : (real)1; });
     double v[NV];
     for (int k = 0; k < 6; ++k) {
         v[k] = (double)w[k];
@@ -1545,91 +1499,346 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
         }
     }
     v[12] = (double)(qt / QROW);  // every queued neighbour was evaluated once
-    // second half kick of the velocity-Verlet step, c += dt/2 (F/m - L c),
-    // with the particle's final force, and the kinetic partial sums m c c
-    if (kick && act) {
-        const int i = B.off + own_id;
-        real* c = (real*)C.c;
-        const real hdt = (real)(0.5 * C.dt), im = (real)C.inv_mass;
-        real c0 = ci0, c1 = ci1, c2 = ci2;
-        const real lc0 = L00 * c0 + L01 * c1, lc1 = L10 * c0 + L11 * c1;
-        c0 += hdt * (fx * im - lc0);
-        c1 += hdt * (fy * im - lc1);
-        c2 += hdt * (fz * im);
-        bool in_core = true;
-        real u0 = (real)0, u1 = (real)0;  // imposed field at the particle (boundary regions)
-        if (afbc) {
-            const real x = h00 * (own_s0 - (real)0.5) + h01 * (own_s1 - (real)0.5);
-            const real y = h10 * (own_s0 - (real)0.5) + h11 * (own_s1 - (real)0.5);
-            const real G[4] = {(real)D.G[0], (real)D.G[1], (real)D.G[2], (real)D.G[3]};
-            ring_relax<real>(x, y, hcr, (real)D.hb, G, (real)C.ou_damp, (real)C.ou_amp, (unsigned)own_id, 1u, stepc,
-                             B.rng_id, C.key0, C.key1, c0, c1);
-            in_core = fmax(fabs(x), fabs(y)) < hcr;
-            u0 = G[0] * x + G[1] * y;
-            u1 = G[2] * x + G[3] * y;
+    if (act && A.kick) {
+        const V4 S = srcS[src];  // read again rather than held through the search
+        double kin[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        end_step<real, AF>(C, A, B, D, C.dyn[(size_t)(A.slot ^ 1) * C.n_boxes + b], pos, own_id, S.x, S.y, S.z, ci0, ci1,
+                           ci2, fx, fy, fz, L00, L01, L10, L11, stepc, true, kin);
+        for (int k = 0; k < 6; ++k) v[13 + k] = kin[k];
+    } else if (act) {
+        real* f = (real*)C.f;
+        const int i = B.off + own_id, N = C.n_total;
+        f[i] = fx; f[(size_t)N + i] = fy; f[2 * (size_t)N + i] = fz;
+    }
+    block_sum<NV>(v, red, C.part + (size_t)A.w * C.part_step + (size_t)(A.part0 + work) * NV);
+}
+
+// The force pass for launches too small to fill the chip, where the lone
+// waves of k_forces wait for their ~37 dependent search loads and ~20 serial
+// evaluation rounds (32 us however few particles).  Sixteen lanes own one
+// particle: nine of them search a stencil row each, then all evaluate one
+// neighbour each, and one lane per component adds the results in the order
+// k_forces adds them (row by row, in cell order), so the sums are the same to
+// the bit.  A workgroup takes the sixteen particles l = r + 4 j of a wave's 64
+// (r = 0 .. 3): their partial sums are a subtree of k_forces's wave sum.
+// Slower per particle (four particles per wave), so only for at most
+// WIDE_BLOCKS work blocks; the design notes have both kernels' times.
+constexpr int WIDE_UNITS = 16;    // workgroups per work block
+constexpr int WIDE_BLOCKS = 256;  // largest launch, in work blocks
+constexpr int WIDE_ROW = 12;      // accepted neighbours per row that LDS holds
+
+// Make a wave's LDS writes visible to its other lanes: one wave's LDS
+// operations execute in order, so only the compiler has to keep it.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename real, bool COMP>
+__global__ __launch_bounds__(BS) void k_forces_wide(Ctx C, Step A) {
+    using R = Rec<real>;
+    using V4 = typename R::T;
+    constexpr int NV = COMP ? 37 : 19;
+    constexpr int NF = COMP ? 19 : 10;   // values per evaluated pair
+    constexpr int NA = COMP ? 27 : 9;    // summed components
+    constexpr int PS = 20;               // stride of a value's 16 entries (16-byte reads)
+    __shared__ real shift_tab[32][4];
+    __shared__ int rowq[16][9][WIDE_ROW];
+    __shared__ int list[16][9 * WIDE_ROW];
+    __shared__ __align__(16) real res[16][NF][PS];
+    __shared__ double vals[16][NV];
+
+    const int unit = xcd_local_work(blockIdx.x, gridDim.x), work = unit / WIDE_UNITS, sub = unit % WIDE_UNITS;
+    const int blk = C.blk_list ? C.blk_list[work] : work;
+    const int b = C.blk_box[blk];
+    const BoxInfo B = C.box[b];
+    const BoxDyn& D = C.dyn[(size_t)A.slot * C.n_boxes + b];
+    const int t = threadIdx.x, a = t & 15, p = t >> 4;  // lane of the particle, particle of the workgroup
+    const int gbase = (t & 63) & ~15;                   // first lane of the particle in its wave
+    const int pos = C.blk_first[blk] - B.off + 64 * (sub >> 2) + (sub & 3) + 4 * p;
+    const bool act = pos < B.n;
+    const V4* pv = (const V4*)C.cell_pv + 2 * (size_t)B.off;
+    const char* sbase = (const char*)((const V4*)C.srec + 2 * B.off);
+    const __amdgpu_buffer_rsrc_t srsrc = rec_rsrc(sbase);
+    const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
+    const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4];
+    const real h22 = (real)D.h[8];
+    if (t < 27) {
+        image_shift<real>(t % 9, h00, h01, h10, h11, shift_tab[t][0], shift_tab[t][1]);
+        shift_tab[t][2] = t < 9 ? (real)0 : (t < 18 ? -h22 : h22);
+    }
+    __syncthreads();
+    real ri0 = 0, ri1 = 0, ri2 = 0, ci0 = 0, ci1 = 0, ci2 = 0, s0 = 0, s1 = 0, s2 = 0;
+    int own_id = 0;
+    if (act) {
+        const V4 u = pv[2 * pos + 1];
+        ci0 = u.x; ci1 = u.y; ci2 = u.z;
+        own_id = R::id(u);
+        const V4 S = srcS[C.perm[B.off + pos]];
+        s0 = S.x; s1 = S.y; s2 = S.z;
+        cell_position<real>(s0, s1, s2, h00, h01, h10, h11, h22, ri0, ri1, ri2);
+    }
+    const real L00 = (real)D.L[0], L01 = (real)D.L[1], L10 = (real)D.L[3], L11 = (real)D.L[4];
+    const int n0 = D.nc[0], n1 = D.nc[1], n2 = D.nc[2], zs = B.zsub;
+    const unsigned stepc = (unsigned)(*C.step + (unsigned long long)A.k);
+    const PairConst<real> P{(real)C.a, (real)C.gamma, (real)(C.sigma * C.rdt), (real)(1.0 / C.rc), L00, L01, L10, L11,
+                            stepc, B.rng_id, C.key0, C.key1};
+    const real rc2 = (real)C.rc2;
+    const int* gstart = C.gcell_start + B.gcell_off;
+    int k0 = 0, k1 = 0, k2 = 0;
+    if (act) cell_coords(s0, s1, s2, D.nc, k0, k1, k2);
+    // the search-layout range of stencil row `row`, its image code, and the
+    // particle's position less the row's in-plane image shift
+    auto row_range = [&](int row, int& q, int& qe, int& ic, real& bx, real& by) {
+        const int d0 = row / 3 - 1, d1 = row % 3 - 1;
+        int m0 = k0 + d0, m1 = k1 + d1;
+        const int sh0 = m0 < 0 ? -1 : (m0 >= n0 ? 1 : 0);
+        const int sh1 = m1 < 0 ? -1 : (m1 >= n1 ? 1 : 0);
+        m0 -= sh0 * n0;
+        m1 -= sh1 * n1;
+        const int gb = (m0 * n1 + m1) * (n2 + 2 * zs) + k2;
+        ic = 3 * (sh0 + 1) + (sh1 + 1);
+        bx = ri0 - shift_tab[ic][0];
+        by = ri1 - shift_tab[ic][1];
+        q = gstart[gb];
+        qe = gstart[gb + 2 * zs + 1];
+    };
+    auto accepted = [&](const V4& v, real bx, real by) {
+        const real dx = bx - v.x, dy = by - v.y, dz = ri2 - v.z;
+        const real r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+        return (r2 < rc2) & (r2 > (real)0);
+    };
+    // summed components: force 3, virial 6 (C, D, R virials 6 each) as sums of
+    // products of two of an entry's values: mag e, d g (and mc, md, mr with d e)
+    auto factors = [](int c, int& fa, int& fb) {
+        if (c < 3) {
+            fa = 0;
+            fb = 1 + c;
+            return;
         }
-        c[i] = c0; c[N + i] = c1; c[2 * N + i] = c2;
-        if (in_core) {
-            const double mm = C.mass, x = (double)(c0 - u0), y = (double)(c1 - u1), z = (double)c2;
-            v[13] = mm * x * x; v[14] = mm * y * y; v[15] = mm * z * z;
-            v[16] = mm * x * y; v[17] = mm * x * z; v[18] = mm * y * z;
+        const int k = (c - 3) % 6, part = (c - 3) / 6;
+        const int ia = k < 3 ? k : (k == 5 ? 1 : 0), ib = k < 3 ? k : (k == 3 ? 1 : 2);
+        fa = part == 0 ? 4 + ia : 9 + part;
+        fb = part == 0 ? 7 + ib : 13 + k;
+    };
+    int fa0, fb0, fa1, fb1;
+    factors(min(a, NA - 1), fa0, fb0);
+    factors(min(a + 16, NA - 1), fa1, fb1);
+    real acc0 = 0, acc1 = 0;
+    // evaluate entry e of the particle's m (one per lane, m <= 16), then add
+    // the results in entry order; entries past m contribute exact zeros
+    auto evaluate = [&](int m, int e) {
+        real o[NF];
+#pragma unroll
+        for (int k = 0; k < NF; ++k) o[k] = (real)0;
+        if (a < m) {
+            const unsigned po = ((unsigned)e >> 5) * (unsigned)(2 * sizeof(V4));
+            const V4 pj = *(const V4*)((const char*)pv + po);
+            const V4 cj = *(const V4*)((const char*)pv + po + sizeof(V4));
+            const int code = e & 31;
+            const real sx = shift_tab[code][0], sy = shift_tab[code][1];
+            const real zj = pj.z + shift_tab[code][2];
+            const real dx = (ri0 - sx) - pj.x, dy = (ri1 - sy) - pj.y, dz = ri2 - zj;
+            const PairOut<real> w = pair_force<real>(P, dx, dy, dz, ci0, ci1, ci2, cj.x, cj.y, cj.z, (unsigned)own_id,
+                                                     (unsigned)R::id(cj));
+            o[0] = w.mag; o[1] = w.ex; o[2] = w.ey; o[3] = w.ez;
+            o[4] = dx; o[5] = dy; o[6] = dz;
+            o[7] = w.gx; o[8] = w.gy; o[9] = w.gz;
+            if constexpr (COMP) {
+                o[10] = w.wR * P.a;
+                o[11] = -(w.wR * P.gam * w.wR * w.ev);
+                o[12] = w.wR * P.sig * w.th;
+                o[13] = dx * w.ex; o[14] = dy * w.ey; o[15] = dz * w.ez;
+                o[16] = dx * w.ey; o[17] = dx * w.ez; o[18] = dy * w.ez;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NF; ++k) res[p][k][a] = o[k];
+        wave_lds_sync();
+        const real* xa = res[p][fa0];
+        const real* xb = res[p][fb0];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc0 = fma(xa[k], xb[k], acc0);
+        if constexpr (COMP) {
+            const real* ya = res[p][fa1];
+            const real* yb = res[p][fb1];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) acc1 = fma(ya[k], yb[k], acc1);
+        }
+        wave_lds_sync();
+    };
+
+    // search: lane a < 9 scans row a
+    int q = 0, qe = 0, ic = 4, found = 0;
+    real bx = 0, by = 0;
+    if (act && a < 9) row_range(a, q, qe, ic, bx, by);
+    while (__ballot(q < qe) != 0ull) {
+        V4 cand[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) cand[u] = load_rec<real>(srsrc, sbase, (unsigned)(q + u) * (unsigned)sizeof(V4));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if ((q + u < qe) & accepted(cand[u], bx, by)) {
+                if (found < WIDE_ROW) rowq[p][a][found] = R::id(cand[u]) + ic;
+                ++found;
+            }
+        q = min(q + 4, qe);
+    }
+    int incl = found;  // accepted in this row and the ones before it
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        const int y = __shfl_up(incl, o, 16);
+        if (a >= o) incl += y;
+    }
+    const int total = __shfl(incl, 15, 16);
+    const unsigned over = (unsigned)(__ballot(found > WIDE_ROW) >> gbase) & 0xFFFFu;
+    if (over == 0u)
+        for (int k = 0; k < found; ++k) list[p][incl - found + k] = rowq[p][a][k];
+    wave_lds_sync();
+    const int fast = over == 0u ? total : 0;
+    for (int e0 = 0; __ballot(e0 < fast) != 0ull; e0 += 16)
+        evaluate(min(fast - e0, 16), e0 + a < fast ? list[p][e0 + a] : 0);
+    // a row holds more than WIDE_ROW neighbours (a very dense spot): row by
+    // row, sixteen candidates at a time, in the same order
+    if (__ballot(over != 0u) != 0ull) {
+        for (int row = 0; row < 9; ++row) {
+            int rq = 0, re = 0, rc = 4;
+            real rx = 0, ry = 0;
+            if (act && over != 0u) row_range(row, rq, re, rc, rx, ry);
+            while (__ballot(rq < re) != 0ull) {
+                const V4 v = load_rec<real>(srsrc, sbase, (unsigned)min(rq + a, max(re - 1, 0)) * (unsigned)sizeof(V4));
+                const bool ok = (rq + a < re) & accepted(v, rx, ry);
+                const unsigned mask = (unsigned)(__ballot(ok) >> gbase) & 0xFFFFu;
+                if (ok) list[p][__popc(mask & ((1u << a) - 1u))] = R::id(v) + rc;
+                wave_lds_sync();
+                const int m = __popc(mask);
+                evaluate(m, a < m ? list[p][a] : 0);
+                rq = min(rq + 16, re);
+            }
         }
     }
-    block_sum<NV>(v, red);
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 12; ++k) C.part_vir[(size_t)C.pv_stride * blk + k] = v[k];
-        if constexpr (COMP)
-            for (int k = 0; k < 18; ++k) C.part_vir[(size_t)C.pv_stride * blk + 12 + k] = v[19 + k];
-        C.part_pairs[blk] = (unsigned)v[12];
-        if (kick)
-            for (int k = 0; k < 6; ++k) C.part_kin[6 * blk + k] = v[13 + k];
+    real fx = __shfl(acc0, 0, 16), fy = __shfl(acc0, 1, 16), fz = __shfl(acc0, 2, 16);
+    real wf[6] = {0, 0, 0, 0, 0, 0};
+    if (act && own_id < B.n_beads)
+        bond_forces<real>(C, b, own_id, (const V4*)C.sid[A.slot] + B.off, h00, h01, h10, h11, h22, fx, fy,
+                          fz, wf, [](real, real) { return (real)1; });
+    double kin[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (act && A.kick) {
+        end_step<real, false>(C, A, B, D, C.dyn[(size_t)(A.slot ^ 1) * C.n_boxes + b], pos, own_id, s0, s1, s2, ci0,
+                              ci1, ci2, fx, fy, fz, L00, L01, L10, L11, stepc, a == 0, kin);
+    } else if (act && a == 0) {
+        real* f = (real*)C.f;
+        const int i = B.off + own_id, N = C.n_total;
+        f[i] = fx; f[(size_t)N + i] = fy; f[2 * (size_t)N + i] = fz;
+    }
+    if (a >= 3 && a < 9) vals[p][a - 3] = act ? (double)acc0 : 0.0;
+    if constexpr (COMP) {
+        if (a >= 9) vals[p][19 + a - 9] = (double)acc0;
+        if (a + 16 < NA) vals[p][19 + a + 7] = (double)acc1;
+    }
+    if (a == 0) {
+        for (int k = 0; k < 6; ++k) {
+            vals[p][6 + k] = (double)wf[k];
+            vals[p][13 + k] = kin[k];
+        }
+        vals[p][12] = act ? (double)total : 0.0;
+    }
+    __syncthreads();
+    // the subtree over j (lanes 32, 16, 8, 4 apart)
+    if (t < NV) {
+        double x[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = vals[j][t];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+            for (int j = 0; j < o; ++j) x[j] += x[j + o];
+        C.part[(size_t)A.w * C.part_step + ((size_t)work * WIDE_UNITS + sub) * NV + t] = x[0];
     }
 }
 
-// One wave per box: the step's stress, sigma = -(K + W)/V, by part.  Lane l
-// sums the partials of blocks l, l+64, ...; a fixed shuffle tree combines
-// the lanes, so the order of every sum is fixed.  With the C, D, R parts
-// kept (pv_stride 30) they are reduced alongside.
-__global__ __launch_bounds__(64) void k_box_stress(Ctx C) {
-    const int b = C.sel ? C.sel[blockIdx.x] : (int)blockIdx.x;
-    const int lane = threadIdx.x;
+// The stresses of a window of nw steps, one workgroup per box: sigma =
+// -(K + W)/V by part and step.  Wave w sums the partials of steps w, w + 16,
+// ...: lane l those of blocks l, l + 64, ..., then a fixed tree; the steps are
+// then added in order.  After a chunk's last window the box's cell returns to
+// slot 0 and, when this launch covers all of the chunk's boxes, the step
+// counter advances by `add`.
+constexpr int FLUSH_THREADS = 1024;
+
+template <int NV>
+__global__ __launch_bounds__(FLUSH_THREADS) void k_flush(Ctx C, int nw, int part0, int wide, int copy_dyn, int add) {
+    __shared__ double sum[MAX_WINDOW][NV];
+    const int q = blockIdx.x, b = C.sel ? C.sel[q] : q;
     const BoxInfo B = C.box[b];
-    const bool comp = C.pv_stride > 12;
-    double v[37];
-    for (int q = 0; q < 37; ++q) v[q] = 0.0;
-    for (int k = lane; k < B.nblk; k += 64) {
-        const int blk = B.blk_off + k;
-        for (int q = 0; q < 6; ++q) v[q] += C.part_kin[6 * blk + q];
-        for (int q = 0; q < 12; ++q) v[6 + q] += C.part_vir[(size_t)C.pv_stride * blk + q];
-        v[18] += (double)C.part_pairs[blk];
-        if (comp)
-            for (int q = 0; q < 18; ++q) v[19 + q] += C.part_vir[(size_t)C.pv_stride * blk + 12 + q];
-    }
+    const int first = C.sel ? C.blk0[q] : B.blk_off;
+    const int lane = threadIdx.x & 63;
+    for (int w = threadIdx.x >> 6; w < nw; w += FLUSH_THREADS / 64) {
+        double v[NV];
 #pragma unroll
-    for (int q = 0; q < 37; ++q)
+        for (int k = 0; k < NV; ++k) v[k] = 0.0;
+        const double* part = C.part + (size_t)w * C.part_step;
+        for (int k = lane; k < B.nblk; k += 64) {
+            const double* p = part + (size_t)(part0 + first + k) * NV * (wide ? WIDE_UNITS : 1);
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
-    if (lane == 0) {
-        const double iv = 1.0 / C.dyn[b].vol;
-        double* acc = C.acc + ACC * b;
-        bool finite = true;
-        for (int q = 0; q < 6; ++q) {
-            const double sk = -v[q] * iv, sp = -C.vir_scale * v[6 + q] * iv, sf = -v[12 + q] * iv;
-            acc[q] += sk;
-            acc[6 + q] += sp;
-            acc[12 + q] += sf;
-            if (!(fabs(sk + sp + sf) <= 1e300)) finite = false;
-            if (comp)
-                for (int r = 0; r < 3; ++r) acc[18 + 6 * r + q] += -C.vir_scale * v[19 + 6 * r + q] * iv;
+            for (int r = 0; r < NV; ++r) {
+                double x;
+                if (wide) {  // per wave of 64 particles the residues two and one apart, then the waves in order
+                    x = 0.0;
+                    for (int s = 0; s < 4; ++s) {
+                        const double* y = p + (size_t)(4 * s) * NV + r;
+                        x += (y[0] + y[2 * NV]) + (y[NV] + y[3 * NV]);
+                    }
+                } else {
+                    x = p[r];
+                }
+                v[r] += x;
+            }
         }
-        if (!finite) C.flags[b] |= LHMM_FLAG_NONFINITE;
-        const unsigned long long np = (unsigned long long)v[18];
-        const unsigned long long up = C.vir_scale < 1.0 ? np / 2 : np;
+#pragma unroll
+        for (int r = 0; r < NV; ++r) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v[r] += __shfl_xor(v[r], o, 64);
+            if (lane == 0) sum[w][r] = v[r];
+        }
+    }
+    __syncthreads();
+    double* acc = C.acc + (size_t)ACC * b;
+    const int r = threadIdx.x;
+    if (r < 6) {
+        double a0 = acc[r], a1 = acc[6 + r], a2 = acc[12 + r];
+        bool finite = true;
+        for (int w = 0; w < nw; ++w) {
+            const double iv = 1.0 / C.vol[(size_t)w * C.n_boxes + b];
+            const double sk = -sum[w][13 + r] * iv, sp = -C.vir_scale * sum[w][r] * iv, sf = -sum[w][6 + r] * iv;
+            a0 += sk;
+            a1 += sp;
+            a2 += sf;
+            if (!(fabs(sk + sp + sf) <= 1e300)) finite = false;
+        }
+        acc[r] = a0;
+        acc[6 + r] = a1;
+        acc[12 + r] = a2;
+        if (!finite) atomicOr(&C.flags[b], LHMM_FLAG_NONFINITE);
+    } else if (NV > 19 && r >= 18 && r < 36) {
+        double a = acc[r];
+        for (int w = 0; w < nw; ++w) a += -C.vir_scale * sum[w][r + 1] * (1.0 / C.vol[(size_t)w * C.n_boxes + b]);
+        acc[r] = a;
+    } else if (r == 64) {
+        unsigned long long up = 0ull;
+        for (int w = 0; w < nw; ++w) {
+            const unsigned long long np = (unsigned long long)sum[w][12];
+            up += C.vir_scale < 1.0 ? np / 2 : np;
+        }
         C.acc_pairs[b] += up;
         C.tot_pairs[b] += up;
-        if (blockIdx.x == 0) *C.step += 1ull;
+        if (add && blockIdx.x == 0) *C.step += (unsigned long long)add;
+    } else if (copy_dyn && r >= 128 && r < 128 + (int)(sizeof(BoxDyn) / sizeof(int))) {
+        ((int*)&C.dyn[b])[r - 128] = ((const int*)&C.dyn[(size_t)C.n_boxes + b])[r - 128];
     }
 }
+
+__global__ void k_step_add(unsigned long long* __restrict__ step, int add) { *step += (unsigned long long)add; }
 
 // Copy the snapshot state of the selected boxes back (one workgroup per box)
 // and clear their flags.
@@ -1673,30 +1882,32 @@ __global__ void k_finalize(Ctx C, double* __restrict__ stress_out, double* __res
 struct lhmm_micro {
     lhmm_params p{};
     lhmm_micro_config cfg{};
-    int bin_lds_cells = 0, bin_lds_cols = 0, bin_lds_parts = 0;  // dynamic LDS of the binning kernel (ints)
+    int lds_cells = 0, lds_cols = 0;  // dynamic LDS of the binning (ints)
+    int n_slabs = 0, window = 1;      // slabs of all boxes; steps whose partial sums are kept
+    std::vector<double> hz;           // largest z extent each box has had (bounds its cells per column)
     int n_boxes = 0, n_blocks = 0, precision = LHMM_FP32;
     long long n_total = 0;
     size_t real_size = 4;
     std::vector<BoxInfo> box;
-    std::vector<int> blk_box, blk_first;
+    std::vector<int> blk_box, blk_first, slab_box;
     hipStream_t user_stream = nullptr, stream = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     // device buffers
     BoxInfo* d_box = nullptr;
     BoxDyn* d_dyn = nullptr;
     unsigned* d_flags = nullptr;
-    int *d_blk_box = nullptr, *d_blk_first = nullptr;
+    int *d_blk_box = nullptr, *d_blk_first = nullptr, *d_slab_box = nullptr;
     void *d_s = nullptr, *d_c = nullptr, *d_f = nullptr;
-    int *d_pcell = nullptr, *d_cell_start = nullptr, *d_gcell_start = nullptr;
+    int *d_key = nullptr, *d_perm = nullptr, *d_gcell_start = nullptr;
+    void *d_sid[2] = {}, *d_sord[2] = {}, *d_cord = nullptr;
     void* d_cell_pv = nullptr;
     void* d_srec = nullptr;
-    double *d_part_vir = nullptr, *d_part_kin = nullptr;
-    unsigned* d_part_pairs = nullptr;
+    double *d_part = nullptr, *d_vol = nullptr;
     double *d_acc = nullptr, *d_parts = nullptr, *d_gradL = nullptr;
     unsigned long long *d_acc_pairs = nullptr, *d_tot_pairs = nullptr, *d_step = nullptr;
-    unsigned long long* d_gstep = nullptr;  // step counters of the groups inside a captured chunk
     // selection lists (device) and their pinned staging, reused once ev_sel completes
-    int *d_sel = nullptr, *d_blk_list = nullptr, *h_sel = nullptr;
+    int *d_sel = nullptr, *h_sel = nullptr;
+    size_t sel_cap = 0;
     hipEvent_t ev_sel = nullptr;
     // snapshot of the particle state and per-box cells
     void *d_snap_s = nullptr, *d_snap_c = nullptr, *d_snap_f = nullptr;
@@ -1705,22 +1916,16 @@ struct lhmm_micro {
     bool have_state = false, forces_valid = false;
     bool afbc = false;  // some box has boundary regions (lhmm_micro_set_afbc)
     std::map<int, hipGraphExec_t> graphs;
-    // graphs of subset steps, keyed by (boxes, blocks, steps): a shape is
+    // graphs of subset steps, keyed by (boxes, blocks, slabs, steps): a shape is
     // captured the second time it is asked for (history replays repeat it)
-    std::map<std::tuple<int, int, int>, hipGraphExec_t> sub_graphs;
-    std::map<std::tuple<int, int, int>, int> sub_seen;
+    std::map<std::tuple<int, int, int, int>, hipGraphExec_t> sub_graphs;
+    std::map<std::tuple<int, int, int, int>, int> sub_seen;
     // overlapped groups of boxes (cfg.groups > 1): boxes by particle count,
     // smallest first; inside a captured chunk of steps each group runs all
-    // its steps (binning, forces, stress) on its own stream with its own step
-    // counter, and the groups join at the chunk's end
+    // its steps on its own stream, and the groups join at the chunk's end
     struct Group {
-        int* d_sel = nullptr;
-        int* d_blk = nullptr;
-        int n_sel = 0, nblk = 0, lds_cells = 0, lds_cols = 0, lds_parts = 0;
-        // split binning (cfg.bin_split > 0, the group of the largest boxes)
-        int n_chunks = 0;
-        int* d_split = nullptr;  // box_chunk0, chunk_boxj, cnt, off, col in one allocation
-        SplitArgs S{};
+        int* d_lists = nullptr;  // sel, blk0, blk_list, slab_list in one allocation
+        int n_sel = 0, nblk = 0, nslab = 0, part0 = 0;
     };
     std::vector<Group> groups;
     hipStream_t aux[MAX_GROUPS - 1] = {};
@@ -1734,38 +1939,60 @@ namespace {
 // n2 >= 2 zsub + 1, or n0, n1 <= 3 when the grid had to be clipped.
 int box_cols(const BoxInfo& B) { return std::max(B.cell_cap / (2 * B.zsub + 1), 9) + 1; }
 
+// What a launch covers: all boxes (C without lists), or the lists in C.
+struct Launch {
+    Ctx C;
+    int nbox, nblk, nslab, part0;
+    bool wide;  // sixteen lanes per particle (its partial sums take WIDE_UNITS places per block, from 0)
+    hipStream_t st;
+};
+
+// Sixteen lanes per particle where one lane each would leave the chip idle:
+// below 256 work blocks of 256 particles (a wave per SIMD) k_forces's time is
+// that of one wave's dependent loads and rounds.  The wide kernel has no
+// variant for boundary regions or pruning.
+bool use_wide(const lhmm_micro* m, int nblk) { return nblk <= WIDE_BLOCKS && !m->afbc && !m->cfg.prune; }
+
+Launch all_boxes(lhmm_micro* m) {
+    return Launch{m->ctx, m->n_boxes, m->n_blocks, m->n_slabs, 0, use_wide(m, m->n_blocks), m->stream};
+}
+
 template <typename real>
-void launch_bin(lhmm_micro* m, const Ctx& C, int nbox, hipStream_t st, int fuse, int lc = 0, int lcol = 0,
-                int lp = 0) {
-    if (lc == 0) {
-        lc = m->bin_lds_cells;
-        lcol = m->bin_lds_cols;
-        lp = m->bin_lds_parts;
-    }
-    const size_t bytes = sizeof(int) * ((size_t)lc + 3 * (size_t)lcol + (size_t)lp);
-    switch (m->cfg.bin_threads) {
-        case 256: k_bin_box<real, 256><<<nbox, 256, bytes, st>>>(C, lc, lcol, lp, fuse); break;
-        case 512: k_bin_box<real, 512><<<nbox, 512, bytes, st>>>(C, lc, lcol, lp, fuse); break;
-        default: k_bin_box<real, 1024><<<nbox, 1024, bytes, st>>>(C, lc, lcol, lp, fuse); break;
+void launch_bin(lhmm_micro* m, const Launch& L, const Step& A) {
+    const int T = m->cfg.bin_threads, nc = (L.nbox + T - 1) / T;
+    const size_t bytes = sizeof(int) * ((size_t)m->lds_cells + 3 * (size_t)m->lds_cols + 2 * (size_t)SLAB_CAP);
+    const int grid = nc + L.nslab;
+    switch (T) {
+        case 256: k_bin<real, 256><<<grid, 256, bytes, L.st>>>(L.C, A, nc, m->lds_cells, m->lds_cols); break;
+        case 512: k_bin<real, 512><<<grid, 512, bytes, L.st>>>(L.C, A, nc, m->lds_cells, m->lds_cols); break;
+        default: k_bin<real, 1024><<<grid, 1024, bytes, L.st>>>(L.C, A, nc, m->lds_cells, m->lds_cols); break;
     }
 }
 
-// kick = 1: a full step's force pass, which ends with the second half kick
 template <typename real>
-void launch_forces(lhmm_micro* m, const Ctx& C, int nblk, int step_offset, int kick, hipStream_t st) {
+void launch_forces(lhmm_micro* m, const Launch& L, const Step& A) {
     const int drain = m->cfg.drain, busy = m->cfg.busy_lanes;
-#define LHMM_FORCES(QD)                                                                              \
-    do {                                                                                             \
-        if (m->afbc && C.pv_stride > 12)                                                             \
-            k_forces<real, QD, false, true, true><<<nblk, BS, 0, st>>>(C, step_offset, drain, busy, kick);  \
-        else if (m->afbc)                                                                            \
-            k_forces<real, QD, false, false, true><<<nblk, BS, 0, st>>>(C, step_offset, drain, busy, kick); \
-        else if (C.pv_stride > 12)                                                                   \
-            k_forces<real, QD, false, true><<<nblk, BS, 0, st>>>(C, step_offset, drain, busy, kick);        \
-        else if (m->cfg.prune)                                                                       \
-            k_forces<real, QD, true><<<nblk, BS, 0, st>>>(C, step_offset, drain, busy, kick);               \
-        else                                                                                         \
-            k_forces<real, QD, false><<<nblk, BS, 0, st>>>(C, step_offset, drain, busy, kick);              \
+    const Ctx& C = L.C;
+    const bool comp = C.nv > 19;
+    if (L.wide) {
+        if (comp)
+            k_forces_wide<real, true><<<L.nblk * WIDE_UNITS, BS, 0, L.st>>>(C, A);
+        else
+            k_forces_wide<real, false><<<L.nblk * WIDE_UNITS, BS, 0, L.st>>>(C, A);
+        return;
+    }
+#define LHMM_FORCES(QD)                                                                      \
+    do {                                                                                     \
+        if (m->afbc && comp)                                                                 \
+            k_forces<real, QD, false, true, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);  \
+        else if (m->afbc)                                                                    \
+            k_forces<real, QD, false, false, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy); \
+        else if (comp)                                                                       \
+            k_forces<real, QD, false, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);        \
+        else if (m->cfg.prune)                                                               \
+            k_forces<real, QD, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);               \
+        else                                                                                 \
+            k_forces<real, QD, false><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);              \
     } while (0)
     switch (m->cfg.queue_depth) {
         case 2: LHMM_FORCES(2); break;
@@ -1777,124 +2004,114 @@ void launch_forces(lhmm_micro* m, const Ctx& C, int nblk, int step_offset, int k
 #undef LHMM_FORCES
 }
 
-// One step (or a force evaluation) of the boxes C selects: all n_boxes boxes
-// and n_blocks work blocks, or the n_sel selected boxes and their nblk blocks.
-template <typename real>
-void launch_step_kernels(lhmm_micro* m, const Ctx& C, int nbox, int nblk, int step_offset, bool advance,
-                         bool full_step) {
-    const int bt = 256, bg = (nbox + bt - 1) / bt;
-    if (m->cfg.fuse_bin) {
-        launch_bin<real>(m, C, nbox, m->stream, advance ? 1 : 0);
-    } else {
-        k_cell_step<<<bg, bt, 0, m->stream>>>(C, advance ? 1 : 0);
-        k_kick_drift<real><<<nblk, BS, 0, m->stream>>>(C, advance ? 1 : 0);
-        launch_bin<real>(m, C, nbox, m->stream, -1);
+void launch_flush(lhmm_micro* m, const Launch& L, int nw, bool copy_dyn, int add) {
+    const int wide = L.wide ? 1 : 0;
+    if (L.C.nv > 19)
+        k_flush<37><<<L.nbox, FLUSH_THREADS, 0, L.st>>>(L.C, nw, L.part0, wide, copy_dyn ? 1 : 0, add);
+    else
+        k_flush<19><<<L.nbox, FLUSH_THREADS, 0, L.st>>>(L.C, nw, L.part0, wide, copy_dyn ? 1 : 0, add);
+}
+
+// n steps of the boxes L covers, the random-force counters *C.step + k0 + 1
+// .. k0 + n; add: advance *C.step by that much at the end.  between(q, i):
+// called around the launches (q: the kernel, i = 0 before, 1 after).
+template <typename real, class Between>
+void launch_chunk(lhmm_micro* m, const Launch& L, int k0, int n, int add, Between between) {
+    between(LHMM_K_KICK_DRIFT, 0);
+    k_begin_chunk<real><<<L.nblk, BS, 0, L.st>>>(L.C, k0, 1);
+    between(LHMM_K_KICK_DRIFT, 1);
+    for (int k = 1; k <= n; ++k) {
+        Step A{};
+        A.slot = k & 1;
+        A.first = k == 1;
+        A.more = k < n;
+        A.kick = 1;
+        A.w = (k - 1) % m->window;
+        A.k = k0 + k;
+        A.part0 = L.part0;
+        between(LHMM_K_BIN, 0);
+        launch_bin<real>(m, L, A);
+        between(LHMM_K_BIN, 1);
+        between(LHMM_K_FORCES, 0);
+        launch_forces<real>(m, L, A);
+        between(LHMM_K_FORCES, 1);
+        if (A.w == m->window - 1 || k == n) {
+            between(LHMM_K_STRESS, 0);
+            launch_flush(m, L, A.w + 1, k == n && (n & 1), k == n ? add : 0);
+            between(LHMM_K_STRESS, 1);
+        }
     }
-    launch_forces<real>(m, C, nblk, step_offset, full_step ? 1 : 0, m->stream);
-    if (full_step) k_box_stress<<<nbox, 64, 0, m->stream>>>(C);
 }
 
-// One step with an event pair around each kernel (ev: 2 * LHMM_N_KERNELS events).
-template <typename real>
-void launch_step_timed(lhmm_micro* m, hipEvent_t* ev) {
-    const Ctx& C = m->ctx;
-    const int bt = 256, bg = (m->n_boxes + bt - 1) / bt;
-    hipStream_t st = m->stream;
-    // with the fused binning kernel the cell step and kick-drift pairs time nothing
-    const bool fused = m->cfg.fuse_bin != 0;
-    (void)hipEventRecord(ev[0], st);
-    if (!fused) k_cell_step<<<bg, bt, 0, st>>>(C, 1);
-    (void)hipEventRecord(ev[1], st);
-    (void)hipEventRecord(ev[2], st);
-    if (!fused) k_kick_drift<real><<<m->n_blocks, BS, 0, st>>>(C, 1);
-    (void)hipEventRecord(ev[3], st);
-    (void)hipEventRecord(ev[4], st);
-    launch_bin<real>(m, C, m->n_boxes, st, fused ? 1 : -1);
-    (void)hipEventRecord(ev[5], st);
-    (void)hipEventRecord(ev[6], st);
-    launch_forces<real>(m, C, m->n_blocks, 1, 1, st);
-    (void)hipEventRecord(ev[7], st);
-    (void)hipEventRecord(ev[8], st);  // the second half kick runs inside the force kernel
-    (void)hipEventRecord(ev[9], st);
-    (void)hipEventRecord(ev[10], st);
-    k_box_stress<<<m->n_boxes, 64, 0, st>>>(C);
-    (void)hipEventRecord(ev[11], st);
+// With fuse_bin off every step takes the particles from and back to index
+// order: the half kick and drift run as their own launch.
+template <typename real, class Between>
+void launch_steps(lhmm_micro* m, const Launch& L, int n, bool add, Between between) {
+    if (m->cfg.fuse_bin) {
+        launch_chunk<real>(m, L, 0, n, add ? n : 0, between);
+        return;
+    }
+    for (int k = 0; k < n; ++k) launch_chunk<real>(m, L, k, 1, add && k + 1 == n ? n : 0, between);
 }
 
-// Copy the step counter *src to dst[0 .. n-1].
-__global__ void k_step_copy(unsigned long long* __restrict__ dst, const unsigned long long* __restrict__ src, int n) {
-    if ((int)threadIdx.x < n) dst[threadIdx.x] = *src;
+void launch_steps(lhmm_micro* m, const Launch& L, int n, bool add = true) {
+    auto nothing = [](int, int) {};
+    if (m->precision == LHMM_FP64)
+        launch_steps<double>(m, L, n, add, nothing);
+    else
+        launch_steps<float>(m, L, n, add, nothing);
 }
 
 // A captured chunk of nsteps steps with the boxes in overlapped groups.  The
-// boxes of one group never read another group's data, so each group runs
-// its whole chunk (fused binning, forces, stress) on its own stream with its
-// own copy of the step counter: a group with small boxes does not wait each
-// step for the binning of the largest ones.  The counters fork from the
-// engine's at the start and join into it at the end; every box computes
-// exactly what the stepwise order computes.
-template <typename real>
+// boxes of one group never read another group's data, so each group runs its
+// whole chunk on its own stream; the step counter advances once they joined.
 void launch_chunk_grouped(lhmm_micro* m, int nsteps) {
     const int G = (int)m->groups.size();
-    k_step_copy<<<1, 64, 0, m->stream>>>(m->d_gstep, m->d_step, G);
     (void)hipEventRecord(m->ev_fork, m->stream);
     for (int g = 1; g < G; ++g) (void)hipStreamWaitEvent(m->aux[g - 1], m->ev_fork, 0);
     for (int g = 0; g < G; ++g) {
         const lhmm_micro::Group& gr = m->groups[g];
-        hipStream_t st = g == 0 ? m->stream : m->aux[g - 1];
-        Ctx C = m->ctx;
-        C.sel = gr.d_sel;
-        C.blk_list = gr.d_blk;
-        C.n_sel = gr.n_sel;
-        C.step = m->d_gstep + g;
-        for (int k = 0; k < nsteps; ++k) {
-            if (gr.n_chunks > 0) {
-                const SplitArgs& S = gr.S;
-                const size_t scan_lds = sizeof(int) * ((size_t)gr.lds_cells + 3 * (size_t)gr.lds_cols);
-                k_cell_step<<<(gr.n_sel + 255) / 256, 256, 0, st>>>(C, 1);
-                k_bin_count<real><<<gr.n_chunks, SPLIT_BT, sizeof(int) * (size_t)S.cap, st>>>(C, S);
-                k_bin_scan<<<gr.n_sel, SPLIT_BT, scan_lds, st>>>(C, S, gr.lds_cells, gr.lds_cols);
-                k_bin_scatter<real><<<gr.n_chunks, SPLIT_BT, sizeof(int) * ((size_t)S.cap + S.chunk), st>>>(C, S);
-            } else {
-                launch_bin<real>(m, C, gr.n_sel, st, 1, gr.lds_cells, gr.lds_cols, gr.lds_parts);
-            }
-            launch_forces<real>(m, C, gr.nblk, 1, 1, st);
-            k_box_stress<<<gr.n_sel, 64, 0, st>>>(C);
-        }
+        Launch L{m->ctx, gr.n_sel, gr.nblk, gr.nslab, gr.part0, false, g == 0 ? m->stream : m->aux[g - 1]};
+        L.C.sel = gr.d_lists;
+        L.C.blk0 = gr.d_lists + gr.n_sel;
+        L.C.blk_list = gr.d_lists + 2 * gr.n_sel;
+        L.C.slab_list = gr.d_lists + 2 * gr.n_sel + gr.nblk;
+        L.C.n_sel = gr.n_sel;
+        launch_steps(m, L, nsteps, false);
     }
     for (int g = 1; g < G; ++g) {
         (void)hipEventRecord(m->ev_join[g - 1], m->aux[g - 1]);
         (void)hipStreamWaitEvent(m->stream, m->ev_join[g - 1], 0);
     }
-    k_step_copy<<<1, 64, 0, m->stream>>>(m->d_step, m->d_gstep, 1);
+    k_step_add<<<1, 1, 0, m->stream>>>(m->d_step, nsteps);
 }
 
-void launch_one_step(lhmm_micro* m) {
-    if (m->precision == LHMM_FP64)
-        launch_step_kernels<double>(m, m->ctx, m->n_boxes, m->n_blocks, 1, true, true);
-    else
-        launch_step_kernels<float>(m, m->ctx, m->n_boxes, m->n_blocks, 1, true, true);
-}
-
-void launch_one_step_sel(lhmm_micro* m, const Ctx& C, int nbox, int nblk) {
-    if (m->precision == LHMM_FP64)
-        launch_step_kernels<double>(m, C, nbox, nblk, 1, true, true);
-    else
-        launch_step_kernels<float>(m, C, nbox, nblk, 1, true, true);
-}
-
-void launch_remove_mean(lhmm_micro* m, const Ctx& C, int nbox) {
-    if (m->precision == LHMM_FP64)
-        k_remove_mean<double><<<nbox, 256, 0, m->stream>>>(C);
-    else
-        k_remove_mean<float><<<nbox, 256, 0, m->stream>>>(C);
+// Set-up of a call: gradients and cleared sums of every box, zero mean
+// velocity of the boxes L covers; the forces if none are carried.
+template <typename real>
+void launch_force_eval_t(lhmm_micro* m) {
+    const Launch L = all_boxes(m);
+    Step A{};
+    A.slot = 1;
+    A.first = 1;
+    k_begin_chunk<real><<<L.nblk, BS, 0, L.st>>>(L.C, 0, 0);
+    launch_bin<real>(m, L, A);
+    launch_forces<real>(m, L, A);
 }
 
 void launch_force_eval(lhmm_micro* m) {
     if (m->precision == LHMM_FP64)
-        launch_step_kernels<double>(m, m->ctx, m->n_boxes, m->n_blocks, 0, false, false);
+        launch_force_eval_t<double>(m);
     else
-        launch_step_kernels<float>(m, m->ctx, m->n_boxes, m->n_blocks, 0, false, false);
+        launch_force_eval_t<float>(m);
+}
+
+void launch_begin_call(lhmm_micro* m, const Ctx& C, int n_mean, const double* gradL) {
+    const int grid = n_mean + (m->n_boxes + 63) / 64;
+    if (m->precision == LHMM_FP64)
+        k_begin_call<double><<<grid, CALL_THREADS, 0, m->stream>>>(C, gradL, n_mean);
+    else
+        k_begin_call<float><<<grid, CALL_THREADS, 0, m->stream>>>(C, gradL, n_mean);
 }
 
 int get_graph(lhmm_micro* m, int nsteps, hipGraphExec_t* out) {
@@ -1904,14 +2121,13 @@ int get_graph(lhmm_micro* m, int nsteps, hipGraphExec_t* out) {
         return LHMM_OK;
     }
     hipGraph_t g = nullptr;
-    const bool grouped = m->groups.size() > 1 && m->cfg.fuse_bin;
+    // launches that use the wide force kernel do not fill the chip: one stream
+    const bool grouped = m->groups.size() > 1 && m->cfg.fuse_bin && !use_wide(m, m->n_blocks);
     HIPCHK(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));
-    if (!grouped)
-        for (int k = 0; k < nsteps; ++k) launch_one_step(m);
-    else if (m->precision == LHMM_FP64)
-        launch_chunk_grouped<double>(m, nsteps);
+    if (grouped)
+        launch_chunk_grouped(m, nsteps);
     else
-        launch_chunk_grouped<float>(m, nsteps);
+        launch_steps(m, all_boxes(m), nsteps);
     HIPCHK(hipStreamEndCapture(m->stream, &g));
     hipGraphExec_t ex = nullptr;
     hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
@@ -1944,18 +2160,15 @@ void release(lhmm_micro* m) {
     m->graphs.clear();
     for (auto& kv : m->sub_graphs) (void)hipGraphExecDestroy(kv.second);
     m->sub_graphs.clear();
-    void* bufs[] = {m->d_box, m->d_dyn, m->d_flags, m->d_blk_box, m->d_blk_first, m->d_s, m->d_c, m->d_f,
-                    m->d_pcell, m->d_cell_start, m->d_gcell_start, m->d_cell_pv, m->d_srec,
-                    m->d_part_vir, m->d_part_kin,
-                    m->d_part_pairs, m->d_acc, m->d_parts, m->d_gradL, m->d_acc_pairs, m->d_tot_pairs, m->d_step, m->d_gstep,
-                    m->d_sel, m->d_blk_list, m->d_snap_s, m->d_snap_c, m->d_snap_f, m->d_snap_dyn};
+    void* bufs[] = {m->d_box, m->d_dyn, m->d_flags, m->d_blk_box, m->d_blk_first, m->d_slab_box, m->d_s, m->d_c, m->d_f,
+                    m->d_key, m->d_perm, m->d_gcell_start, m->d_sid[0], m->d_sid[1], m->d_sord[0], m->d_sord[1],
+                    m->d_cord, m->d_cell_pv, m->d_srec, m->d_part, m->d_vol, m->d_acc, m->d_parts, m->d_gradL,
+                    m->d_acc_pairs, m->d_tot_pairs, m->d_step, m->d_sel, m->d_snap_s, m->d_snap_c, m->d_snap_f,
+                    m->d_snap_dyn};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
-    for (auto& gr : m->groups) {
-        if (gr.d_sel) (void)hipFree(gr.d_sel);
-        if (gr.d_blk) (void)hipFree(gr.d_blk);
-        if (gr.d_split) (void)hipFree(gr.d_split);
-    }
+    for (auto& gr : m->groups)
+        if (gr.d_lists) (void)hipFree(gr.d_lists);
     m->groups.clear();
     for (int g = 0; g < MAX_GROUPS - 1; ++g) {
         if (m->aux[g]) (void)hipStreamDestroy(m->aux[g]);
@@ -1979,9 +2192,10 @@ constexpr size_t MAX_SUB_GRAPHS = 64;
 
 // len steps of the selected boxes: a captured graph for a shape seen before,
 // else eager launches.  The graph reads the selection lists from the fixed
-// device buffers, so any selection of the same shape can replay it.
-int launch_subset_steps(lhmm_micro* m, const Ctx& C, int n_sel, int nblk, int len) {
-    const auto key = std::make_tuple(n_sel, nblk, len);
+// device buffer, whose layout goes by the shape, so any selection of the same
+// shape can replay it.
+int launch_subset_steps(lhmm_micro* m, const Launch& L, int len) {
+    const auto key = std::make_tuple(L.nbox, L.nblk, L.nslab, len);
     auto it = m->sub_graphs.find(key);
     if (it == m->sub_graphs.end() && ++m->sub_seen[key] >= 2) {
         if (m->sub_graphs.size() >= MAX_SUB_GRAPHS) {
@@ -1990,7 +2204,7 @@ int launch_subset_steps(lhmm_micro* m, const Ctx& C, int n_sel, int nblk, int le
         }
         hipGraph_t g = nullptr;
         HIPCHK(hipStreamBeginCapture(m->stream, hipStreamCaptureModeThreadLocal));
-        for (int k = 0; k < len; ++k) launch_one_step_sel(m, C, n_sel, nblk);
+        launch_steps(m, L, len);
         HIPCHK(hipStreamEndCapture(m->stream, &g));
         hipGraphExec_t ex = nullptr;
         hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
@@ -2001,20 +2215,89 @@ int launch_subset_steps(lhmm_micro* m, const Ctx& C, int n_sel, int nblk, int le
     if (it != m->sub_graphs.end()) {
         HIPCHK(hipGraphLaunch(it->second, m->stream));
     } else {
-        for (int k = 0; k < len; ++k) launch_one_step_sel(m, C, n_sel, nblk);
+        launch_steps(m, L, len);
     }
     return LHMM_OK;
 }
 
+// LDS of the binning for the boxes' present z extents.  The cells of a
+// column are at most those of the largest z extent the box has had.
+void bin_lds(lhmm_micro* m) {
+    m->lds_cells = m->lds_cols = 0;
+    for (int b = 0; b < m->n_boxes; ++b) {
+        const BoxInfo& B = m->box[b];
+        const long long nz = (long long)std::floor(B.zsub * m->hz[b] / m->p.rc * (1.0 + 1e-9));
+        // the grid is clipped to cell_cap cells with at least 9 columns
+        const int n2 = (int)std::min<long long>(std::max<long long>(nz, 2 * B.zsub + 1), std::max(B.cell_cap / 9, 2 * B.zsub + 1));
+        const int cols = box_cols(B);
+        m->lds_cells = std::max(m->lds_cells, std::min(B.cell_cap, B.cell_cap / B.nslab + n2) + 1);
+        m->lds_cols = std::max(m->lds_cols, std::min(cols, cols / B.nslab + 2));
+    }
+}
+
+// Cut the boxes into slabs for the binning: about SLAB_TARGET particles (or
+// bin_split, where that is smaller) and at most SLAB_CELLS cells each.
+int build_slabs(lhmm_micro* m) {
+    const int target = m->cfg.bin_split > 0 ? std::min(m->cfg.bin_split, SLAB_TARGET) : SLAB_TARGET;
+    m->slab_box.clear();
+    for (int b = 0; b < m->n_boxes; ++b) {
+        BoxInfo& B = m->box[b];
+        B.slab_off = (int)m->slab_box.size();
+        // every column belongs to one slab, so more slabs than columns (9 at least) would only idle
+        B.nslab = std::max((B.n + target - 1) / target, (B.cell_cap + SLAB_CELLS - 1) / SLAB_CELLS);
+        B.nslab = std::min(B.nslab, box_cols(B));
+        for (int q = 0; q < B.nslab; ++q) m->slab_box.push_back(b);
+    }
+    m->n_slabs = (int)m->slab_box.size();
+    bin_lds(m);
+    if (m->d_slab_box) HIPCHK(hipFree(m->d_slab_box));
+    m->d_slab_box = nullptr;
+    int rc = dalloc(&m->d_slab_box, (size_t)m->n_slabs);
+    if (rc != LHMM_OK) return rc;
+    HIPCHK(hipMemcpy(m->d_slab_box, m->slab_box.data(), m->n_slabs * sizeof(int), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(m->d_box, m->box.data(), m->n_boxes * sizeof(BoxInfo), hipMemcpyHostToDevice));
+    m->ctx.slab_box = m->d_slab_box;
+    return LHMM_OK;
+}
+
+// Drop every captured graph (they hold launch shapes and contexts).
+void drop_graphs(lhmm_micro* m) {
+    for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
+    m->graphs.clear();
+    for (auto& kv : m->sub_graphs) (void)hipGraphExecDestroy(kv.second);
+    m->sub_graphs.clear();
+    m->sub_seen.clear();
+}
+
+// Lists of a selection in one host array: the boxes, each one's first work
+// block in the block list, the work blocks, the slabs.
+struct Lists {
+    int nblk = 0, nslab = 0;
+};
+
+Lists fill_lists(const lhmm_micro* m, const int* boxes, int n_sel, int* out) {
+    Lists L;
+    int *sel = out, *blk0 = out + n_sel, *blk = out + 2 * n_sel;
+    for (int q = 0; q < n_sel; ++q) {
+        const BoxInfo& B = m->box[boxes[q]];
+        sel[q] = boxes[q];
+        blk0[q] = L.nblk;
+        for (int k = 0; k < B.nblk; ++k) blk[L.nblk++] = B.blk_off + k;
+    }
+    int* slab = blk + L.nblk;
+    for (int q = 0; q < n_sel; ++q) {
+        const BoxInfo& B = m->box[boxes[q]];
+        for (int k = 0; k < B.nslab; ++k) slab[L.nslab++] = B.slab_off + k;
+    }
+    return L;
+}
+
 // Partition the boxes into G groups by particle count (smallest first), with
-// their block lists and binning LDS.
+// their lists.
 int prepare_groups(lhmm_micro* m, int G) {
     HIPCHK(hipStreamSynchronize(m->stream));
-    for (auto& gr : m->groups) {
-        if (gr.d_sel) (void)hipFree(gr.d_sel);
-        if (gr.d_blk) (void)hipFree(gr.d_blk);
-        if (gr.d_split) (void)hipFree(gr.d_split);
-    }
+    for (auto& gr : m->groups)
+        if (gr.d_lists) (void)hipFree(gr.d_lists);
     m->groups.clear();
     if (G <= 1) return LHMM_OK;
     if (!m->ev_fork) {
@@ -2038,104 +2321,60 @@ int prepare_groups(lhmm_micro* m, int G) {
         members[std::min(g, G - 1)].push_back(b);
         acc += m->box[b].n;
     }
+    int part0 = 0;
+    std::vector<int> lists(2 * (size_t)m->n_boxes + m->n_blocks + m->n_slabs);
     for (int g = 0; g < G; ++g) {
         if (members[g].empty()) continue;
         std::sort(members[g].begin(), members[g].end());
         lhmm_micro::Group gr;
-        std::vector<int> blks;
-        int max_cells = 0, max_cols = 0, max_n = 0;
-        for (int b : members[g]) {
-            const BoxInfo& B = m->box[b];
-            for (int k = 0; k < B.nblk; ++k) blks.push_back(B.blk_off + k);
-            max_cells = std::max(max_cells, B.cell_cap + 1);
-            max_cols = std::max(max_cols, box_cols(B));
-            max_n = std::max(max_n, B.n);
-        }
         gr.n_sel = (int)members[g].size();
-        gr.nblk = (int)blks.size();
-        gr.lds_cells = max_cells;
-        gr.lds_cols = max_cols;
-        const int fixed = max_cells + 3 * max_cols;
-        const int room = m->bin_lds_cells + 3 * m->bin_lds_cols + m->bin_lds_parts - fixed;
-        gr.lds_parts = std::max(0, std::min(max_n, room));
-        int rc = dalloc(&gr.d_sel, gr.n_sel);
-        if (rc == LHMM_OK) rc = dalloc(&gr.d_blk, gr.nblk);
-        if (rc != LHMM_OK) {
-            if (gr.d_sel) (void)hipFree(gr.d_sel);
-            return rc;
-        }
-        if (g == G - 1 && m->cfg.bin_split > 0) {
-            // chunks of the largest boxes for the split binning
-            const int chunk = m->cfg.bin_split;
-            std::vector<int> box_chunk0(gr.n_sel + 1, 0), chunk_boxj;
-            for (int q = 0; q < gr.n_sel; ++q) {
-                const int nck = std::max(1, (m->box[members[g][q]].n + chunk - 1) / chunk);
-                box_chunk0[q + 1] = box_chunk0[q] + nck;
-                for (int c = 0; c < nck; ++c) chunk_boxj.push_back(q);
-            }
-            gr.n_chunks = box_chunk0[gr.n_sel];
-            const int cap = max_cells, colcap = max_cols;
-            const size_t ints = (size_t)(gr.n_sel + 1) + gr.n_chunks + 2 * (size_t)gr.n_chunks * cap +
-                                3 * (size_t)gr.n_sel * colcap;
-            rc = dalloc(&gr.d_split, ints);
-            if (rc != LHMM_OK) {
-                (void)hipFree(gr.d_sel);
-                (void)hipFree(gr.d_blk);
-                return rc;
-            }
-            int* base = gr.d_split;
-            gr.S.box_chunk0 = base;
-            gr.S.chunk_boxj = base + gr.n_sel + 1;
-            gr.S.cnt = base + gr.n_sel + 1 + gr.n_chunks;
-            gr.S.off = gr.S.cnt + (size_t)gr.n_chunks * cap;
-            gr.S.col = gr.S.off + (size_t)gr.n_chunks * cap;
-            gr.S.chunk = chunk;
-            gr.S.cap = cap;
-            gr.S.colcap = colcap;
-            HIPCHK(hipMemcpy(base, box_chunk0.data(), sizeof(int) * box_chunk0.size(), hipMemcpyHostToDevice));
-            HIPCHK(hipMemcpy(base + gr.n_sel + 1, chunk_boxj.data(), sizeof(int) * chunk_boxj.size(),
-                             hipMemcpyHostToDevice));
-        }
+        const Lists L = fill_lists(m, members[g].data(), gr.n_sel, lists.data());
+        gr.nblk = L.nblk;
+        gr.nslab = L.nslab;
+        gr.part0 = part0;
+        part0 += L.nblk;
+        const size_t n = 2 * (size_t)gr.n_sel + L.nblk + L.nslab;
+        int rc = dalloc(&gr.d_lists, n);
+        if (rc != LHMM_OK) return rc;
         m->groups.push_back(gr);
-        HIPCHK(hipMemcpy(gr.d_sel, members[g].data(), sizeof(int) * gr.n_sel, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(gr.d_blk, blks.data(), sizeof(int) * gr.nblk, hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(gr.d_lists, lists.data(), sizeof(int) * n, hipMemcpyHostToDevice));
     }
     return LHMM_OK;
 }
 
 // Validate a host list of boxes (strictly increasing, in range), upload it
-// and the list of their work blocks on the engine stream, and return a
-// context that selects them.
-int select_boxes(lhmm_micro* m, const int32_t* boxes, int32_t n_sel, Ctx* out, int* nblk) {
+// with its lists on the engine stream, and return a launch that covers them.
+int select_boxes(lhmm_micro* m, const int32_t* boxes, int32_t n_sel, Launch* out) {
     if (!boxes || n_sel < 1 || n_sel > m->n_boxes) return fail(LHMM_ERR_ARG, "need 1..%d boxes (got %d)", m->n_boxes, n_sel);
     for (int q = 0; q < n_sel; ++q) {
         if (boxes[q] < 0 || boxes[q] >= m->n_boxes) return fail(LHMM_ERR_ARG, "box %d out of range", boxes[q]);
         if (q && boxes[q] <= boxes[q - 1]) return fail(LHMM_ERR_ARG, "boxes must be strictly increasing");
     }
-    if (!m->d_sel) {
-        int rc = dalloc(&m->d_sel, m->n_boxes);
-        if (rc == LHMM_OK) rc = dalloc(&m->d_blk_list, m->n_blocks);
+    const size_t cap = 2 * (size_t)m->n_boxes + m->n_blocks + m->n_slabs;
+    if (m->sel_cap < cap) {  // first use, or more slabs than before (set_config waited and dropped the graphs)
+        if (m->d_sel) HIPCHK(hipFree(m->d_sel));
+        m->d_sel = nullptr;
+        if (m->h_sel) HIPCHK(hipHostFree(m->h_sel));
+        m->h_sel = nullptr;
+        m->sel_cap = 0;
+        int rc = dalloc(&m->d_sel, cap);
         if (rc != LHMM_OK) return rc;
-        HIPCHK(hipHostMalloc((void**)&m->h_sel, sizeof(int) * (m->n_boxes + m->n_blocks)));
-        HIPCHK(hipEventCreateWithFlags(&m->ev_sel, hipEventDisableTiming));
+        HIPCHK(hipHostMalloc((void**)&m->h_sel, sizeof(int) * cap));
+        if (!m->ev_sel) HIPCHK(hipEventCreateWithFlags(&m->ev_sel, hipEventDisableTiming));
+        m->sel_cap = cap;
     } else {
         HIPCHK(hipEventSynchronize(m->ev_sel));  // the previous upload has left the staging buffer
     }
-    int nb = 0;
-    int* hb = m->h_sel + m->n_boxes;
-    for (int q = 0; q < n_sel; ++q) {
-        const BoxInfo& B = m->box[boxes[q]];
-        m->h_sel[q] = boxes[q];
-        for (int k = 0; k < B.nblk; ++k) hb[nb++] = B.blk_off + k;
-    }
-    HIPCHK(hipMemcpyAsync(m->d_sel, m->h_sel, sizeof(int) * n_sel, hipMemcpyHostToDevice, m->stream));
-    HIPCHK(hipMemcpyAsync(m->d_blk_list, hb, sizeof(int) * nb, hipMemcpyHostToDevice, m->stream));
+    const Lists L = fill_lists(m, boxes, n_sel, m->h_sel);
+    const size_t n = 2 * (size_t)n_sel + L.nblk + L.nslab;
+    HIPCHK(hipMemcpyAsync(m->d_sel, m->h_sel, sizeof(int) * n, hipMemcpyHostToDevice, m->stream));
     HIPCHK(hipEventRecord(m->ev_sel, m->stream));
-    *out = m->ctx;
-    out->sel = m->d_sel;
-    out->blk_list = m->d_blk_list;
-    out->n_sel = n_sel;
-    *nblk = nb;
+    *out = Launch{m->ctx, n_sel, L.nblk, L.nslab, 0, use_wide(m, L.nblk), m->stream};
+    out->C.sel = m->d_sel;
+    out->C.blk0 = m->d_sel + n_sel;
+    out->C.blk_list = m->d_sel + 2 * n_sel;
+    out->C.slab_list = m->d_sel + 2 * n_sel + L.nblk;
+    out->C.n_sel = n_sel;
     return LHMM_OK;
 }
 
@@ -2181,7 +2420,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     m->cfg.queue_depth = 16;
     m->cfg.drain = 12;
     m->cfg.busy_lanes = 65;
-    m->cfg.bin_threads = BIN_THREADS_MAX;
+    m->cfg.bin_threads = 512;
     m->cfg.graph_chunk = GRAPH_CHUNK;
     m->cfg.prune = 0;
     m->cfg.fuse_bin = 1;
@@ -2191,7 +2430,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     m->user_stream = (hipStream_t)stream;
 
     long long off = 0;
-    int cell_off = 0, gcell_off = 0, blk_off = 0;
+    int gcell_off = 0, blk_off = 0;
     m->box.resize(n_boxes);
     for (int b = 0; b < n_boxes; ++b) {
         const lhmm_box& in = boxes[b];
@@ -2228,7 +2467,6 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
         B.off = (int)off;
         B.n = in.n_particles;
         B.n_beads = in.n_chains * p->chain_len;
-        B.cell_off = cell_off;
         B.cell_cap = (int)cap;
         B.gcell_off = gcell_off;
         B.zsub = zsub;
@@ -2240,7 +2478,6 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
             m->blk_first.push_back(B.off + k * BS);
         }
         off += in.n_particles;
-        cell_off += (int)cap + 1;
         gcell_off += 2 * (int)cap + 1;  // n0 n1 (n2 + 2 zsub) cells, n2 >= 2 zsub + 1
         blk_off += B.nblk;
         if (off > (1LL << 30)) {
@@ -2250,85 +2487,41 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     }
     m->n_total = off;
     m->n_blocks = blk_off;
-    {
-        // binning LDS: three arrays over every box's cells, and entries for
-        // the boxes that fit in what the workgroup may still use
-        int max_cells = 0, max_cols = 0, max_n = 0;
-        for (const BoxInfo& B : m->box) {
-            max_cells = std::max(max_cells, B.cell_cap + 1);
-            max_cols = std::max(max_cols, box_cols(B));
-            max_n = std::max(max_n, B.n);
-        }
-        int dev = 0, max_lds = 65536;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-            max_lds = 65536;
-        const int budget = (int)((max_lds - 64 * (int)sizeof(int)) / sizeof(int));  // less the scan's wave sums
-        const int fixed = max_cells + 3 * max_cols;  // cells and column offsets
-        if (fixed > budget) {
-            delete m;
-            return fail(LHMM_ERR_ARG, "boxes need %d cells, more than the binning LDS holds", max_cells - 1);
-        }
-        m->bin_lds_cells = max_cells;
-        m->bin_lds_cols = max_cols;
-        m->bin_lds_parts = std::max(0, std::min(max_n, budget - fixed));
-        const size_t bytes = sizeof(int) * ((size_t)fixed + (size_t)m->bin_lds_parts);
-        const void* kernels[] = {(const void*)&k_bin_box<float, 256>, (const void*)&k_bin_box<float, 512>,
-                                 (const void*)&k_bin_box<float, 1024>, (const void*)&k_bin_box<double, 256>,
-                                 (const void*)&k_bin_box<double, 512>, (const void*)&k_bin_box<double, 1024>};
-        for (const void* k : kernels) {
-            hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-            if (e != hipSuccess) {
-                delete m;
-                return fail(LHMM_ERR_HIP, "binning LDS of %zu bytes: %s", bytes, hipGetErrorString(e));
-            }
-        }
-        // split binning: cells + column offsets (scan), cells + a chunk (scatter), cells (count)
-        const size_t split_bytes[] = {sizeof(int) * (size_t)fixed, sizeof(int) * ((size_t)max_cells + SPLIT_PER * SPLIT_BT),
-                                      sizeof(int) * (size_t)max_cells};
-        const void* split_kernels[][2] = {{(const void*)&k_bin_scan, (const void*)&k_bin_scan},
-                                          {(const void*)&k_bin_scatter<float>, (const void*)&k_bin_scatter<double>},
-                                          {(const void*)&k_bin_count<float>, (const void*)&k_bin_count<double>}};
-        for (int q = 0; q < 3; ++q)
-            for (const void* k : split_kernels[q]) {
-                hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)split_bytes[q]);
-                if (e != hipSuccess) {
-                    delete m;
-                    return fail(LHMM_ERR_HIP, "split binning LDS of %zu bytes: %s", split_bytes[q], hipGetErrorString(e));
-                }
-            }
-    }
+    m->hz.resize(n_boxes);
+    for (int b = 0; b < n_boxes; ++b) m->hz[b] = boxes[b].h0[8];
     const size_t N = (size_t)m->n_total;
     int rc = LHMM_OK;
 #define ALLOC(ptr, cnt)                     \
     if (rc == LHMM_OK) rc = dalloc(&(ptr), (cnt));
     ALLOC(m->d_box, (size_t)n_boxes);
-    ALLOC(m->d_dyn, (size_t)n_boxes);
+    ALLOC(m->d_dyn, 2 * (size_t)n_boxes);
     ALLOC(m->d_flags, (size_t)n_boxes);
     ALLOC(m->d_blk_box, (size_t)m->n_blocks);
     ALLOC(m->d_blk_first, (size_t)m->n_blocks);
-    ALLOC(m->d_pcell, N);
-    ALLOC(m->d_cell_start, (size_t)cell_off);
+    ALLOC(m->d_key, N);
+    ALLOC(m->d_perm, N);
     ALLOC(m->d_gcell_start, (size_t)gcell_off);
-    const int pv_stride = (p->flags & LHMM_OPT_COMPONENTS) ? 30 : 12;
-    ALLOC(m->d_part_vir, (size_t)m->n_blocks * pv_stride);
-    ALLOC(m->d_part_kin, (size_t)m->n_blocks * 6);
-    ALLOC(m->d_part_pairs, (size_t)m->n_blocks);
+    const int nv = (p->flags & LHMM_OPT_COMPONENTS) ? 37 : 19;
+    const size_t part_step = nv * std::max((size_t)m->n_blocks, (size_t)WIDE_UNITS * std::min(m->n_blocks, WIDE_BLOCKS));
+    m->window = (int)std::min<size_t>(MAX_WINDOW, std::max<size_t>(1, PART_BYTES / (part_step * sizeof(double))));
+    ALLOC(m->d_part, part_step * m->window);
+    ALLOC(m->d_vol, (size_t)n_boxes * m->window);
     ALLOC(m->d_acc, (size_t)n_boxes * ACC);
     ALLOC(m->d_parts, (size_t)n_boxes * ACC);
     ALLOC(m->d_gradL, (size_t)n_boxes * 9);
     ALLOC(m->d_acc_pairs, (size_t)n_boxes);
     ALLOC(m->d_tot_pairs, (size_t)n_boxes);
     ALLOC(m->d_step, (size_t)1);
-    ALLOC(m->d_gstep, (size_t)MAX_GROUPS);
 #undef ALLOC
     if (rc == LHMM_OK) {
         const size_t bytes = 3 * N * m->real_size;
         // search layout: each particle at most twice (its cell, and the
         // image of a bottom or top cell; n2 >= 3)
-        for (void** pp : {&m->d_s, &m->d_c, &m->d_f, &m->d_cell_pv, &m->d_srec}) {
+        for (void** pp : {&m->d_s, &m->d_c, &m->d_f, &m->d_sid[0], &m->d_sid[1], &m->d_sord[0], &m->d_sord[1], &m->d_cord,
+                          &m->d_cell_pv, &m->d_srec}) {
             const size_t nb = pp == &m->d_cell_pv ? 8 * N * m->real_size
-                              : pp == &m->d_srec ? (8 * N + 16) * m->real_size : bytes;
+                              : pp == &m->d_srec ? (8 * N + 16) * m->real_size
+                              : pp == &m->d_s || pp == &m->d_c || pp == &m->d_f ? bytes : 4 * N * m->real_size;
             if (hipMalloc(pp, nb ? nb : 1) != hipSuccess) {
                 rc = fail(LHMM_ERR_OOM, "hipMalloc of particle arrays failed");
                 break;
@@ -2344,7 +2537,6 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
         HIPCHK(hipStreamCreateWithFlags(&m->stream, hipStreamNonBlocking));
         HIPCHK(hipEventCreateWithFlags(&m->ev_in, hipEventDisableTiming));
         HIPCHK(hipEventCreateWithFlags(&m->ev_out, hipEventDisableTiming));
-        HIPCHK(hipMemcpy(m->d_box, m->box.data(), n_boxes * sizeof(BoxInfo), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(m->d_blk_box, m->blk_box.data(), m->n_blocks * sizeof(int), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(m->d_blk_first, m->blk_first.data(), m->n_blocks * sizeof(int), hipMemcpyHostToDevice));
         std::vector<BoxDyn> dyn(n_boxes);
@@ -2352,7 +2544,8 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
             memset(&dyn[b], 0, sizeof(BoxDyn));
             for (int k = 0; k < 9; ++k) dyn[b].h[k] = boxes[b].h0[k];
         }
-        HIPCHK(hipMemcpy(m->d_dyn, dyn.data(), n_boxes * sizeof(BoxDyn), hipMemcpyHostToDevice));
+        for (int slot = 0; slot < 2; ++slot)
+            HIPCHK(hipMemcpy(m->d_dyn + (size_t)slot * n_boxes, dyn.data(), n_boxes * sizeof(BoxDyn), hipMemcpyHostToDevice));
         HIPCHK(hipMemset(m->d_flags, 0, n_boxes * sizeof(unsigned)));
         HIPCHK(hipMemset(m->d_acc, 0, n_boxes * ACC * sizeof(double)));
         HIPCHK(hipMemset(m->d_parts, 0, n_boxes * ACC * sizeof(double)));
@@ -2381,16 +2574,21 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     C.s = m->d_s;
     C.c = m->d_c;
     C.f = m->d_f;
-    C.pcell = m->d_pcell;
-    C.cell_start = m->d_cell_start;
+    for (int k = 0; k < 2; ++k) {
+        C.sid[k] = m->d_sid[k];
+        C.sord[k] = m->d_sord[k];
+    }
+    C.cord = m->d_cord;
+    C.key = m->d_key;
+    C.perm = m->d_perm;
     C.gcell_start = m->d_gcell_start;
     C.cell_pv = m->d_cell_pv;
     C.srec = m->d_srec;
     C.vir_scale = 0.5;  // every unordered pair is evaluated from both ends
-    C.part_vir = m->d_part_vir;
-    C.pv_stride = pv_stride;
-    C.part_kin = m->d_part_kin;
-    C.part_pairs = m->d_part_pairs;
+    C.part = m->d_part;
+    C.part_step = part_step;
+    C.nv = nv;
+    C.vol = m->d_vol;
     C.acc = m->d_acc;
     C.acc_pairs = m->d_acc_pairs;
     C.tot_pairs = m->d_tot_pairs;
@@ -2408,7 +2606,8 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     C.inv_R02 = 1.0 / (p->R0 * p->R0);
     C.key0 = (unsigned)(p->seed & 0xFFFFFFFFull);
     C.key1 = (unsigned)(p->seed >> 32);
-    rc = prepare_groups(m, m->cfg.groups);
+    rc = build_slabs(m);
+    if (rc == LHMM_OK) rc = prepare_groups(m, m->cfg.groups);
     if (rc != LHMM_OK) {
         release(m);
         delete m;
@@ -2458,6 +2657,16 @@ int lhmm_micro_set_state(lhmm_micro* m, const double* s, const double* c, const 
         for (int b = 0; b < m->n_boxes; ++b)
             for (int k = 0; k < 9; ++k) dyn[b].h[k] = h[9 * b + k];
         HIPCHK(hipMemcpy(m->d_dyn, dyn.data(), m->n_boxes * sizeof(BoxDyn), hipMemcpyHostToDevice));
+        bool taller = false;
+        for (int b = 0; b < m->n_boxes; ++b)
+            if (h[9 * b + 8] > m->hz[b]) {
+                m->hz[b] = h[9 * b + 8];
+                taller = true;
+            }
+        if (taller) {  // captured binning launches hold their LDS size
+            bin_lds(m);
+            drop_graphs(m);
+        }
     }
     unsigned long long st = step;
     HIPCHK(hipMemcpy(m->d_step, &st, sizeof st, hipMemcpyHostToDevice));
@@ -2506,16 +2715,15 @@ int lhmm_micro_step(lhmm_micro* m, const double* gradL, int32_t n_steps, double*
     const int bt = 256, bg = (m->n_boxes + bt - 1) / bt;
     HIPCHK(hipEventRecord(m->ev_in, m->user_stream));
     HIPCHK(hipStreamWaitEvent(m->stream, m->ev_in, 0));
-    k_setup_call<<<bg, bt, 0, m->stream>>>(m->ctx, gradL);
-    k_zero_acc<<<(ACC * m->n_boxes + 255) / 256, 256, 0, m->stream>>>(m->ctx);
-    launch_remove_mean(m, m->ctx, m->n_boxes);
+    launch_begin_call(m, m->ctx, m->n_boxes, gradL);
     if (!m->forces_valid) {
         launch_force_eval(m);
         m->forces_valid = true;
     }
     HIPCHK(hipGetLastError());
     if (m->p.flags & LHMM_OPT_NO_GRAPH) {
-        for (int k = 0; k < n_steps; ++k) launch_one_step(m);
+        for (int k = 0; k < n_steps; k += m->cfg.graph_chunk)
+            launch_steps(m, all_boxes(m), std::min(m->cfg.graph_chunk, n_steps - k));
     } else {
         const int chunk = n_steps < m->cfg.graph_chunk ? n_steps : m->cfg.graph_chunk;
         const int full = n_steps / chunk, rest = n_steps % chunk;
@@ -2554,17 +2762,14 @@ int lhmm_micro_set_config(lhmm_micro* m, const lhmm_micro_config* cfg) {
     if (cfg->prune != 0 && cfg->prune != 1) return fail(LHMM_ERR_ARG, "prune must be 0 or 1");
     if (cfg->fuse_bin != 0 && cfg->fuse_bin != 1) return fail(LHMM_ERR_ARG, "fuse_bin must be 0 or 1");
     if (cfg->groups < 1 || cfg->groups > MAX_GROUPS) return fail(LHMM_ERR_ARG, "groups must be 1..%d", MAX_GROUPS);
-    if (cfg->bin_split != 0 && (cfg->bin_split < 256 || cfg->bin_split > SPLIT_PER * SPLIT_BT))
-        return fail(LHMM_ERR_ARG, "bin_split must be 0 or 256..%d", SPLIT_PER * SPLIT_BT);
+    if (cfg->bin_split != 0 && (cfg->bin_split < 256 || cfg->bin_split > 4096))
+        return fail(LHMM_ERR_ARG, "bin_split must be 0 or 256..4096");
     HIPCHK(hipStreamSynchronize(m->stream));
-    for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
-    m->graphs.clear();
-    for (auto& kv : m->sub_graphs) (void)hipGraphExecDestroy(kv.second);
-    m->sub_graphs.clear();
-    m->sub_seen.clear();
-    const bool regroup = cfg->groups != m->cfg.groups || cfg->bin_split != m->cfg.bin_split;
+    drop_graphs(m);
+    const bool reslab = cfg->bin_split != m->cfg.bin_split, regroup = cfg->groups != m->cfg.groups || reslab;
     m->cfg = *cfg;
-    return regroup ? prepare_groups(m, cfg->groups) : LHMM_OK;
+    const int rc = reslab ? build_slabs(m) : LHMM_OK;
+    return rc == LHMM_OK && regroup ? prepare_groups(m, cfg->groups) : rc;
 }
 
 int lhmm_micro_set_afbc(lhmm_micro* m, const double* regions, double zeta) {
@@ -2597,11 +2802,7 @@ int lhmm_micro_set_afbc(lhmm_micro* m, const double* regions, double zeta) {
     m->ctx.ou_damp = std::exp(-0.5 * zeta * dt);
     m->ctx.ou_amp = std::sqrt(m->p.kBT / m->p.mass * (1.0 - std::exp(-zeta * dt)));
     // captured graphs hold the kernel variant and the context
-    for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
-    m->graphs.clear();
-    for (auto& kv : m->sub_graphs) (void)hipGraphExecDestroy(kv.second);
-    m->sub_graphs.clear();
-    m->sub_seen.clear();
+    drop_graphs(m);
     return LHMM_OK;
 }
 
@@ -2781,25 +2982,23 @@ int lhmm_micro_step_subset(lhmm_micro* m, const double* gradL, int32_t n_steps, 
     const int bt = 256, bg = (m->n_boxes + bt - 1) / bt;
     HIPCHK(hipEventRecord(m->ev_in, m->user_stream));
     HIPCHK(hipStreamWaitEvent(m->stream, m->ev_in, 0));
-    Ctx C{};
-    int nblk = 0;
-    int rc = select_boxes(m, boxes, n_sel, &C, &nblk);
+    Launch L{};
+    int rc = select_boxes(m, boxes, n_sel, &L);
     if (rc != LHMM_OK) return rc;
-    k_setup_call<<<bg, bt, 0, m->stream>>>(m->ctx, gradL);
-    k_zero_acc<<<(ACC * m->n_boxes + 255) / 256, 256, 0, m->stream>>>(m->ctx);
-    launch_remove_mean(m, C, n_sel);
+    launch_begin_call(m, L.C, n_sel, gradL);
     if (!m->forces_valid) {
         launch_force_eval(m);
         m->forces_valid = true;
     }
     if (m->p.flags & LHMM_OPT_NO_GRAPH) {
-        for (int k = 0; k < n_steps; ++k) launch_one_step_sel(m, C, n_sel, nblk);
+        for (int k = 0; k < n_steps; k += m->cfg.graph_chunk)
+            launch_steps(m, L, std::min(m->cfg.graph_chunk, n_steps - k));
     } else {
         const int chunk = n_steps < m->cfg.graph_chunk ? n_steps : m->cfg.graph_chunk;
         int done = 0;
         while (done < n_steps) {
             const int len = n_steps - done >= chunk ? chunk : n_steps - done;
-            rc = launch_subset_steps(m, C, n_sel, nblk, len);
+            rc = launch_subset_steps(m, L, len);
             if (rc != LHMM_OK) return rc;
             done += len;
         }
@@ -2845,10 +3044,10 @@ int lhmm_micro_restore(lhmm_micro* m, const int32_t* boxes, int32_t n_sel) {
     if (!m->have_snapshot) return fail(LHMM_ERR_STATE, "no snapshot taken");
     HIPCHK(hipEventRecord(m->ev_in, m->user_stream));
     HIPCHK(hipStreamWaitEvent(m->stream, m->ev_in, 0));
-    Ctx C{};
-    int nblk = 0;
-    int rc = select_boxes(m, boxes, n_sel, &C, &nblk);
+    Launch L{};
+    int rc = select_boxes(m, boxes, n_sel, &L);
     if (rc != LHMM_OK) return rc;
+    const Ctx& C = L.C;
     if (m->precision == LHMM_FP64)
         k_restore<double><<<n_sel, 256, 0, m->stream>>>(C, (const double*)m->d_snap_s, (const double*)m->d_snap_c,
                                                         (const double*)m->d_snap_f, m->d_snap_dyn);
@@ -2870,8 +3069,7 @@ int lhmm_micro_forces(lhmm_micro* m, const double* gradL, double* f_out, double*
     int rc = sync_engine(m);
     if (rc != LHMM_OK) return rc;
     HIPCHK(hipMemcpy(m->d_gradL, gradL, 9 * m->n_boxes * sizeof(double), hipMemcpyHostToDevice));
-    const int bt = 256, bg = (m->n_boxes + bt - 1) / bt;
-    k_setup_call<<<bg, bt, 0, m->stream>>>(m->ctx, m->d_gradL);
+    launch_begin_call(m, m->ctx, 0, m->d_gradL);  // gradients only: the velocities keep their mean
     launch_force_eval(m);
     HIPCHK(hipGetLastError());
     rc = sync_engine(m);
@@ -2885,14 +3083,28 @@ int lhmm_micro_forces(lhmm_micro* m, const double* gradL, double* f_out, double*
             f_out[3 * i + k] = m->precision == LHMM_FP64 ? ((double*)buf.data())[k * N + i]
                                                          : (double)((float*)buf.data())[k * N + i];
     if (virial_out) {
-        const size_t ps = (size_t)m->ctx.pv_stride;
-        std::vector<double> pv((size_t)m->n_blocks * ps);
-        HIPCHK(hipMemcpy(pv.data(), m->d_part_vir, pv.size() * sizeof(double), hipMemcpyDeviceToHost));
+        const size_t nv = (size_t)m->ctx.nv;
+        const bool wide = use_wide(m, m->n_blocks);
+        std::vector<double> pv((size_t)m->n_blocks * nv * (wide ? WIDE_UNITS : 1));
+        HIPCHK(hipMemcpy(pv.data(), m->d_part, pv.size() * sizeof(double), hipMemcpyDeviceToHost));
         for (int b = 0; b < m->n_boxes; ++b) {
             double* o = virial_out + 12 * b;
             for (int q = 0; q < 12; ++q) o[q] = 0.0;
-            for (int k = 0; k < m->box[b].nblk; ++k)
-                for (int q = 0; q < 12; ++q) o[q] += pv[ps * (size_t)(m->box[b].blk_off + k) + q];
+            for (int k = 0; k < m->box[b].nblk; ++k) {
+                const size_t blk = (size_t)(m->box[b].blk_off + k);
+                for (int q = 0; q < 12; ++q) {
+                    double x = 0.0;
+                    if (wide) {  // as k_flush adds them
+                        for (int w = 0; w < 4; ++w) {
+                            const double* y = &pv[(blk * WIDE_UNITS + 4 * w) * nv + q];
+                            x += (y[0] + y[2 * nv]) + (y[nv] + y[3 * nv]);
+                        }
+                    } else {
+                        x = pv[blk * nv + q];
+                    }
+                    o[q] += x;
+                }
+            }
             for (int q = 0; q < 6; ++q) o[q] *= m->ctx.vir_scale;  // ordered pairs count each pair twice
         }
     }
@@ -2909,33 +3121,27 @@ int lhmm_micro_time(lhmm_micro* m, const double* gradL, int32_t n_steps, double*
     for (auto& e : ev) HIPCHK(hipEventCreate(&e));
     HIPCHK(hipEventRecord(m->ev_in, m->user_stream));
     HIPCHK(hipStreamWaitEvent(m->stream, m->ev_in, 0));
-    k_setup_call<<<bg, bt, 0, m->stream>>>(m->ctx, gradL);
-    k_zero_acc<<<(ACC * m->n_boxes + 255) / 256, 256, 0, m->stream>>>(m->ctx);
-    launch_remove_mean(m, m->ctx, m->n_boxes);
+    launch_begin_call(m, m->ctx, m->n_boxes, gradL);
     if (!m->forces_valid) {
         launch_force_eval(m);
         m->forces_valid = true;
     }
     double sum[LHMM_N_KERNELS] = {0, 0, 0, 0, 0, 0};
     int rc = LHMM_OK;
-    for (int k = 0; k < n_steps && rc == LHMM_OK; ++k) {
+    auto around = [&](int q, int after) {
+        (void)hipEventRecord(ev[2 * q + after], m->stream);
+        if (!after || rc != LHMM_OK) return;
+        float ms = 0.f;
+        if (hipEventSynchronize(ev[2 * q + 1]) != hipSuccess || hipEventElapsedTime(&ms, ev[2 * q], ev[2 * q + 1]) != hipSuccess)
+            rc = fail(LHMM_ERR_HIP, "timing of a kernel failed");
+        sum[q] += ms;
+    };
+    for (int k = 0; k < n_steps && rc == LHMM_OK; k += m->cfg.graph_chunk) {
+        const int n = std::min(m->cfg.graph_chunk, n_steps - k);
         if (m->precision == LHMM_FP64)
-            launch_step_timed<double>(m, ev);
+            launch_steps<double>(m, all_boxes(m), n, true, around);
         else
-            launch_step_timed<float>(m, ev);
-        hipError_t e = hipEventSynchronize(ev[2 * LHMM_N_KERNELS - 1]);
-        if (e != hipSuccess) {
-            rc = fail(LHMM_ERR_HIP, "hipEventSynchronize: %s", hipGetErrorString(e));
-            break;
-        }
-        for (int q = 0; q < LHMM_N_KERNELS; ++q) {
-            float ms = 0.f;
-            if (hipEventElapsedTime(&ms, ev[2 * q], ev[2 * q + 1]) != hipSuccess) {
-                rc = fail(LHMM_ERR_HIP, "hipEventElapsedTime failed");
-                break;
-            }
-            sum[q] += ms;
-        }
+            launch_steps<float>(m, all_boxes(m), n, true, around);
     }
     if (rc == LHMM_OK) {
         for (int q = 0; q < LHMM_N_KERNELS; ++q) avg_ms[q] = sum[q] / n_steps;

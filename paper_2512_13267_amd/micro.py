@@ -155,7 +155,7 @@ class Micro:
 
     def time_kernels(self, gradL, n_steps: int) -> dict:
         """Advance n_steps eagerly with HIP events around every kernel on the
-        engine's stream; returns {kernel name: mean ms per launch}."""
+        engine's stream; returns {kernel name: ms per step}."""
         g = gradL.reshape(self.n_boxes, 9)
         if g.dtype != self._torch.float64 or not g.is_cuda or not g.is_contiguous():
             raise ValueError("gradL must be a contiguous cuda float64 tensor")
