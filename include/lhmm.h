@@ -210,7 +210,8 @@ int lhmm_micro_step_subset(lhmm_micro* m, const double* gradL, int32_t n_steps, 
  *   busy_lanes:  the search also stops, and rounds also continue, while at
  *                least this many of a wave's 64 lanes hold a neighbour
  *                (1 .. 64; 65 turns the rule off);
- *   bin_threads: threads of a binning workgroup (256, 512, 1024);
+ *   bin_threads: threads of a binning workgroup (256, 512, 1024; launches of
+ *                at most 256 workgroups always use 1024);
  *   graph_chunk: micro steps per captured HIP graph (1 .. 1000);
  *   prune:       1 skips stencil cells that lie provably beyond the cutoff
  *                (the accepted pairs and their order are unchanged), 0
@@ -220,9 +221,8 @@ int lhmm_micro_step_subset(lhmm_micro* m, const double* gradL, int32_t n_steps, 
  *                in cell order through a chunk of steps; 0 makes them in a
  *                launch of their own, from and back to index order every step;
  *   groups:      1 .. 4: with fuse_bin 1, a captured chunk splits the
- *                boxes by particle count into this many groups (the largest
- *                boxes, two thirds of the particles, in the last), each
- *                on its own stream (1: one stream; small launches use one);
+ *                boxes into this many groups of about equal particle counts,
+ *                each on its own stream (1: one stream; small launches use one);
  *   bin_split:   0, or 256 .. 4096: particles per binning workgroup aimed at
  *                (0 and values above 1024 aim at 1024). */
 typedef struct {

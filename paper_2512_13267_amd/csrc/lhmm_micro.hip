@@ -23,8 +23,8 @@
 //                  per particle, for launches too small to fill the chip.
 // Steps come in chunks (captured in HIP graphs): k_begin_chunk takes the
 // particles from their arrays in index order through the first half kick and
-// drift, the last step's force pass puts them back, and k_flush reduces the
-// window's partial sums to the boxes' stresses (Eqs. IKtotal, kinetic_stress,
+// drift, the last step's force pass puts them back, and k_window_sums and
+// k_flush reduce the window's partial sums to the boxes' stresses (Eqs. IKtotal, kinetic_stress,
 // potential_stress with a uniform weight over the cell).
 // A box may instead be a micro-domain with boundary regions (Sec.
 // "Macro-to-Micro Coupling", Tab. 2): its cell stays fixed, the particles of
@@ -56,6 +56,7 @@
 namespace {
 
 constexpr int BS = 256;                 // particles per work block
+constexpr int SREC_PAD = 4;             // padding records per column of the search layout
 constexpr int MAX_CELLS_PER_BOX = 17424;
 constexpr int GRAPH_CHUNK = 50;         // default steps per captured graph
 constexpr int MAX_GROUPS = 4;           // overlapped box groups of a captured step
@@ -87,6 +88,7 @@ struct BoxInfo {
     int n_beads;   // n_chains * chain_len
     int cell_cap;  // cell capacity
     int gcell_off; // first slot in gcell_start (2 cap + 1 slots per box)
+    long long srec_off;  // first record in srec
     int zsub;      // cells per cutoff along z (1 or 2): the z range of a stencil row is 2 zsub + 1 cells
     int blk_off;   // first work block
     int nblk;      // work blocks
@@ -149,8 +151,10 @@ struct Ctx {
     // Search layout: per box (at 2 x its particle offset) every cell column
     // (m0, m1) as [images of its top zsub cells shifted by -h_z][its cells]
     // [images of its bottom zsub cells shifted by +h_z], so the z cells
-    // k2 - zsub .. k2 + zsub around any cell are one contiguous range;
-    // gcell_start holds the range starts of these n0 n1 (n2 + 2 zsub) cells.
+    // k2 - zsub .. k2 + zsub around any cell are one contiguous range.
+    // SREC_PAD records far away follow each column, so that a search may read
+    // past a range's end; gcell_start holds the starts of a column's n2 + 2 zsub
+    // cells and the end of the last.
     // srec: (x, y, z, cell-order position << 5 | 9 x z image: 0 none,
     // 1 below, 2 above), r = h s; padded by four records.
     int* gcell_start;
@@ -161,6 +165,7 @@ struct Ctx {
     double* part;
     size_t part_step;
     int nv;             // 19, or 37 when the conservative, dissipative and random parts are kept
+    double* sums;       // nv per box and step of the window: the partial sums reduced
     double* vol;        // n_boxes per step of the window
     double vir_scale;   // 1 when each pair is evaluated once, 1/2 when twice
     double* acc;        // n_boxes x ACC: kinetic, pair, FENE, C, D, R stress sums
@@ -745,10 +750,9 @@ __device__ __forceinline__ void kick_drift(const KickDrift<real>& K, real (&sv)[
         const real y = fma(K.h10, sv[0] - (real)0.5, K.h11 * (sv[1] - (real)0.5));
         ring_relax<real>(x, y, K.hc, K.hb, K.G, K.damp, K.amp, (unsigned)id, 0u, K.step, K.box, K.k0, K.k1, cv[0], cv[1]);
     }
-    auto row = [&](int k) { return fma(K.M[k + 2], cv[2], fma(K.M[k + 1], cv[1], K.M[k] * cv[0])); };
-    real s0 = fma(K.dt, row(0), sv[0]);
-    real s1 = fma(K.dt, row(3), sv[1]);
-    const real s2 = fma(K.dt, row(6), sv[2]);
+    real s0 = fma(K.dt, fma(K.M[2], cv[2], fma(K.M[1], cv[1], K.M[0] * cv[0])), sv[0]);
+    real s1 = fma(K.dt, fma(K.M[5], cv[2], fma(K.M[4], cv[1], K.M[3] * cv[0])), sv[1]);
+    const real s2 = fma(K.dt, fma(K.M[8], cv[2], fma(K.M[7], cv[1], K.M[6] * cv[0])), sv[2]);
     if (K.changed) {  // s <- U^{-1} s in the plane, U^{-1} = [[u11, -u01], [-u10, u00]]
         const real x = s0, y = s1;
         s0 = fma((real)K.U[3], x, -((real)K.U[1] * y));
@@ -866,6 +870,12 @@ __device__ __forceinline__ void block_scan(int n, int* wsum /* BT / 64 */, Val v
 //
 // The first n_cell workgroups, a thread per box, make the next step's cell
 // (slot of this step -> the other slot) and note this step's volume.
+// a coordinate beyond the cutoff of every particle of the cell
+template <typename real>
+__device__ __forceinline__ real far_away(const Ctx& C, const BoxDyn& D) {
+    return (real)(1.0e6 * (C.rc + fabs(D.h[0]) + fabs(D.h[1]) + fabs(D.h[3]) + fabs(D.h[4]) + D.h[8]));
+}
+
 constexpr int SLAB_TARGET = 1024;  // particles per slab
 constexpr int SLAB_CAP = 2048;     // particles a slab can order in LDS
 constexpr int SLAB_CELLS = 4096;   // a box has at least cells / SLAB_CELLS slabs
@@ -899,7 +909,7 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
     const int b = C.slab_box[slab];
     const BoxInfo B = C.box[b];
     const BoxDyn& D = C.dyn[(size_t)A.slot * C.n_boxes + b];
-    const int n2 = D.nc[2], zs = B.zsub, gn2 = n2 + 2 * zs, ncol = D.nc[0] * D.nc[1];
+    const int n2 = D.nc[2], zs = B.zsub, gs = n2 + 2 * zs + 1, ncol = D.nc[0] * D.nc[1];
     const int q = slab - B.slab_off;
     const int c0 = (int)((long long)q * ncol / B.nslab), c1 = (int)((long long)(q + 1) * ncol / B.nslab);
     const int nc = c1 - c0, s0 = c0 * n2, s1 = c1 * n2, ncell = nc * n2;
@@ -950,22 +960,27 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
                 return;
             }
             const int k = col * n2;
-            const int first = cnt[k] + img + excl, top = cnt[k + n2] - cnt[k + n2 - zs];
+            const int first = cnt[k] + img + excl + SREC_PAD * (c0 + col), top = cnt[k + n2] - cnt[k + n2 - zs];
             lo_off[col] = first - cnt[k + n2 - zs];
             col_off[col] = first + top - cnt[k];
             hi_off[col] = first + top + (cnt[k + n2] - cnt[k]) - cnt[k];
         });
     __syncthreads();
-    // starts of the search-layout cells: a segment's offset plus the start
-    // of the cell it repeats
-    int* gstart = C.gcell_start + B.gcell_off + c0 * gn2;
-    const float inv_gn2 = 1.0f / (float)gn2;
-    for (int g = tid; g < nc * gn2; g += T) {
-        const int col = div_small(g, inv_gn2), zg = g - col * gn2, k = col * n2;
+    // starts of the search-layout cells, a segment's offset plus the start of
+    // the cell it repeats, and the columns' ends; padding after each end
+    int* gstart = C.gcell_start + B.gcell_off + c0 * gs;
+    const float inv_gs = 1.0f / (float)gs;
+    V4* srec = (V4*)C.srec + B.srec_off;
+    const real far = far_away<real>(C, D);
+    for (int g = tid; g < nc * gs; g += T) {
+        const int col = div_small(g, inv_gs), zg = g - col * gs, k = col * n2;
         gstart[g] = before + (zg < zs ? lo_off[col] + cnt[k + n2 - zs + zg]
                                       : (zg < zs + n2 ? col_off[col] + cnt[k + zg - zs] : hi_off[col] + cnt[k + zg - zs - n2]));
     }
-    if (tid == 0 && c1 == ncol) gstart[nc * gn2] = before + total + img + base[2];
+    for (int g = tid; g < nc * SREC_PAD; g += T) {
+        const int col = g / SREC_PAD;
+        srec[before + hi_off[col] + cnt[col * n2 + zs] + g % SREC_PAD] = R::make(far, far, far, 0);
+    }
     __syncthreads();
     const bool fits = total <= SLAB_CAP;
     int* perm = C.perm + B.off;
@@ -986,7 +1001,6 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
     const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
     const V4* srcC = (const V4*)C.cord + B.off;
     V4* pv = (V4*)C.cell_pv + 2 * (size_t)B.off;
-    V4* srec = (V4*)C.srec + 2 * (size_t)B.off;
     const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4];
     const real h22 = (real)D.h[8];
     // particle `src` (records S, V) to cell-order position p (local to the slab)
@@ -1092,8 +1106,15 @@ __device__ __forceinline__ double inv_sqrt<double>(double x) { return 1.0 / sqrt
 //   Rounds run when a queue could overflow, until every queue holds at most
 //   `drain` entries (and while `busy` or more lanes have work), and the
 //   queues are drained at the end.  Deep queues let most lanes hold work in
-//   every round; the float kernel is bounded to 96 VGPRs so five waves share
-//   each SIMD (the loop is latency-bound).
+//   every round.
+//   What bounds it (256 relaxed boxes, 1.5M particles): a wave makes ~5300
+//   accesses to the vector cache, one per cycle and CU (28 for a search step's
+//   16-byte load, 64 for each of a round's two gathers), and issues ~4400 vector
+//   instructions, both near the limit of the CU, so that what helped last was
+//   waves to overlap them: 64 registers, eight waves per SIMD, 173 us; six
+//   waves 181; the previous form of the loops, six waves, 183.  Evaluating a
+//   round without its branch (idle lanes on a zero force) cost 2 us, loading
+//   only for lanes with records left gained nothing.
 // records tested per lane and search iteration for a queue of depth QD
 __host__ __device__ constexpr int scan_unroll(int qd) { return qd >= 8 ? 4 : (qd >= 4 ? 2 : 1); }
 
@@ -1122,8 +1143,7 @@ __device__ __forceinline__ real core_fraction(real ax, real ay, real ex, real ey
     return t1 > t0 ? t1 - t0 : (real)0;
 }
 
-// PRUNE selects the stencil-pruning variant; without it the float kernel
-// fits 80 VGPRs, six waves per SIMD.  COMP keeps the virials of the
+// PRUNE selects the stencil-pruning variant.  COMP keeps the virials of the
 // conservative, dissipative and random forces apart as well (their sum is
 // accumulated as in the default variant), at the cost of 18 more registers.
 // AF handles boxes with boundary regions: each pair's and bond's virial is
@@ -1255,7 +1275,7 @@ __device__ __forceinline__ void end_step(const Ctx& C, const Step& A, const BoxI
 }
 
 template <typename real, int QD, bool PRUNE, bool COMP = false, bool AF = false>
-__global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4 : (PRUNE ? 5 : 6)) : 1) void k_forces(
+__global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ? 4 : (COMP || AF ? 6 : (PRUNE ? 5 : 8))) : 1) void k_forces(
     Ctx C, Step A, int drain, int busy) {
     constexpr bool prune = PRUNE;
     constexpr int NV = COMP ? 37 : 19;  // block partial sums
@@ -1281,7 +1301,7 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
     const int pos = p0 + t;
     const bool act = pos < B.n;
     const V4* pv = (const V4*)C.cell_pv + 2 * (size_t)B.off;
-    const char* sbase = (const char*)((const V4*)C.srec + 2 * B.off);
+    const char* sbase = (const char*)((const V4*)C.srec + B.srec_off);
     const __amdgpu_buffer_rsrc_t srsrc = rec_rsrc(sbase);
     const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
 
@@ -1373,59 +1393,67 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
             const PairOut<real> o = pair_force<real>(P, dx, dy, dz, ci0, ci1, ci2, cj.x, cj.y, cj.z, (unsigned)own_id,
                                                      (unsigned)R::id(cj));
             const real ex = o.ex, ey = o.ey, ez = o.ez, gx = o.gx, gy = o.gy, gz = o.gz;
-            fx += gx; fy += gy; fz += gz;
+            fx = fma(o.mag, ex, fx); fy = fma(o.mag, ey, fy); fz = fma(o.mag, ez, fz);
             // a boundary-region box weighs the pair by its segment's share of the core
             const real wgt = afbc ? core_fraction<real>(ri0 - cx, ri1 - cy, -dx, -dy, hcr) : (real)1;
             const real dxw = AF ? dx * wgt : dx, dyw = AF ? dy * wgt : dy, dzw = AF ? dz * wgt : dz;
-            w[0] += dxw * gx; w[1] += dyw * gy; w[2] += dzw * gz;
-            w[3] += dxw * gy; w[4] += dxw * gz; w[5] += dyw * gz;
+            w[0] = fma(dxw, gx, w[0]); w[1] = fma(dyw, gy, w[1]); w[2] = fma(dzw, gz, w[2]);
+            w[3] = fma(dxw, gy, w[3]); w[4] = fma(dxw, gz, w[4]); w[5] = fma(dyw, gz, w[5]);
             if constexpr (COMP) {
                 // d (x) e times each force's magnitude
                 const real mc = o.wR * P.a, md = -(o.wR * P.gam * o.wR * o.ev), mr = o.wR * P.sig * o.th;
                 const real de[6] = {dxw * ex, dyw * ey, dzw * ez, dxw * ey, dxw * ez, dyw * ez};
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
-                    wc[k] += mc * de[k];
-                    wd[k] += md * de[k];
-                    wr[k] += mr * de[k];
+                    wc[k] = fma(mc, de[k], wc[k]);
+                    wd[k] = fma(md, de[k], wd[k]);
+                    wr[k] = fma(mr, de[k], wr[k]);
                 }
             }
         }
     };
-    // test one candidate record v against (px, py, pz), the lane's
-    // position minus the image shift of the range scanned; queue it if accepted
-    auto push = [&](bool valid, const V4& v, real px, real py, real pz) {
-        const real dx = px - v.x, dy = py - v.y, dz = pz - v.z;
+    // test one candidate record v against (bx, by, ri2), the lane's position
+    // minus the image shift of the range scanned; queue it if accepted
+    real bx = 0, by = 0;
+    auto push = [&](const V4& v) {
+        const real dx = bx - v.x, dy = by - v.y, dz = ri2 - v.z;
         // the acceptance test's rounding is fixed by explicit fmas, whatever the
         // surrounding code lets the compiler contract
         const real r2 = fma(dz, dz, fma(dy, dy, dx * dx));
         // one branch per candidate: the tests combined without short-circuit
-        if (valid & (r2 < rc2) & (r2 > (real)0)) {
-            *(int*)(qbase + ((qt & QMASK) | qlane)) = R::id(v) + ic;
+        if ((r2 < rc2) & (r2 > (real)0)) {
+            const unsigned at = (qt & QMASK) | qlane;
+            asm volatile("" : "+v"(qt) : "v"(at));  // the address first, so the count advances in place
+            *(int*)(qbase + at) = R::id(v) + ic;
             qt += QROW;
         }
     };
 
     // Scan state: the wave is at stencil row `row` (d0, d1); each lane scans
-    // the search-layout records q .. qe-1 (z cells k2 - zsub .. k2 + zsub of
-    // the row's column, the periodic images included) against (bx, by, ri2), its
-    // position less the in-plane image shift of the column.
+    // the search-layout records from byte q to byte qe (z cells k2 - zsub ..
+    // k2 + zsub of the row's column, the periodic images included).
+    // Up to SREC_PAD records past a range's end are the column's next z cells, at
+    // least the cutoff away along z while zsub cells span it, or the column's
+    // padding: they need no test of their own, and a lane whose range has ended
+    // stays at its end.  A box too flat for
+    // that (flagged) scans one record per iteration; a lane that scans nothing
+    // (no particle, a pruned row) tests from far away.
     int row = 0;
-    int q = 0, qe = 0;
-    real bx = 0, by = 0;
+    unsigned q = 0, qe = 0;
+    const bool spans = D.h[8] * zs >= C.rc * n2;
+    const unsigned step = (spans ? SU : 1) * (unsigned)sizeof(V4);
+    const real far = far_away<real>(C, D);
     auto set_range = [&]() {
         const int d0 = row / 3 - 1, d1 = row % 3 - 1;
         int m0 = k0 + d0, m1 = k1 + d1;
-        const int sh0 = m0 < 0 ? -1 : (m0 >= n0 ? 1 : 0);
-        const int sh1 = m1 < 0 ? -1 : (m1 >= n1 ? 1 : 0);
-        m0 -= sh0 * n0;
-        m1 -= sh1 * n1;
-        const int gb = (m0 * n1 + m1) * (n2 + 2 * zs) + k2;
-        ic = 3 * (sh0 + 1) + (sh1 + 1);
+        const int i0 = m0 < 0 ? 0 : (m0 >= n0 ? 6 : 3), i1 = m1 < 0 ? 0 : (m1 >= n1 ? 2 : 1);
+        m0 += m0 < 0 ? n0 : (m0 >= n0 ? -n0 : 0);
+        m1 += m1 < 0 ? n1 : (m1 >= n1 ? -n1 : 0);
+        // cells and columns are below 2^24 (MAX_CELLS_PER_BOX)
+        const int gb = __mul24(__mul24(m0, n1) + m1, n2 + 2 * zs + 1) + k2;
+        ic = i0 + i1;
         bx = ri0 - shift_tab[ic][0];
         by = ri1 - shift_tab[ic][1];
-        q = 0;
-        qe = 0;
         int lo = 0, hi = 2 * zs + 1;
         bool live = act;
         if (act && prune) {
@@ -1438,15 +1466,24 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
             for (int j = zs; j >= 1 && !(sqr(zl + (real)(j - 1) * dzc) < zmax2); --j) ++lo;
             for (int j = zs; j >= 1 && !(sqr(zh + (real)(j - 1) * dzc) < zmax2); --j) --hi;
         }
-        if (live) {
-            q = gstart[gb + lo];
-            qe = gstart[gb + hi];
+        if constexpr (prune) {
+            q = qe = 0u;
+            if (!live) bx = far;
+            if (live) {
+                q = (unsigned)gstart[gb + lo] * (unsigned)sizeof(V4);
+                qe = (unsigned)gstart[gb + hi] * (unsigned)sizeof(V4);
+            }
+        } else {
+            q = (unsigned)gstart[(unsigned)gb] * (unsigned)sizeof(V4);
+            qe = (unsigned)gstart[(unsigned)(gb + 2 * zs + 1)] * (unsigned)sizeof(V4);
         }
     };
+    if (!act) ri0 = far;
     set_range();
-    bool scanning = true;  // wave-uniform
+    unsigned qfull = (QD - SU) * QROW;  // pushed entries beyond which the queue may not take SU more
+    bool scanning = true;               // wave-uniform
     while (true) {
-        // search until the stencil is done or some queue might not take two more
+        // search until the stencil is done or some queue might not take SU more
         while (scanning) {
             if (__ballot(q < qe) == 0ull) {
                 if (++row == 9) {
@@ -1458,30 +1495,31 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (COMP || AF || QD >= 32 ? 4
             }
             // SU records per lane per iteration, all loads issued before the
             // first test, addressed by one 32-bit byte offset from the box's
-            // records; slots past the range end read the next records (the
-            // array is padded) and are discarded
+            // records
             V4 cand[SU];
-            const unsigned qo = (unsigned)q * (unsigned)sizeof(V4);
-            const int rem = qe - q;
 #pragma unroll
-            for (int u = 0; u < SU; ++u) cand[u] = load_rec<real>(srsrc, sbase, qo + u * (unsigned)sizeof(V4));
+            for (int u = 0; u < SU; ++u) cand[u] = load_rec<real>(srsrc, sbase, q + u * (unsigned)sizeof(V4));
+            push(cand[0]);
+            if (spans) {
 #pragma unroll
-            for (int u = 0; u < SU; ++u) push(u < rem, cand[u], bx, by, ri2);
-            q += SU;
+                for (int u = 1; u < SU; ++u) push(cand[u]);
+            }
+            q = min(q + step, qe);
             // evaluate when a queue may not take SU more, or when enough
             // lanes hold a neighbour for a well-filled round
-            if (__ballot(qt - qh > (QD - SU) * QROW) != 0ull || __popcll(__ballot(qt > qh)) >= busy) break;
+            if (__ballot(qt > qfull) != 0ull) break;
+            if (busy <= 64 && __popcll(__ballot(qt > qh)) >= busy) break;
         }
-        if (!scanning) {
-            while (__ballot(qt > qh) != 0ull) round();
-            break;
-        }
-        // evaluate until every queue holds at most `drain` entries and fewer
-        // than `busy` lanes hold one
+        // evaluate until every queue holds at most `drain` entries (none once
+        // the stencil is done) and fewer than `busy` lanes hold one
+        const unsigned keep = scanning ? (unsigned)drain * QROW : 0u;
         do {
             round();
-        } while (__ballot(qt - qh > (unsigned)drain * QROW) != 0ull || __popcll(__ballot(qt > qh)) >= busy);
+        } while (__ballot(qt - qh > keep) != 0ull || (busy <= 64 && __popcll(__ballot(qt > qh)) >= busy));
+        if (!scanning) break;
+        qfull = qh + (QD - SU) * QROW;
     }
+    if (!act) ri0 = 0;
 
     real wf[6] = {0, 0, 0, 0, 0, 0};
     if (act && own_id < B.n_beads)
@@ -1559,7 +1597,7 @@ __global__ __launch_bounds__(BS) void k_forces_wide(Ctx C, Step A) {
     const int pos = C.blk_first[blk] - B.off + 64 * (sub >> 2) + (sub & 3) + 4 * p;
     const bool act = pos < B.n;
     const V4* pv = (const V4*)C.cell_pv + 2 * (size_t)B.off;
-    const char* sbase = (const char*)((const V4*)C.srec + 2 * B.off);
+    const char* sbase = (const char*)((const V4*)C.srec + B.srec_off);
     const __amdgpu_buffer_rsrc_t srsrc = rec_rsrc(sbase);
     const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
     const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4];
@@ -1597,7 +1635,7 @@ __global__ __launch_bounds__(BS) void k_forces_wide(Ctx C, Step A) {
         const int sh1 = m1 < 0 ? -1 : (m1 >= n1 ? 1 : 0);
         m0 -= sh0 * n0;
         m1 -= sh1 * n1;
-        const int gb = (m0 * n1 + m1) * (n2 + 2 * zs) + k2;
+        const int gb = (m0 * n1 + m1) * (n2 + 2 * zs + 1) + k2;
         ic = 3 * (sh0 + 1) + (sh1 + 1);
         bx = ri0 - shift_tab[ic][0];
         by = ri1 - shift_tab[ic][1];
@@ -1758,59 +1796,67 @@ __global__ __launch_bounds__(BS) void k_forces_wide(Ctx C, Step A) {
     }
 }
 
-// The stresses of a window of nw steps, one workgroup per box: sigma =
-// -(K + W)/V by part and step.  Wave w sums the partials of steps w, w + 16,
-// ...: lane l those of blocks l, l + 64, ..., then a fixed tree; the steps are
-// then added in order.  After a chunk's last window the box's cell returns to
-// slot 0 and, when this launch covers all of the chunk's boxes, the step
-// counter advances by `add`.
-constexpr int FLUSH_THREADS = 1024;
+// One step's partial sums of one box, a workgroup per (box, step of the
+// window): column l of LDS takes blocks l, l + 64, ... in order, then a fixed
+// tree (lanes 32, 16, .. 1 apart; missing blocks are zero).
+constexpr int SUM_THREADS = 256;
 
 template <int NV>
-__global__ __launch_bounds__(FLUSH_THREADS) void k_flush(Ctx C, int nw, int part0, int wide, int copy_dyn, int add) {
-    __shared__ double sum[MAX_WINDOW][NV];
-    const int q = blockIdx.x, b = C.sel ? C.sel[q] : q;
+__global__ __launch_bounds__(SUM_THREADS) void k_window_sums(Ctx C, int nbox, int part0, int wide) {
+    __shared__ double x[64][NV];
+    const int q = blockIdx.x % nbox, w = blockIdx.x / nbox, b = C.sel ? C.sel[q] : q;
     const BoxInfo B = C.box[b];
-    const int first = C.sel ? C.blk0[q] : B.blk_off;
-    const int lane = threadIdx.x & 63;
-    for (int w = threadIdx.x >> 6; w < nw; w += FLUSH_THREADS / 64) {
-        double v[NV];
+    const int first = C.sel ? C.blk0[q] : B.blk_off, cols = min(B.nblk, 64);
+    const double* part = C.part + (size_t)w * C.part_step + (size_t)(part0 + first) * NV * (wide ? WIDE_UNITS : 1);
+    for (int i = threadIdx.x; i < cols * NV; i += SUM_THREADS) {
+        const int l = i / NV, r = i - l * NV;
+        double s = 0.0;
+        for (int k = l; k < B.nblk; k += 64) {
+            if (wide) {  // per wave of 64 particles the residues two and one apart, then the waves in order
+                const double* p = part + (size_t)k * NV * WIDE_UNITS + r;
+                double y[WIDE_UNITS];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) v[k] = 0.0;
-        const double* part = C.part + (size_t)w * C.part_step;
-        for (int k = lane; k < B.nblk; k += 64) {
-            const double* p = part + (size_t)(part0 + first + k) * NV * (wide ? WIDE_UNITS : 1);
+                for (int u = 0; u < WIDE_UNITS; ++u) y[u] = p[(size_t)u * NV];
+                double z = 0.0;
 #pragma unroll
-            for (int r = 0; r < NV; ++r) {
-                double x;
-                if (wide) {  // per wave of 64 particles the residues two and one apart, then the waves in order
-                    x = 0.0;
-                    for (int s = 0; s < 4; ++s) {
-                        const double* y = p + (size_t)(4 * s) * NV + r;
-                        x += (y[0] + y[2 * NV]) + (y[NV] + y[3 * NV]);
-                    }
-                } else {
-                    x = p[r];
-                }
-                v[r] += x;
+                for (int v = 0; v < WIDE_UNITS; v += 4) z += (y[v] + y[v + 2]) + (y[v + 1] + y[v + 3]);
+                s += z;
+            } else {
+                s += part[(size_t)k * NV + r];
             }
         }
-#pragma unroll
-        for (int r = 0; r < NV; ++r) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v[r] += __shfl_xor(v[r], o, 64);
-            if (lane == 0) sum[w][r] = v[r];
-        }
+        x[l][r] = s;
     }
     __syncthreads();
+    if ((int)threadIdx.x < NV) {
+        const int r = threadIdx.x;
+        int o = 32;
+        while (o >= cols) o >>= 1;  // upper halves that hold no block
+        for (; o > 0; o >>= 1)
+            for (int l = 0; l < o && l + o < cols; ++l) x[l][r] += x[l + o][r];
+        C.sums[((size_t)w * C.n_boxes + b) * NV + r] = x[0][r];
+    }
+}
+
+// The stresses of a window of nw steps, one wave per box: sigma = -(K + W)/V
+// by part and step, the steps added in order.  After a chunk's last window
+// the box's cell returns to slot 0 and, when this launch covers all of the
+// chunk's boxes, the step counter advances by `add`.
+template <int NV>
+__global__ __launch_bounds__(64) void k_flush(Ctx C, int nw, int copy_dyn, int add) {
+    const int b = C.sel ? C.sel[blockIdx.x] : (int)blockIdx.x;
+    const size_t sw = (size_t)C.n_boxes * NV;
+    const double* sum = C.sums + (size_t)b * NV;
+    const double* vol = C.vol + b;
     double* acc = C.acc + (size_t)ACC * b;
     const int r = threadIdx.x;
     if (r < 6) {
         double a0 = acc[r], a1 = acc[6 + r], a2 = acc[12 + r];
         bool finite = true;
+#pragma unroll 4
         for (int w = 0; w < nw; ++w) {
-            const double iv = 1.0 / C.vol[(size_t)w * C.n_boxes + b];
-            const double sk = -sum[w][13 + r] * iv, sp = -C.vir_scale * sum[w][r] * iv, sf = -sum[w][6 + r] * iv;
+            const double iv = 1.0 / vol[(size_t)w * C.n_boxes];
+            const double sk = -sum[w * sw + 13 + r] * iv, sp = -C.vir_scale * sum[w * sw + r] * iv, sf = -sum[w * sw + 6 + r] * iv;
             a0 += sk;
             a1 += sp;
             a2 += sf;
@@ -1820,22 +1866,25 @@ __global__ __launch_bounds__(FLUSH_THREADS) void k_flush(Ctx C, int nw, int part
         acc[6 + r] = a1;
         acc[12 + r] = a2;
         if (!finite) atomicOr(&C.flags[b], LHMM_FLAG_NONFINITE);
-    } else if (NV > 19 && r >= 18 && r < 36) {
-        double a = acc[r];
-        for (int w = 0; w < nw; ++w) a += -C.vir_scale * sum[w][r + 1] * (1.0 / C.vol[(size_t)w * C.n_boxes + b]);
-        acc[r] = a;
-    } else if (r == 64) {
+    } else if (r == 6) {
         unsigned long long up = 0ull;
+#pragma unroll 4
         for (int w = 0; w < nw; ++w) {
-            const unsigned long long np = (unsigned long long)sum[w][12];
+            const unsigned long long np = (unsigned long long)sum[w * sw + 12];
             up += C.vir_scale < 1.0 ? np / 2 : np;
         }
         C.acc_pairs[b] += up;
         C.tot_pairs[b] += up;
         if (add && blockIdx.x == 0) *C.step += (unsigned long long)add;
-    } else if (copy_dyn && r >= 128 && r < 128 + (int)(sizeof(BoxDyn) / sizeof(int))) {
-        ((int*)&C.dyn[b])[r - 128] = ((const int*)&C.dyn[(size_t)C.n_boxes + b])[r - 128];
+    } else if (NV > 19 && r >= 18 && r < 36) {
+        double a = acc[r];
+#pragma unroll 4
+        for (int w = 0; w < nw; ++w) a += -C.vir_scale * sum[w * sw + r + 1] * (1.0 / vol[(size_t)w * C.n_boxes]);
+        acc[r] = a;
     }
+    if (copy_dyn)
+        for (int k = r; k < (int)(sizeof(BoxDyn) / sizeof(int)); k += 64)
+            ((int*)&C.dyn[b])[k] = ((const int*)&C.dyn[(size_t)C.n_boxes + b])[k];
 }
 
 __global__ void k_step_add(unsigned long long* __restrict__ step, int add) { *step += (unsigned long long)add; }
@@ -1902,7 +1951,7 @@ struct lhmm_micro {
     void *d_sid[2] = {}, *d_sord[2] = {}, *d_cord = nullptr;
     void* d_cell_pv = nullptr;
     void* d_srec = nullptr;
-    double *d_part = nullptr, *d_vol = nullptr;
+    double *d_part = nullptr, *d_sums = nullptr, *d_vol = nullptr;
     double *d_acc = nullptr, *d_parts = nullptr, *d_gradL = nullptr;
     unsigned long long *d_acc_pairs = nullptr, *d_tot_pairs = nullptr, *d_step = nullptr;
     // selection lists (device) and their pinned staging, reused once ev_sel completes
@@ -1959,7 +2008,10 @@ Launch all_boxes(lhmm_micro* m) {
 
 template <typename real>
 void launch_bin(lhmm_micro* m, const Launch& L, const Step& A) {
-    const int T = m->cfg.bin_threads, nc = (L.nbox + T - 1) / T;
+    // where the slabs do not fill the chip a workgroup's latency counts: 1024
+    // threads (5 boxes of 4000: 1393 us per 50 steps against 1469 with 512; the
+    // batch of 256, 1.5k slabs: 5046 per 20 steps with 512, 5666 with 1024)
+    const int T = L.nslab <= 256 ? 1024 : m->cfg.bin_threads, nc = (L.nbox + T - 1) / T;
     const size_t bytes = sizeof(int) * ((size_t)m->lds_cells + 3 * (size_t)m->lds_cols + 2 * (size_t)SLAB_CAP);
     const int grid = nc + L.nslab;
     switch (T) {
@@ -2006,10 +2058,13 @@ void launch_forces(lhmm_micro* m, const Launch& L, const Step& A) {
 
 void launch_flush(lhmm_micro* m, const Launch& L, int nw, bool copy_dyn, int add) {
     const int wide = L.wide ? 1 : 0;
-    if (L.C.nv > 19)
-        k_flush<37><<<L.nbox, FLUSH_THREADS, 0, L.st>>>(L.C, nw, L.part0, wide, copy_dyn ? 1 : 0, add);
-    else
-        k_flush<19><<<L.nbox, FLUSH_THREADS, 0, L.st>>>(L.C, nw, L.part0, wide, copy_dyn ? 1 : 0, add);
+    if (L.C.nv > 19) {
+        k_window_sums<37><<<L.nbox * nw, SUM_THREADS, 0, L.st>>>(L.C, L.nbox, L.part0, wide);
+        k_flush<37><<<L.nbox, 64, 0, L.st>>>(L.C, nw, copy_dyn ? 1 : 0, add);
+    } else {
+        k_window_sums<19><<<L.nbox * nw, SUM_THREADS, 0, L.st>>>(L.C, L.nbox, L.part0, wide);
+        k_flush<19><<<L.nbox, 64, 0, L.st>>>(L.C, nw, copy_dyn ? 1 : 0, add);
+    }
 }
 
 // n steps of the boxes L covers, the random-force counters *C.step + k0 + 1
@@ -2162,7 +2217,7 @@ void release(lhmm_micro* m) {
     m->sub_graphs.clear();
     void* bufs[] = {m->d_box, m->d_dyn, m->d_flags, m->d_blk_box, m->d_blk_first, m->d_slab_box, m->d_s, m->d_c, m->d_f,
                     m->d_key, m->d_perm, m->d_gcell_start, m->d_sid[0], m->d_sid[1], m->d_sord[0], m->d_sord[1],
-                    m->d_cord, m->d_cell_pv, m->d_srec, m->d_part, m->d_vol, m->d_acc, m->d_parts, m->d_gradL,
+                    m->d_cord, m->d_cell_pv, m->d_srec, m->d_part, m->d_sums, m->d_vol, m->d_acc, m->d_parts, m->d_gradL,
                     m->d_acc_pairs, m->d_tot_pairs, m->d_step, m->d_sel, m->d_snap_s, m->d_snap_c, m->d_snap_f,
                     m->d_snap_dyn};
     for (void* b : bufs)
@@ -2292,8 +2347,11 @@ Lists fill_lists(const lhmm_micro* m, const int* boxes, int n_sel, int* out) {
     return L;
 }
 
-// Partition the boxes into G groups by particle count (smallest first), with
-// their lists.
+// Partition the boxes into G groups of about equal particle counts and mixed
+// sizes (largest first, each to the least loaded group), with their lists:
+// groups that take equally long overlap to the chunk's end (batch of 256, 20
+// steps: 4800 us; 5046 with the largest boxes, two thirds of the particles, in
+// one group, which ran alone after the other; one group 5240).
 int prepare_groups(lhmm_micro* m, int G) {
     HIPCHK(hipStreamSynchronize(m->stream));
     for (auto& gr : m->groups)
@@ -2310,16 +2368,12 @@ int prepare_groups(lhmm_micro* m, int G) {
     std::vector<int> order(m->n_boxes);
     for (int b = 0; b < m->n_boxes; ++b) order[b] = b;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return m->box[a].n < m->box[b].n; });
-    // the largest boxes, two thirds of the particles, form the last group
-    // (their binning is the longest; measured best on uneven batches), the
-    // rest is shared equally by the others
     std::vector<std::vector<int>> members(G);
-    long long acc = 0;
-    const long long third = std::max(1LL, m->n_total / 3);
-    for (int b : order) {
-        const int g = acc >= third ? G - 1 : (int)(acc * (G - 1) / third);
-        members[std::min(g, G - 1)].push_back(b);
-        acc += m->box[b].n;
+    std::vector<long long> load(G, 0);
+    for (auto it = order.rbegin(); it != order.rend(); ++it) {
+        const int g = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        members[g].push_back(*it);
+        load[g] += m->box[*it].n;
     }
     int part0 = 0;
     std::vector<int> lists(2 * (size_t)m->n_boxes + m->n_blocks + m->n_slabs);
@@ -2429,7 +2483,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     m->real_size = p->precision == LHMM_FP64 ? sizeof(double) : sizeof(float);
     m->user_stream = (hipStream_t)stream;
 
-    long long off = 0;
+    long long off = 0, srec_off = 0;
     int gcell_off = 0, blk_off = 0;
     m->box.resize(n_boxes);
     for (int b = 0; b < n_boxes; ++b) {
@@ -2478,7 +2532,9 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
             m->blk_first.push_back(B.off + k * BS);
         }
         off += in.n_particles;
-        gcell_off += 2 * (int)cap + 1;  // n0 n1 (n2 + 2 zsub) cells, n2 >= 2 zsub + 1
+        B.srec_off = srec_off;
+        srec_off += 2 * (long long)in.n_particles + SREC_PAD * (long long)box_cols(B);
+        gcell_off += 2 * (int)cap + 1;  // n0 n1 (n2 + 2 zsub + 1) starts and ends, n2 >= 2 zsub + 1
         blk_off += B.nblk;
         if (off > (1LL << 30)) {
             delete m;
@@ -2505,6 +2561,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     const size_t part_step = nv * std::max((size_t)m->n_blocks, (size_t)WIDE_UNITS * std::min(m->n_blocks, WIDE_BLOCKS));
     m->window = (int)std::min<size_t>(MAX_WINDOW, std::max<size_t>(1, PART_BYTES / (part_step * sizeof(double))));
     ALLOC(m->d_part, part_step * m->window);
+    ALLOC(m->d_sums, (size_t)n_boxes * m->window * nv);
     ALLOC(m->d_vol, (size_t)n_boxes * m->window);
     ALLOC(m->d_acc, (size_t)n_boxes * ACC);
     ALLOC(m->d_parts, (size_t)n_boxes * ACC);
@@ -2520,7 +2577,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
         for (void** pp : {&m->d_s, &m->d_c, &m->d_f, &m->d_sid[0], &m->d_sid[1], &m->d_sord[0], &m->d_sord[1], &m->d_cord,
                           &m->d_cell_pv, &m->d_srec}) {
             const size_t nb = pp == &m->d_cell_pv ? 8 * N * m->real_size
-                              : pp == &m->d_srec ? (8 * N + 16) * m->real_size
+                              : pp == &m->d_srec ? 4 * (size_t)srec_off * m->real_size
                               : pp == &m->d_s || pp == &m->d_c || pp == &m->d_f ? bytes : 4 * N * m->real_size;
             if (hipMalloc(pp, nb ? nb : 1) != hipSuccess) {
                 rc = fail(LHMM_ERR_OOM, "hipMalloc of particle arrays failed");
@@ -2588,6 +2645,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     C.part = m->d_part;
     C.part_step = part_step;
     C.nv = nv;
+    C.sums = m->d_sums;
     C.vol = m->d_vol;
     C.acc = m->d_acc;
     C.acc_pairs = m->d_acc_pairs;
@@ -3094,7 +3152,7 @@ int lhmm_micro_forces(lhmm_micro* m, const double* gradL, double* f_out, double*
                 const size_t blk = (size_t)(m->box[b].blk_off + k);
                 for (int q = 0; q < 12; ++q) {
                     double x = 0.0;
-                    if (wide) {  // as k_flush adds them
+                    if (wide) {  // as k_window_sums adds them
                         for (int w = 0; w < 4; ++w) {
                             const double* y = &pv[(blk * WIDE_UNITS + 4 * w) * nv + q];
                             x += (y[0] + y[2 * nv]) + (y[nv] + y[3 * nv]);
