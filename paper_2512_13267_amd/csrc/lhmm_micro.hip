@@ -1275,7 +1275,7 @@ __device__ __forceinline__ void end_step(const Ctx& C, const Step& A, const BoxI
 }
 
 template <typename real, int QD, bool PRUNE, bool COMP = false, bool AF = false>
-__global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ? 4 : (COMP || AF ? 6 : (PRUNE ? 5 : 8))) : 1) void k_forces(
+__global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ? 4 : (COMP || AF || PRUNE ? 5 : 8)) : 1) void k_forces(
     Ctx C, Step A, int drain, int busy) {
     constexpr bool prune = PRUNE;
     constexpr int NV = COMP ? 37 : 19;  // block partial sums
