@@ -15,8 +15,12 @@
 //      those particles;
 //   5. boxes whose cell became thin (LHMM_FLAG_THIN) are restored and
 //      replayed the same way, after their stress has been used.
-// Host work per step: one readback of the gate flags and one of the micro
-// flags; the particle lists are built on the host and uploaded once.
+// Host work per step: the gate flags, which the gate kernel writes to pinned
+// host memory, and one readback of the micro flags; the particle lists are
+// built on the host and uploaded once, the mask of step 4 is read from pinned
+// host memory.  With a quiet gate a step is nine launches (five of them the
+// SPH step) and one wait: 72 us of kernels for 3572 particles, 24 us of them
+// the forward pass.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,13 +43,13 @@ struct lhmm_hybrid {
     long long box_steps = 0;
     // device
     float *ring = nullptr, *phi = nullptr, *X = nullptr, *Y = nullptr, *mean = nullptr;
-    unsigned *gflag = nullptr, *on_d = nullptr;
     double *sigma = nullptr, *sigma_dpd = nullptr, *gradL = nullptr, *gradL_r = nullptr, *scratch = nullptr;
     double* sigma_sum = nullptr;  // running sum of the stresses handed to SPH
     long long n_sum = 0;
     std::vector<void*> bufs;
-    // host (pinned)
-    unsigned *gflag_h = nullptr, *on_h = nullptr;
+    // host (pinned), and as the device sees it.  The mask of a step is read by
+    // its last launch; the next step writes it after waiting for the stream.
+    unsigned *gflag_h = nullptr, *on_h = nullptr, *gflag_d = nullptr, *on_d = nullptr;
     std::vector<int> hold_left;
     std::vector<unsigned char> was_on;   // DPD stress used in the last step
     std::vector<unsigned char> was_run;  // box advanced in the last step (used or warming)
@@ -53,22 +57,6 @@ struct lhmm_hybrid {
 };
 
 namespace {
-
-// Input-range gate: bit 1 of flag[b] is set when the micro gradient of
-// particle b (row-major 3 x 3, FP64) has squared Frobenius norm above max2,
-// bit 2 when above warm2 (the warm band below it); the sum of squares is
-// formed in this fixed order without fused products, so a host computation
-// in FP64 takes the same decisions.
-__global__ void k_input_gate(const double* __restrict__ L, int n, double max2, double warm2,
-                             unsigned* __restrict__ flag) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    const double* l = L + 9 * (long)b;
-    double q = 0.0;
-    for (int k = 0; k < 9; ++k) q = __dadd_rn(q, __dmul_rn(l[k], l[k]));
-    if (q > max2) flag[b] |= 2u;
-    if (q > warm2) flag[b] |= 4u;
-}
 
 __global__ void k_accumulate(const double* __restrict__ x, long n, double* __restrict__ sum) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -167,8 +155,6 @@ int lhmm_hybrid_create(const lhmm_hybrid_params* p, lhmm_sph* sph, lhmm_micro* m
     if (rc == LHMM_OK) rc = hy_alloc(h, &h->X, m * LHMM_SUR_FEATURES);
     if (rc == LHMM_OK) rc = hy_alloc(h, &h->Y, (size_t)std::max(E, 1) * m * 3);
     if (rc == LHMM_OK) rc = hy_alloc(h, &h->mean, m * 3);
-    if (rc == LHMM_OK) rc = hy_alloc(h, &h->gflag, m);
-    if (rc == LHMM_OK) rc = hy_alloc(h, &h->on_d, m);
     if (rc == LHMM_OK) rc = hy_alloc(h, &h->sigma, (size_t)n * 6);
     if (rc == LHMM_OK) rc = hy_alloc(h, &h->sigma_dpd, m * 6);
     if (rc == LHMM_OK) rc = hy_alloc(h, &h->gradL, (size_t)n * 9);
@@ -180,6 +166,8 @@ int lhmm_hybrid_create(const lhmm_hybrid_params* p, lhmm_sph* sph, lhmm_micro* m
     if (rc == LHMM_OK && hipHostMalloc((void**)&h->on_h, m * sizeof(unsigned)) != hipSuccess)
         rc = lhmm_fail(LHMM_ERR_OOM, "pinned allocation failed");
     auto init = [&]() -> int {
+        LHMM_HIPCHK(hipHostGetDevicePointer((void**)&h->gflag_d, h->gflag_h, 0));
+        LHMM_HIPCHK(hipHostGetDevicePointer((void**)&h->on_d, h->on_h, 0));
         LHMM_HIPCHK(hipStreamSynchronize(st));
         LHMM_HIPCHK(hipMemset(h->ring, 0, m * LHMM_SUR_HIST * 4 * sizeof(float)));
         LHMM_HIPCHK(hipMemset(h->sigma, 0, (size_t)n * 6 * sizeof(double)));
@@ -215,12 +203,14 @@ int lhmm_hybrid_step(lhmm_hybrid* h, lhmm_hybrid_stats* stats) {
     const int nm = h->nm;
     const long long t = h->t;
     lhmm_hybrid_stats S{};
-    // 1-2: SPH step and history
+    // 1: SPH step
     int rc = lhmm_sph_step(h->sph, h->sigma, h->gradL);
-    if (rc == LHMM_OK) rc = lhmm_sur_push_history(h->ring, nm, h->gradL, t, h->p.grad_scale, h->stream);
     if (rc != LHMM_OK) return rc;
     std::vector<int> on, entering;
     if (h->p.mode == LHMM_HYBRID_DPD) {
+        // 2, 4: history, micro-domains
+        rc = lhmm_sur_push_history(h->ring, nm, h->gradL, t, h->p.grad_scale, h->stream);
+        if (rc != LHMM_OK) return rc;
         rc = lhmm_micro_step(h->micro, h->gradL, h->p.k_micro, h->sigma);
         if (rc != LHMM_OK) return rc;
         h->box_steps += (long long)h->p.k_micro * nm;
@@ -228,18 +218,19 @@ int lhmm_hybrid_step(lhmm_hybrid* h, lhmm_hybrid_stats* stats) {
         on.resize(nm);
         for (int b = 0; b < nm; ++b) on[b] = b;
     } else {
-        // 3: surrogate and gate
-        rc = lhmm_sur_features(h->ring, nm, t, h->phi, h->X, h->stream);
+        // 2-3: history, surrogate and gate
+        rc = lhmm_sur_push_features(h->ring, nm, h->gradL, t, h->p.grad_scale, h->phi, h->X, h->stream);
         if (rc == LHMM_OK) rc = lhmm_sur_forward(h->sur, h->X, nm, h->Y);
-        if (rc == LHMM_OK)
-            rc = lhmm_sur_gate(h->Y, h->E, nm, 3, h->p.threshold, h->p.floor, h->mean, h->gflag, h->stream);
         if (rc != LHMM_OK) return rc;
+        double max2 = -1.0, warm2 = -1.0;
         if (h->p.max_grad > 0.0f) {
             const double mg = (double)h->p.max_grad, wg = mg * (h->p.warm_frac > 0.0f ? (double)h->p.warm_frac : 1.0);
-            k_input_gate<<<(nm + 255) / 256, 256, 0, h->stream>>>(h->gradL, nm, mg * mg, wg * wg, h->gflag);
-            LHMM_HIPCHK(hipGetLastError());
+            max2 = mg * mg;
+            warm2 = wg * wg;
         }
-        LHMM_HIPCHK(hipMemcpyAsync(h->gflag_h, h->gflag, nm * sizeof(unsigned), hipMemcpyDeviceToHost, h->stream));
+        rc = lhmm_sur_decide(h->Y, h->E, nm, h->p.threshold, h->p.floor, h->gradL, max2, warm2, h->mean, h->gflag_d,
+                             h->stream);
+        if (rc != LHMM_OK) return rc;
         LHMM_HIPCHK(hipStreamSynchronize(h->stream));
         // run: boxes advanced this step, the flagged ones (their DPD stress
         // is used) and, with a warm band, those whose gradient lies in it
@@ -286,9 +277,6 @@ int lhmm_hybrid_step(lhmm_hybrid* h, lhmm_hybrid_stats* stats) {
             h->box_steps += (long long)h->p.k_micro * (long long)run.size();
         }
         on.swap(run);  // the thin-cell check below covers every box that moved
-        LHMM_HIPCHK(hipMemcpyAsync(h->on_d, h->on_h, nm * sizeof(unsigned), hipMemcpyHostToDevice, h->stream));
-        rc = lhmm_sur_blend(h->mean, h->on_d, h->sigma_dpd, nm, h->p.stress_scale, h->sigma, h->stream);
-        if (rc != LHMM_OK) return rc;
     }
     // 5: thin cells among the boxes that moved
     if (!on.empty()) {
@@ -305,9 +293,15 @@ int lhmm_hybrid_step(lhmm_hybrid* h, lhmm_hybrid_stats* stats) {
         if (rc == LHMM_OK) rc = restore_and_replay(h, reset_warm, 0, -1);
         if (rc != LHMM_OK) return rc;
     }
-    const long n6 = 6L * h->n;
-    k_accumulate<<<(n6 + 255) / 256, 256, 0, h->stream>>>(h->sigma, n6, h->sigma_sum);
-    LHMM_HIPCHK(hipGetLastError());
+    if (h->p.mode == LHMM_HYBRID_DPD) {
+        const long n6 = 6L * h->n;
+        k_accumulate<<<(n6 + 255) / 256, 256, 0, h->stream>>>(h->sigma, n6, h->sigma_sum);
+        LHMM_HIPCHK(hipGetLastError());
+    } else {
+        rc = lhmm_sur_settle(h->mean, h->on_d, h->sigma_dpd, nm, h->n, h->p.stress_scale, h->sigma, h->sigma_sum,
+                             h->stream);
+        if (rc != LHMM_OK) return rc;
+    }
     h->n_sum += 1;
     h->t += 1;
     S.macro_step = h->t;

@@ -277,16 +277,16 @@ __global__ void k_outputs(const float* __restrict__ Ysrc, long stride, int nout_
 
 // history ring of the in-plane gradient components: sample t of particle b
 // goes to slot t mod HIST as (L_xx, L_xy, L_yx, L_yy)
+__device__ __forceinline__ float history_value(const double* L, int c, float scale) {
+    return (float)(L[c < 2 ? c : c + 1] * scale);
+}
+
 __global__ void k_push_history(float* __restrict__ ring, int n, const double* __restrict__ gradL, long t,
                                float scale) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= n) return;
-    const double* L = gradL + 9 * (long)b;
     float* o = ring + ((long)b * HIST + (int)(t % HIST)) * 4;
-    o[0] = (float)(L[0] * scale);
-    o[1] = (float)(L[1] * scale);
-    o[2] = (float)(L[3] * scale);
-    o[3] = (float)(L[4] * scale);
+    for (int c = 0; c < 4; ++c) o[c] = history_value(gradL + 9 * (long)b, c, scale);
 }
 
 // features of particle b after sample t: samples t-HIST+1 .. t (oldest
@@ -308,12 +308,31 @@ __global__ void k_features(const float* __restrict__ ring, int n, long t, const 
     X[i] = x;
 }
 
+// k_push_history and k_features in one pass: the newest sample goes to the
+// ring and to the features
+__global__ void k_push_features(float* __restrict__ ring, int n, const double* __restrict__ gradL, int slot0,
+                                float scale, const float* __restrict__ phi, float* __restrict__ X) {
+    constexpr int NF = 4 * HIST + 1;
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (long)n * NF) return;
+    const int b = (int)(i / NF), f = (int)(i % NF);
+    float x;
+    if (f < 4 * (HIST - 1)) {
+        const int slot = slot0 + 1 + f / 4;  // slot0: the newest sample's
+        x = ring[((long)b * HIST + (slot < HIST ? slot : slot - HIST)) * 4 + f % 4];
+    } else if (f < 4 * HIST) {
+        x = history_value(gradL + 9 * (long)b, f % 4, scale);
+        ring[((long)b * HIST + slot0) * 4 + f % 4] = x;
+    } else {
+        x = phi[b];
+    }
+    X[i] = x;
+}
+
 // ensemble mean and spread gate: spread = sqrt(mean_j var_members(Y_j)),
 // flag if spread > threshold x max(|mean|_2, floor)
-__global__ void k_gate(const float* __restrict__ Y, int n_members, int B, int Bp, int n_out, int nout_p,
-                       float threshold, float floor_, float* __restrict__ mean, unsigned* __restrict__ flag) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
+__device__ __forceinline__ unsigned gate(const float* Y, int n_members, int Bp, int n_out, int nout_p, float threshold,
+                                         float floor_, int b, float* mean) {
     float var_sum = 0.0f, norm2 = 0.0f;
     for (int j = 0; j < n_out; ++j) {
         float s = 0.0f, s2 = 0.0f;
@@ -328,7 +347,35 @@ __global__ void k_gate(const float* __restrict__ Y, int n_members, int B, int Bp
         mean[(long)b * n_out + j] = mu;
     }
     const float spread = sqrtf(var_sum / n_out);
-    flag[b] = spread > threshold * fmaxf(sqrtf(norm2), floor_) ? 1u : 0u;
+    return spread > threshold * fmaxf(sqrtf(norm2), floor_) ? 1u : 0u;
+}
+
+__global__ void k_gate(const float* __restrict__ Y, int n_members, int B, int Bp, int n_out, int nout_p,
+                       float threshold, float floor_, float* __restrict__ mean, unsigned* __restrict__ flag) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < B) flag[b] = gate(Y, n_members, Bp, n_out, nout_p, threshold, floor_, b, mean);
+}
+
+// The gate of a macro step.  With max2 >= 0 also the input-range gate: bit 1
+// of flag[b] is set when the micro gradient of particle b (row-major 3 x 3,
+// FP64) has squared Frobenius norm above max2, bit 2 when above warm2 (the
+// warm band below it); the sum of squares is formed in this fixed order
+// without fused products, so a host computation in FP64 takes the same
+// decisions.
+__global__ void k_decide(const float* __restrict__ Y, int n_members, int B, float threshold, float floor_,
+                         const double* __restrict__ L, double max2, double warm2, float* __restrict__ mean,
+                         unsigned* __restrict__ flag) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= B) return;
+    unsigned f = gate(Y, n_members, B, 3, 3, threshold, floor_, b, mean);
+    if (max2 >= 0.0) {
+        const double* l = L + 9 * (long)b;
+        double q = 0.0;
+        for (int k = 0; k < 9; ++k) q = __dadd_rn(q, __dmul_rn(l[k], l[k]));
+        if (q > max2) f |= 2u;
+        if (q > warm2) f |= 4u;
+    }
+    flag[b] = f;
 }
 
 // micro stresses (xx, yy, zz, xy, xz, yz) -> deviatoric in-plane targets
@@ -345,11 +392,8 @@ __global__ void k_targets(const double* __restrict__ sigma, int n, float inv_sca
 
 // stress for the macro solver: the micro stress where use_dpd[b], else the
 // traceless tensor built from the surrogate mean
-__global__ void k_blend(const float* __restrict__ mean, const unsigned* __restrict__ use_dpd,
-                        const double* __restrict__ sigma_dpd, int n, float scale, double* __restrict__ out) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    double* o = out + 6 * (long)b;
+__device__ __forceinline__ void blend(const float* mean, const unsigned* use_dpd, const double* sigma_dpd, int b,
+                                      float scale, double (&o)[6]) {
     if (use_dpd && use_dpd[b]) {
         for (int q = 0; q < 6; ++q) o[q] = sigma_dpd[6 * (long)b + q];
     } else {
@@ -362,6 +406,31 @@ __global__ void k_blend(const float* __restrict__ mean, const unsigned* __restri
         o[4] = 0.0;
         o[5] = 0.0;
     }
+}
+
+__global__ void k_blend(const float* __restrict__ mean, const unsigned* __restrict__ use_dpd,
+                        const double* __restrict__ sigma_dpd, int n, float scale, double* __restrict__ out) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= n) return;
+    double o[6];
+    blend(mean, use_dpd, sigma_dpd, b, scale, o);
+    for (int q = 0; q < 6; ++q) out[6 * (long)b + q] = o[q];
+}
+
+// k_blend for the n_blend first particles, then sum += out over all n
+__global__ void k_settle(const float* __restrict__ mean, const unsigned* __restrict__ use_dpd,
+                         const double* __restrict__ sigma_dpd, int n_blend, int n, float scale,
+                         double* __restrict__ out, double* __restrict__ sum) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= n) return;
+    double o[6];
+    if (b < n_blend) {
+        blend(mean, use_dpd, sigma_dpd, b, scale, o);
+        for (int q = 0; q < 6; ++q) out[6 * (long)b + q] = o[q];
+    } else {
+        for (int q = 0; q < 6; ++q) o[q] = out[6 * (long)b + q];
+    }
+    for (int q = 0; q < 6; ++q) sum[6 * (long)b + q] += o[q];
 }
 
 // gradient sample s of the history ring back to micro gradients (n x 9)
@@ -856,6 +925,30 @@ int copy_packed(lhmm_sur* s, bool grads, float* out) {
 }
 
 }  // namespace
+
+// The hybrid macro step's own passes (lhmm_internal.h).  Blocks of one or four
+// waves: a few thousand particles have to reach as many CUs as they can.
+int lhmm_sur_push_features(float* ring, int n, const double* gradL, long long t, float scale, const float* phi,
+                           float* X, hipStream_t stream) {
+    const long total = (long)n * (4 * HIST + 1);
+    k_push_features<<<(total + 255) / 256, 256, 0, stream>>>(ring, n, gradL, (int)(t % HIST), scale, phi, X);
+    LHMM_HIPCHK(hipGetLastError());
+    return LHMM_OK;
+}
+
+int lhmm_sur_decide(const float* Y, int n_members, int n, float threshold, float floor_, const double* gradL,
+                    double max2, double warm2, float* mean, unsigned* flag, hipStream_t stream) {
+    k_decide<<<(n + 63) / 64, 64, 0, stream>>>(Y, n_members, n, threshold, floor_, gradL, max2, warm2, mean, flag);
+    LHMM_HIPCHK(hipGetLastError());
+    return LHMM_OK;
+}
+
+int lhmm_sur_settle(const float* mean, const unsigned* use_dpd, const double* sigma_dpd, int n_blend, int n,
+                    float scale, double* sigma, double* sum, hipStream_t stream) {
+    k_settle<<<(n + 63) / 64, 64, 0, stream>>>(mean, use_dpd, sigma_dpd, n_blend, n, scale, sigma, sum);
+    LHMM_HIPCHK(hipGetLastError());
+    return LHMM_OK;
+}
 
 extern "C" {
 
