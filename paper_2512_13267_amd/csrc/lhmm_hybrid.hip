@@ -30,6 +30,7 @@
 
 #include "lhmm.h"
 #include "lhmm_internal.h"
+#include "lhmm_stage.h"
 
 struct lhmm_hybrid {
     lhmm_hybrid_params p{};
@@ -47,12 +48,14 @@ struct lhmm_hybrid {
     double* sigma_sum = nullptr;  // running sum of the stresses handed to SPH
     long long n_sum = 0;
     std::vector<void*> bufs;
+    HostStage stage;
     // host (pinned), and as the device sees it.  The mask of a step is read by
     // its last launch; the next step writes it after waiting for the stream.
     unsigned *gflag_h = nullptr, *on_h = nullptr, *gflag_d = nullptr, *on_d = nullptr;
     std::vector<int> hold_left;
     std::vector<unsigned char> was_on;   // DPD stress used in the last step
     std::vector<unsigned char> was_run;  // box advanced in the last step (used or warming)
+    bool live = false;                   // any box was
     std::vector<uint32_t> mflags;
 };
 
@@ -82,6 +85,7 @@ void hy_release(lhmm_hybrid* h) {
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     for (void* b : h->bufs) (void)hipFree(b);
     h->bufs.clear();
+    h->stage.release();
     if (h->gflag_h) (void)hipHostFree(h->gflag_h);
     if (h->on_h) (void)hipHostFree(h->on_h);
 }
@@ -166,6 +170,7 @@ int lhmm_hybrid_create(const lhmm_hybrid_params* p, lhmm_sph* sph, lhmm_micro* m
     if (rc == LHMM_OK && hipHostMalloc((void**)&h->on_h, m * sizeof(unsigned)) != hipSuccess)
         rc = lhmm_fail(LHMM_ERR_OOM, "pinned allocation failed");
     auto init = [&]() -> int {
+        LHMM_HIPCHK(h->stage.reserve((size_t)n * 6 * sizeof(double)));
         LHMM_HIPCHK(hipHostGetDevicePointer((void**)&h->gflag_d, h->gflag_h, 0));
         LHMM_HIPCHK(hipHostGetDevicePointer((void**)&h->on_d, h->on_h, 0));
         LHMM_HIPCHK(hipStreamSynchronize(st));
@@ -193,6 +198,7 @@ int lhmm_hybrid_create(const lhmm_hybrid_params* p, lhmm_sph* sph, lhmm_micro* m
     h->hold_left.assign(m, 0);
     h->was_on.assign(m, 0);
     h->was_run.assign(m, 0);
+    memset(h->on_h, 0, m * sizeof(unsigned));
     *out = h;
     return LHMM_OK;
 }
@@ -239,7 +245,11 @@ int lhmm_hybrid_step(lhmm_hybrid* h, lhmm_hybrid_stats* stats) {
         // warming: band boxes that were not live, restored only
         std::vector<int> run, warming;
         const bool band = h->p.max_grad > 0.0f && h->p.warm_frac > 0.0f;
-        for (int b = 0; b < nm; ++b) {
+        // nothing flagged and nothing live: the lists stay empty and every
+        // mark of the last step, all cleared, holds
+        unsigned any = 0;
+        for (int b = 0; b < nm; ++b) any |= h->gflag_h[b];
+        for (int b = 0; b < nm && (any || h->live); ++b) {
             const unsigned fl = h->gflag_h[b];
             if (fl & 3u) {
                 h->hold_left[b] = h->p.hold;
@@ -262,6 +272,7 @@ int lhmm_hybrid_step(lhmm_hybrid* h, lhmm_hybrid_stats* stats) {
             h->was_run[b] = is_on || is_warm;
             h->on_h[b] = is_on ? 1u : 0u;
         }
+        h->live = !run.empty();
         S.n_dpd = (int)on.size();
         S.n_entered = (int)entering.size();
         // entering boxes relive the intervals before this one; warming boxes
@@ -314,8 +325,7 @@ int lhmm_hybrid_step(lhmm_hybrid* h, lhmm_hybrid_stats* stats) {
 int lhmm_hybrid_state(lhmm_hybrid* h, double* sigma, uint32_t* on_dpd) {
     lhmm_clear_error();
     if (!h) return lhmm_fail(LHMM_ERR_ARG, "null argument");
-    LHMM_HIPCHK(hipStreamSynchronize(h->stream));
-    if (sigma) LHMM_HIPCHK(hipMemcpy(sigma, h->sigma, (size_t)h->n * 6 * sizeof(double), hipMemcpyDeviceToHost));
+    LHMM_HIPCHK(h->stage.copy(h->stream, {{h->sigma, (size_t)h->n * 6 * sizeof(double)}}, {sigma}));
     if (on_dpd) {
         if (h->p.mode == LHMM_HYBRID_DPD) {
             for (int b = 0; b < h->nm; ++b) on_dpd[b] = 1u;
@@ -329,13 +339,11 @@ int lhmm_hybrid_state(lhmm_hybrid* h, double* sigma, uint32_t* on_dpd) {
 int lhmm_hybrid_mean_stress(lhmm_hybrid* h, double* sigma_mean, int32_t reset) {
     lhmm_clear_error();
     if (!h) return lhmm_fail(LHMM_ERR_ARG, "null argument");
-    LHMM_HIPCHK(hipStreamSynchronize(h->stream));
     const size_t n6 = 6 * (size_t)h->n;
     if (sigma_mean) {
-        std::vector<double> buf(n6);
-        LHMM_HIPCHK(hipMemcpy(buf.data(), h->sigma_sum, n6 * sizeof(double), hipMemcpyDeviceToHost));
+        LHMM_HIPCHK(h->stage.copy(h->stream, {{h->sigma_sum, n6 * sizeof(double)}}, {sigma_mean}));
         const double w = h->n_sum > 0 ? 1.0 / (double)h->n_sum : 0.0;
-        for (size_t i = 0; i < n6; ++i) sigma_mean[i] = buf[i] * w;
+        for (size_t i = 0; i < n6; ++i) sigma_mean[i] *= w;
     }
     if (reset) {
         k_zero<<<(n6 + 255) / 256, 256, 0, h->stream>>>(h->sigma_sum, (long)n6);

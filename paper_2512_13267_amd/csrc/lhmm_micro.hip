@@ -52,6 +52,7 @@
 
 #include "lhmm.h"
 #include "lhmm_internal.h"
+#include "lhmm_stage.h"
 
 namespace {
 
@@ -1930,6 +1931,7 @@ __global__ void k_finalize(Ctx C, double* __restrict__ stress_out, double* __res
 
 struct lhmm_micro {
     lhmm_params p{};
+    HostStage stage;  // read-backs
     lhmm_micro_config cfg{};
     int lds_cells = 0, lds_cols = 0;  // dynamic LDS of the binning (ints)
     int n_slabs = 0, window = 1;      // slabs of all boxes; steps whose partial sums are kept
@@ -2222,6 +2224,7 @@ void release(lhmm_micro* m) {
                     m->d_snap_dyn};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
+    m->stage.release();
     for (auto& gr : m->groups)
         if (gr.d_lists) (void)hipFree(gr.d_lists);
     m->groups.clear();
@@ -2241,6 +2244,25 @@ int sync_engine(lhmm_micro* m) {
     HIPCHK(hipStreamSynchronize(m->stream));
     HIPCHK(hipGetLastError());
     return LHMM_OK;
+}
+
+// device memory of the engine -> host, after the work on its stream
+int read_back(lhmm_micro* m, void* dst, const void* src, size_t bytes) {
+    HIPCHK(m->stage.copy(m->stream, {{src, bytes}}, {dst}));
+    HIPCHK(hipGetLastError());
+    return LHMM_OK;
+}
+
+// elements [e0, e0 + n) of a 3 x N array -> rows of an N x 3 one
+template <typename real>
+void to_rows(double* dst, size_t N, size_t e0, const real* x, size_t n) {
+    while (n > 0) {
+        const size_t k = e0 / N, i = e0 % N, len = std::min(n, N - i);
+        for (size_t j = 0; j < len; ++j) dst[3 * (i + j) + k] = (double)x[j];
+        e0 += len;
+        x += len;
+        n -= len;
+    }
 }
 
 constexpr size_t MAX_SUB_GRAPHS = 64;
@@ -2572,6 +2594,8 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
 #undef ALLOC
     if (rc == LHMM_OK) {
         const size_t bytes = 3 * N * m->real_size;
+        if (m->stage.reserve(2 * bytes + n_boxes * sizeof(BoxDyn) + 64) != hipSuccess)
+            rc = fail(LHMM_ERR_OOM, "pinned allocation failed");
         // search layout: each particle at most twice (its cell, and the
         // image of a bottom or top cell; n2 >= 3)
         for (void** pp : {&m->d_s, &m->d_c, &m->d_f, &m->d_sid[0], &m->d_sid[1], &m->d_sord[0], &m->d_sord[1], &m->d_cord,
@@ -2736,32 +2760,39 @@ int lhmm_micro_set_state(lhmm_micro* m, const double* s, const double* c, const 
 int lhmm_micro_get_state(lhmm_micro* m, double* s, double* c, double* f, double* h, uint64_t* step) {
     g_err.clear();
     if (!m) return fail(LHMM_ERR_ARG, "null engine");
-    int rc = sync_engine(m);
-    if (rc != LHMM_OK) return rc;
-    const size_t N = (size_t)m->n_total;
-    std::vector<char> buf(3 * N * m->real_size + 1);
-    double* dsts[3] = {s, c, f};
-    const void* srcs[3] = {m->d_s, m->d_c, m->d_f};
-    for (int which = 0; which < 3; ++which) {
-        double* dst = dsts[which];
-        if (!dst) continue;
-        HIPCHK(hipMemcpy(buf.data(), srcs[which], 3 * N * m->real_size, hipMemcpyDeviceToHost));
-        for (size_t i = 0; i < N; ++i)
-            for (int k = 0; k < 3; ++k)
-                dst[3 * i + k] = m->precision == LHMM_FP64 ? ((double*)buf.data())[k * N + i]
-                                                           : (double)((float*)buf.data())[k * N + i];
-    }
+    const size_t N = (size_t)m->n_total, bytes = 3 * N * m->real_size;
+    double* const dsts[3] = {s, c, f};
+    const void* const srcs[3] = {m->d_s, m->d_c, m->d_f};
+    HostStage::Part parts[5];
+    int kind[5], n = 0;
+    for (int k = 0; k < 3; ++k)
+        if (dsts[k]) {
+            kind[n] = k;
+            parts[n++] = {srcs[k], bytes};
+        }
+    std::vector<BoxDyn> dyn(h ? m->n_boxes : 0);
     if (h) {
-        std::vector<BoxDyn> dyn(m->n_boxes);
-        HIPCHK(hipMemcpy(dyn.data(), m->d_dyn, m->n_boxes * sizeof(BoxDyn), hipMemcpyDeviceToHost));
-        for (int b = 0; b < m->n_boxes; ++b)
-            for (int k = 0; k < 9; ++k) h[9 * b + k] = dyn[b].h[k];
+        kind[n] = 3;
+        parts[n++] = {m->d_dyn, m->n_boxes * sizeof(BoxDyn)};
     }
+    unsigned long long st = 0;
     if (step) {
-        unsigned long long st = 0;
-        HIPCHK(hipMemcpy(&st, m->d_step, sizeof st, hipMemcpyDeviceToHost));
-        *step = st;
+        kind[n] = 4;
+        parts[n++] = {m->d_step, sizeof st};
     }
+    HIPCHK(m->stage.read(m->stream, parts, n, [&](int k, size_t at, size_t len, const char* x) {
+        if (kind[k] >= 3) {
+            memcpy((kind[k] == 3 ? (char*)dyn.data() : (char*)&st) + at, x, len);
+        } else if (m->precision == LHMM_FP64) {
+            to_rows(dsts[kind[k]], N, at / sizeof(double), (const double*)x, len / sizeof(double));
+        } else {
+            to_rows(dsts[kind[k]], N, at / sizeof(float), (const float*)x, len / sizeof(float));
+        }
+    }));
+    HIPCHK(hipGetLastError());
+    for (size_t b = 0; b < dyn.size(); ++b)
+        for (int k = 0; k < 9; ++k) h[9 * b + k] = dyn[b].h[k];
+    if (step) *step = st;
     return LHMM_OK;
 }
 
@@ -3214,10 +3245,9 @@ int lhmm_micro_time(lhmm_micro* m, const double* gradL, int32_t n_steps, double*
 int lhmm_micro_stress_parts(lhmm_micro* m, double* parts_out) {
     g_err.clear();
     if (!m || !parts_out) return fail(LHMM_ERR_ARG, "null argument");
-    int rc = sync_engine(m);
-    if (rc != LHMM_OK) return rc;
     std::vector<double> v((size_t)ACC * m->n_boxes);
-    HIPCHK(hipMemcpy(v.data(), m->d_parts, v.size() * sizeof(double), hipMemcpyDeviceToHost));
+    int rc = read_back(m, v.data(), m->d_parts, v.size() * sizeof(double));
+    if (rc != LHMM_OK) return rc;
     for (int b = 0; b < m->n_boxes; ++b)
         for (int q = 0; q < 18; ++q) parts_out[18 * (size_t)b + q] = v[(size_t)ACC * b + q];
     return LHMM_OK;
@@ -3228,10 +3258,9 @@ int lhmm_micro_components(lhmm_micro* m, double* out) {
     if (!m || !out) return fail(LHMM_ERR_ARG, "null argument");
     if (!(m->p.flags & LHMM_OPT_COMPONENTS))
         return fail(LHMM_ERR_STATE, "the engine was created without LHMM_OPT_COMPONENTS");
-    int rc = sync_engine(m);
-    if (rc != LHMM_OK) return rc;
     std::vector<double> v((size_t)ACC * m->n_boxes);
-    HIPCHK(hipMemcpy(v.data(), m->d_parts, v.size() * sizeof(double), hipMemcpyDeviceToHost));
+    int rc = read_back(m, v.data(), m->d_parts, v.size() * sizeof(double));
+    if (rc != LHMM_OK) return rc;
     // sums: kinetic 0, pair 6, FENE 12, C 18, D 24, R 30 -> kin, C, D, R, FENE
     const int src[5] = {0, 18, 24, 30, 12};
     for (int b = 0; b < m->n_boxes; ++b)
@@ -3243,10 +3272,9 @@ int lhmm_micro_components(lhmm_micro* m, double* out) {
 int lhmm_micro_pair_total(lhmm_micro* m, uint64_t* pairs_out) {
     g_err.clear();
     if (!m || !pairs_out) return fail(LHMM_ERR_ARG, "null argument");
-    int rc = sync_engine(m);
-    if (rc != LHMM_OK) return rc;
     std::vector<unsigned long long> v(m->n_boxes);
-    HIPCHK(hipMemcpy(v.data(), m->d_tot_pairs, m->n_boxes * sizeof(unsigned long long), hipMemcpyDeviceToHost));
+    int rc = read_back(m, v.data(), m->d_tot_pairs, m->n_boxes * sizeof(unsigned long long));
+    if (rc != LHMM_OK) return rc;
     for (int b = 0; b < m->n_boxes; ++b) pairs_out[b] = v[b];
     return LHMM_OK;
 }
@@ -3266,10 +3294,9 @@ int lhmm_micro_prepare(lhmm_micro* m, int32_t n_steps) {
 int lhmm_micro_pair_counts(lhmm_micro* m, uint64_t* pairs_out) {
     g_err.clear();
     if (!m || !pairs_out) return fail(LHMM_ERR_ARG, "null argument");
-    int rc = sync_engine(m);
-    if (rc != LHMM_OK) return rc;
     std::vector<unsigned long long> v(m->n_boxes);
-    HIPCHK(hipMemcpy(v.data(), m->d_acc_pairs, m->n_boxes * sizeof(unsigned long long), hipMemcpyDeviceToHost));
+    int rc = read_back(m, v.data(), m->d_acc_pairs, m->n_boxes * sizeof(unsigned long long));
+    if (rc != LHMM_OK) return rc;
     for (int b = 0; b < m->n_boxes; ++b) pairs_out[b] = v[b];
     return LHMM_OK;
 }
@@ -3277,10 +3304,9 @@ int lhmm_micro_pair_counts(lhmm_micro* m, uint64_t* pairs_out) {
 int lhmm_micro_flags(lhmm_micro* m, uint32_t* flags_out, int32_t clear) {
     g_err.clear();
     if (!m || !flags_out) return fail(LHMM_ERR_ARG, "null argument");
-    int rc = sync_engine(m);
+    int rc = read_back(m, flags_out, m->d_flags, m->n_boxes * sizeof(unsigned));
     if (rc != LHMM_OK) return rc;
-    HIPCHK(hipMemcpy(flags_out, m->d_flags, m->n_boxes * sizeof(unsigned), hipMemcpyDeviceToHost));
-    if (clear) HIPCHK(hipMemset(m->d_flags, 0, m->n_boxes * sizeof(unsigned)));
+    if (clear) HIPCHK(hipMemsetAsync(m->d_flags, 0, m->n_boxes * sizeof(unsigned), m->stream));
     return LHMM_OK;
 }
 

@@ -25,6 +25,7 @@
 
 #include "lhmm.h"
 #include "lhmm_internal.h"
+#include "lhmm_stage.h"
 
 namespace {
 
@@ -630,6 +631,7 @@ struct lhmm_sph {
     double* d_sigma = nullptr;  // n x 6, micro stresses of the last interval (zero at start)
     double* d_gradL = nullptr;  // n x 9
     void* bufs[16] = {};
+    HostStage stage;
 };
 
 namespace {
@@ -638,6 +640,7 @@ void sph_release(lhmm_sph* s) {
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     for (void* b : s->bufs)
         if (b) (void)hipFree(b);
+    s->stage.release();
 }
 
 void launch_tile(lhmm_sph* s, const double* sigma) {
@@ -772,6 +775,7 @@ int lhmm_sph_create(const lhmm_sph_params* p, int32_t n, const double* r0, const
     S.s2s = (double*)s->bufs[14];
     S.cell = (unsigned*)s->bufs[15];
     auto init = [&]() -> int {
+        LHMM_HIPCHK(s->stage.reserve(15 * m * sizeof(double)));
         LHMM_HIPCHK(hipMemcpy(S.r, r0, 2 * (size_t)n * sizeof(double), hipMemcpyHostToDevice));
         LHMM_HIPCHK(hipMemcpy(S.v, v0, 2 * (size_t)n * sizeof(double), hipMemcpyHostToDevice));
         LHMM_HIPCHK(hipMemset(s->d_sigma, 0, 6 * (size_t)n * sizeof(double)));
@@ -804,27 +808,18 @@ int lhmm_sph_step(lhmm_sph* s, const double* sigma, double* gradL_out) {
 int lhmm_sph_get_state(lhmm_sph* s, double* r, double* v, double* d) {
     lhmm_clear_error();
     if (!s) return lhmm_fail(LHMM_ERR_ARG, "null engine");
-    LHMM_HIPCHK(hipStreamSynchronize(s->stream));
-    const size_t n = (size_t)s->S.n;
-    if (r) LHMM_HIPCHK(hipMemcpy(r, s->S.r, 2 * n * sizeof(double), hipMemcpyDeviceToHost));
-    if (v) LHMM_HIPCHK(hipMemcpy(v, s->S.v, 2 * n * sizeof(double), hipMemcpyDeviceToHost));
-    if (d) {
-        // density at the current positions
-        launch_density(s);
-        LHMM_HIPCHK(hipGetLastError());
-        LHMM_HIPCHK(hipStreamSynchronize(s->stream));
-        LHMM_HIPCHK(hipMemcpy(d, s->S.d, n * sizeof(double), hipMemcpyDeviceToHost));
-    }
+    if (d) launch_density(s);  // at the current positions
+    LHMM_HIPCHK(hipGetLastError());
+    const size_t b = (size_t)s->S.n * sizeof(double);
+    LHMM_HIPCHK(s->stage.copy(s->stream, {{s->S.r, 2 * b}, {s->S.v, 2 * b}, {s->S.d, b}}, {r, v, d}));
     return LHMM_OK;
 }
 
 int lhmm_sph_coupling_state(lhmm_sph* s, double* sigma, double* gradL) {
     lhmm_clear_error();
     if (!s) return lhmm_fail(LHMM_ERR_ARG, "null engine");
-    LHMM_HIPCHK(hipStreamSynchronize(s->stream));
-    const size_t n = (size_t)s->S.n;
-    if (sigma) LHMM_HIPCHK(hipMemcpy(sigma, s->d_sigma, 6 * n * sizeof(double), hipMemcpyDeviceToHost));
-    if (gradL) LHMM_HIPCHK(hipMemcpy(gradL, s->d_gradL, 9 * n * sizeof(double), hipMemcpyDeviceToHost));
+    const size_t b = (size_t)s->S.n * sizeof(double);
+    LHMM_HIPCHK(s->stage.copy(s->stream, {{s->d_sigma, 6 * b}, {s->d_gradL, 9 * b}}, {sigma, gradL}));
     return LHMM_OK;
 }
 

@@ -29,6 +29,7 @@
 
 #include "lhmm.h"
 #include "lhmm_internal.h"
+#include "lhmm_stage.h"
 #include "lhmm_mlp.h"
 
 namespace {
@@ -488,6 +489,7 @@ struct lhmm_sur {
     int device = 0;  // the device current at create
     hipStream_t stream = nullptr;
     std::vector<void*> bufs;
+    HostStage stage;
     // FP32 masters, grads, Adam moments, per member (stride = size of one member's tensor)
     float *W1 = nullptr, *b1 = nullptr, *W2 = nullptr, *b2 = nullptr, *W3 = nullptr, *b3 = nullptr;
     float *gW1, *gb1, *gW2, *gb2, *gW3, *gb3;
@@ -522,6 +524,7 @@ void sur_release(lhmm_sur* s) {
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     for (void* b : s->bufs) (void)hipFree(b);
     s->bufs.clear();
+    s->stage.release();
 }
 
 constexpr int KCHUNK = 512;  // k-split chunk of the weight-gradient products
@@ -831,6 +834,8 @@ int lhmm_sur_create(const lhmm_sur_params* p, const float* weights, void* stream
             rc = rc ? rc : sur_alloc(s, &s->part_k, E * ((Bm + KCHUNK - 1) / KCHUNK) * mn);
         }
     }
+    if (rc == LHMM_OK && s->stage.reserve(E * (size_t)(w1 + w2 + w3 + 2 * nh + no) * sizeof(float)) != hipSuccess)
+        rc = lhmm_fail(LHMM_ERR_OOM, "pinned allocation failed");
     if (rc == LHMM_OK) rc = lhmm_sur_set_weights(s, weights);
     if (rc != LHMM_OK) {
         sur_release(s);
@@ -897,30 +902,55 @@ int lhmm_sur_set_weights(lhmm_sur* s, const float* weights) {
 
 namespace {
 
-// device FP32 tensors of one kind (masters or gradients) -> packed host layout
+// device FP32 tensors of one kind (masters or gradients) in the packed host
+// layout: member after member W1, b1, W2, b2, W3, b3 without padding; the
+// elements [q0, q0 + n) go to out[0 .. n), pinned host memory
+struct PackArgs {
+    const float* t[6];
+    long stride[6];  // of a member
+    int cols[6], ld[6];
+    long first[7];   // element of a member at which the tensor starts
+};
+
+__global__ void k_pack(PackArgs a, long q0, long n, float* __restrict__ out) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const long e = (q0 + i) / a.first[6], r = (q0 + i) % a.first[6];
+    int k = 0;
+#pragma unroll
+    for (int q = 1; q < 6; ++q) k = r >= a.first[q] ? q : k;
+    const float* t = a.t[0];
+    long stride = a.stride[0], x = r;
+    int cols = a.cols[0], ld = a.ld[0];
+#pragma unroll
+    for (int q = 1; q < 6; ++q)
+        if (k == q) {
+            t = a.t[q];
+            stride = a.stride[q];
+            cols = a.cols[q];
+            ld = a.ld[q];
+            x = r - a.first[q];
+        }
+    out[i] = t[e * stride + x / cols * ld + x % cols];
+}
+
 int copy_packed(lhmm_sur* s, bool grads, float* out) {
-    const int E = s->E, nin = s->nin, nh = s->nh, nout = s->nout, no = s->nout_p;
-    const long w1 = szW1(s), w2 = szW2(s), w3 = szW3(s);
-    std::vector<float> W1((size_t)E * w1), W2((size_t)E * w2), W3((size_t)E * w3), B1((size_t)E * nh),
-        B2((size_t)E * nh), B3((size_t)E * no);
-    const float* src[6] = {grads ? s->gW1 : s->W1, grads ? s->gb1 : s->b1, grads ? s->gW2 : s->W2,
-                           grads ? s->gb2 : s->b2, grads ? s->gW3 : s->W3, grads ? s->gb3 : s->b3};
-    std::vector<float>* dst[6] = {&W1, &B1, &W2, &B2, &W3, &B3};
-    LHMM_HIPCHK(hipStreamSynchronize(s->stream));
-    for (int k = 0; k < 6; ++k)
-        LHMM_HIPCHK(hipMemcpy(dst[k]->data(), src[k], dst[k]->size() * 4, hipMemcpyDeviceToHost));
-    float* q = out;
-    for (int e = 0; e < E; ++e) {
-        for (int i = 0; i < nin; ++i)
-            for (int j = 0; j < nh; ++j) *q++ = W1[e * w1 + (long)i * nh + j];
-        for (int j = 0; j < nh; ++j) *q++ = B1[(size_t)e * nh + j];
-        for (int i = 0; i < nh; ++i)
-            for (int j = 0; j < nh; ++j) *q++ = W2[e * w2 + (long)i * nh + j];
-        for (int j = 0; j < nh; ++j) *q++ = B2[(size_t)e * nh + j];
-        for (int i = 0; i < nh; ++i)
-            for (int j = 0; j < nout; ++j) *q++ = W3[e * w3 + (long)i * no + j];
-        for (int j = 0; j < nout; ++j) *q++ = B3[(size_t)e * no + j];
-    }
+    const int nin = s->nin, nh = s->nh, nout = s->nout, no = s->nout_p;
+    const PackArgs a = {{grads ? s->gW1 : s->W1, grads ? s->gb1 : s->b1, grads ? s->gW2 : s->W2,
+                         grads ? s->gb2 : s->b2, grads ? s->gW3 : s->W3, grads ? s->gb3 : s->b3},
+                        {szW1(s), nh, szW2(s), nh, szW3(s), no},
+                        {nh, nh, nh, nh, nout, nout},
+                        {nh, nh, nh, nh, no, no},
+                        {0, (long)nin * nh, (long)(nin + 1) * nh, (long)(nin + 1 + nh) * nh, (long)(nin + 2 + nh) * nh,
+                         (long)(nin + 2 + nh) * nh + (long)nh * nout, (long)(nin + 2 + nh) * nh + (long)(nh + 1) * nout}};
+    LHMM_HIPCHK(s->stage.run(
+        s->stream, (size_t)s->E * a.first[6] * sizeof(float),
+        [&](size_t o, size_t bytes, char* pinned) {
+            const long n = (long)(bytes / sizeof(float));
+            k_pack<<<(n + 255) / 256, 256, 0, s->stream>>>(a, (long)(o / sizeof(float)), n, (float*)pinned);
+            return hipGetLastError();
+        },
+        [&](size_t o, size_t bytes, const char* x) { std::memcpy((char*)out + o, x, bytes); }));
     return LHMM_OK;
 }
 

@@ -77,12 +77,13 @@ class Micro:
 
     def get_state(self, with_forces: bool = False):
         """(s, c, h (n_boxes, 3, 3), step[, f])."""
-        s = np.zeros((self.n_total, 3))
-        c = np.zeros((self.n_total, 3))
-        f = np.zeros((self.n_total, 3))
-        h = np.zeros((self.n_boxes, 9))
+        s = np.empty((self.n_total, 3))
+        c = np.empty((self.n_total, 3))
+        f = np.empty((self.n_total, 3)) if with_forces else None
+        h = np.empty((self.n_boxes, 9))
         st = C.c_uint64()
-        check(lib().lhmm_micro_get_state(self._h, _dptr(s), _dptr(c), _dptr(f), _dptr(h), C.byref(st)))
+        check(lib().lhmm_micro_get_state(self._h, _dptr(s), _dptr(c), _dptr(f) if with_forces else None, _dptr(h),
+                                         C.byref(st)))
         if with_forces:
             return s, c, h.reshape(self.n_boxes, 3, 3), int(st.value), f
         return s, c, h.reshape(self.n_boxes, 3, 3), int(st.value)
