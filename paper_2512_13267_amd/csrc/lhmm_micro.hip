@@ -857,7 +857,8 @@ __device__ __forceinline__ void block_scan(int n, int* wsum /* BT / 64 */, Val v
 // layout) and, per cell, those in its own; then it ranks and moves its own
 // particles only.  The source records are in the last step's cell order (in
 // index order at a chunk's first step), so a wave's loads and stores fall on
-// neighbouring records.  Written per particle: (x, y, z, index), (c, index) in
+// neighbouring records; they are loaded as soon as the slab's particles are
+// known and arrive during the scans.  Written per particle: (x, y, z, index), (c, index) in
 // cell order, the source position in perm, and (x, y, z, cell-order position)
 // in the search layout, once more for the images of the bottom and top cells.
 //
@@ -888,7 +889,7 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
     constexpr int PER = SLAB_CAP / T;
     extern __shared__ int lds[];
     __shared__ int wsum[T / 64];
-    __shared__ int base[3];  // particles and images before the slab, images in it
+    __shared__ int base[4];  // particles and images before the slab, images in it, its particles
     const int tid = threadIdx.x;
     if ((int)blockIdx.x < n_cell) {
         const int q = blockIdx.x * T + tid;
@@ -903,8 +904,8 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
     int* col_off = cnt + lds_cells;  // offsets from cell order to the search layout: the column's cells,
     int* lo_off = col_off + lds_cols;  // the image of its top cells below it,
     int* hi_off = lo_off + lds_cols;   // the image of its bottom cells above it
-    int* ent = hi_off + lds_cols;    // SLAB_CAP: source positions by slot
-    int* lid = ent + SLAB_CAP;       // SLAB_CAP: particle indices by slot
+    int* own = hi_off + lds_cols;    // SLAB_CAP: source positions of the slab's particles, as found
+    int* lid = own + SLAB_CAP;       // SLAB_CAP: particle indices by cell
     int slab = xcd_local_work(blockIdx.x - n_cell, gridDim.x - n_cell);
     if (C.slab_list) slab = C.slab_list[slab];
     const int b = C.slab_box[slab];
@@ -916,26 +917,39 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
     const int nc = c1 - c0, s0 = c0 * n2, s1 = c1 * n2, ncell = nc * n2;
     if (nc == 0) return;  // fewer columns than slabs
     for (int k = tid; k < ncell; k += T) cnt[k] = 0;
-    if (tid < 3) base[tid] = 0;
+    if (tid < 4) base[tid] = 0;
     __syncthreads();
     const float inv_n2 = 1.0f / (float)n2;
     const int* key = C.key + B.off;
     int before = 0, img = 0;
-#pragma unroll 4
-    for (int k = tid; k < B.n; k += T) {
-        const int cell = key[k];
-        if (cell < s0) {
-            const int z = cell - div_small(cell, inv_n2) * n2;
-            before += 1;
-            img += (z < zs ? 1 : 0) + (z >= n2 - zs ? 1 : 0);
-        } else if (cell < s1) {
-            atomicAdd(&cnt[cell - s0], 1);
-        }
-    }
+    for (int k0 = tid; k0 - tid < B.n; k0 += 4 * T) {  // four keys in flight
+        int cell[4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        before += __shfl_xor(before, o, 64);
-        img += __shfl_xor(img, o, 64);
+        for (int u = 0; u < 4; ++u) cell[u] = key[min(k0 + u * T, B.n - 1)];
+        unsigned long long mine[4];
+        int found = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool on = k0 + u * T < B.n, early = on && cell[u] < s0;
+            const int z = cell[u] - div_small(cell[u], inv_n2) * n2;
+            before += __popcll(__ballot(early));
+            img += __popcll(__ballot(early && z < zs)) + __popcll(__ballot(early && z >= n2 - zs));
+            mine[u] = __ballot(on && cell[u] >= s0 && cell[u] < s1);
+            found += __popcll(mine[u]);
+        }
+        if (found == 0) continue;  // wave-uniform
+        int e = 0;
+        if ((tid & 63) == 0) e = atomicAdd(&base[3], found);
+        e = __builtin_amdgcn_readfirstlane(e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (mine[u] >> (tid & 63) & 1) {
+                const int slot = e + __popcll(mine[u] & ((1ull << (tid & 63)) - 1));
+                atomicAdd(&cnt[cell[u] - s0], 1);
+                if (slot < SLAB_CAP) own[slot] = k0 + u * T;
+            }
+            e += __popcll(mine[u]);
+        }
     }
     if ((tid & 63) == 0) {
         atomicAdd(&base[0], before);
@@ -944,9 +958,24 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
     __syncthreads();
     before = base[0];
     img = base[1];
+    const int total = base[3];
+    const bool fits = total <= SLAB_CAP;
+    const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
+    const V4* srcC = (const V4*)C.cord + B.off;
+    // the records of the slab's particles, on their way during the scans
+    V4 S[PER], V[PER];
+    int src[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int e = tid + u * T;
+        src[u] = fits && e < total ? own[e] : -1;
+        if (src[u] >= 0) {
+            S[u] = srcS[src[u]];
+            V[u] = srcC[src[u]];
+        }
+    }
     block_scan<T>(ncell, wsum, [&](int k) { return cnt[k]; }, [&](int k, int excl) { cnt[k] = excl; });
     __syncthreads();
-    const int total = cnt[ncell];
     // images before each column (its top and bottom zsub cells' particles
     // appear once more), scanned over the slab's columns
     block_scan<T>(
@@ -983,24 +1012,20 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
         srec[before + hi_off[col] + cnt[col * n2 + zs] + g % SREC_PAD] = R::make(far, far, far, 0);
     }
     __syncthreads();
-    const bool fits = total <= SLAB_CAP;
     int* perm = C.perm + B.off;
-#pragma unroll 4
-    for (int k = tid; k < B.n; k += T) {
-        const int cell = key[k];
-        if (cell >= s0 && cell < s1) {
-            const int slot = atomicAdd(&cnt[cell - s0], 1);
-            if (fits)
-                ent[slot] = k;
-            else
-                perm[before + slot] = k;
+    // from here on cnt[k] counts up to the end of cell k
+    if (fits) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (src[u] >= 0) lid[atomicAdd(&cnt[R::id(V[u]) - s0], 1)] = R::id(S[u]);
+    } else {
+        for (int k = tid; k < B.n; k += T) {
+            const int cell = key[k];
+            if (cell >= s0 && cell < s1) perm[before + atomicAdd(&cnt[cell - s0], 1)] = k;
         }
+        __threadfence_block();
     }
-    if (!fits) __threadfence_block();
     __syncthreads();
-    // cnt[k] now ends cell k
-    const V4* srcS = (const V4*)(A.first ? C.sid[A.slot] : C.sord[A.slot]) + B.off;
-    const V4* srcC = (const V4*)C.cord + B.off;
     V4* pv = (V4*)C.cell_pv + 2 * (size_t)B.off;
     const real h00 = (real)D.h[0], h01 = (real)D.h[1], h10 = (real)D.h[3], h11 = (real)D.h[4];
     const real h22 = (real)D.h[8];
@@ -1019,21 +1044,6 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
         if (zc < zs) o[p + hi_off[col]] = R::make(x, y, z + h22, (g << 5) | 18);
     };
     if (fits) {
-        V4 S[PER], V[PER];
-        int src[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int slot = tid + u * T;
-            src[u] = slot < total ? ent[slot] : -1;
-            if (src[u] >= 0) {
-                S[u] = srcS[src[u]];
-                V[u] = srcC[src[u]];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (src[u] >= 0) lid[tid + u * T] = R::id(S[u]);
-        __syncthreads();
         // a particle's position is its cell's start plus the number of its
         // cell's entries with a smaller index (a few each)
 #pragma unroll
