@@ -815,9 +815,27 @@ __global__ __launch_bounds__(BS) void k_begin_chunk(Ctx C, int koff, int advance
     C.key[i] = cell;
 }
 
+// Inclusive scans in registers over rows of 16 lanes and over the wave (six
+// steps through LDS permutes, and wave totals read one by one, cost the
+// binning 1 us a launch).
+__device__ __forceinline__ int row_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // from 1, 2, 4 and 8 lanes below in the row
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    return x;
+}
+
+__device__ __forceinline__ int wave_scan(int x) {
+    x = row_scan(x);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // lane 15 of a row to rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2 and 3
+    return x;
+}
+
 // Exclusive scan over k in [0, n) of val(k) by a workgroup of BT threads:
 // each thread sums a run of consecutive k, the run totals are scanned
-// (wave shuffles, then the wave totals), and each thread walks its run
+// (in the wave, then the wave totals), and each thread walks its run
 // again calling out(k, sum of val(0 .. k-1)); out(n, total) once.  val(k)
 // is read before out(k) is called, by the same thread.
 template <int BT, class Val, class Out>
@@ -827,18 +845,13 @@ __device__ __forceinline__ void block_scan(int n, int* wsum /* BT / 64 */, Val v
     const int k0 = min((int)threadIdx.x * per, n), k1 = min(k0 + per, n);
     int run = 0;
     for (int k = k0; k < k1; ++k) run += val(k);
-    int x = run;  // inclusive scan of the run totals within the wave
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
+    const int x = wave_scan(run);
     if (lane == 63) wsum[wv] = x;
     __syncthreads();
-    int excl = x - run;
-    for (int w = 0; w < wv; ++w) excl += wsum[w];
-    int total = 0;
-    for (int w = 0; w < BT / 64; ++w) total += wsum[w];
+    // the wave totals (16 at most), scanned by every wave
+    const int sums = row_scan(lane < BT / 64 ? wsum[lane] : 0), w = __builtin_amdgcn_readfirstlane(wv);
+    const int total = __builtin_amdgcn_readlane(sums, BT / 64 - 1);
+    int excl = x - run + (w > 0 ? __builtin_amdgcn_readlane(sums, w - 1) : 0);
     __syncthreads();
     for (int k = k0; k < k1; ++k) {
         const int v = val(k);
