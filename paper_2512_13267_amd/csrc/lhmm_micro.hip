@@ -826,6 +826,20 @@ __device__ __forceinline__ int row_scan(int x) {
     return x;
 }
 
+// lane L of each row of 16, in all its lanes
+template <int L>
+__device__ __forceinline__ int row_lane(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, 0x150 + L, 0xF, 0xF, false);
+}
+template <int L>
+__device__ __forceinline__ float row_lane(float x) {
+    return __int_as_float(row_lane<L>(__float_as_int(x)));
+}
+template <int L>
+__device__ __forceinline__ double row_lane(double x) {
+    return __hiloint2double(row_lane<L>(__double2hiint(x)), row_lane<L>(__double2loint(x)));
+}
+
 __device__ __forceinline__ int wave_scan(int x) {
     x = row_scan(x);
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // lane 15 of a row to rows 1 and 3
@@ -1747,13 +1761,8 @@ __global__ __launch_bounds__(BS) void k_forces_wide(Ctx C, Step A) {
             }
         q = min(q + 4, qe);
     }
-    int incl = found;  // accepted in this row and the ones before it
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-        const int y = __shfl_up(incl, o, 16);
-        if (a >= o) incl += y;
-    }
-    const int total = __shfl(incl, 15, 16);
+    const int incl = row_scan(found);  // accepted in this row and the ones before it
+    const int total = row_lane<15>(incl);
     const unsigned over = (unsigned)(__ballot(found > WIDE_ROW) >> gbase) & 0xFFFFu;
     if (over == 0u)
         for (int k = 0; k < found; ++k) list[p][incl - found + k] = rowq[p][a][k];
@@ -1780,7 +1789,7 @@ __global__ __launch_bounds__(BS) void k_forces_wide(Ctx C, Step A) {
             }
         }
     }
-    real fx = __shfl(acc0, 0, 16), fy = __shfl(acc0, 1, 16), fz = __shfl(acc0, 2, 16);
+    real fx = row_lane<0>(acc0), fy = row_lane<1>(acc0), fz = row_lane<2>(acc0);
     real wf[6] = {0, 0, 0, 0, 0, 0};
     if (act && own_id < B.n_beads)
         bond_forces<real>(C, b, own_id, (const V4*)C.sid[A.slot] + B.off, h00, h01, h10, h11, h22, fx, fy,
