@@ -238,7 +238,7 @@ typedef struct {
 } lhmm_micro_config;
 
 /* Set / read the launch parameters (defaults: depth 16, drain 12; busy rule
- * off; 512 binning threads; fused steps; two box groups; 50-step graphs; no pruning: with
+ * off; 512 binning threads; fused steps; one to three box groups by size; 50-step graphs; no pruning: with
  * cells barely wider than the cutoff it skips little and costs more).  Set waits for the
  * engine and drops its captured graphs.  Errors: ARG. */
 int lhmm_micro_set_config(lhmm_micro* m, const lhmm_micro_config* cfg);

@@ -61,6 +61,13 @@ constexpr int SREC_PAD = 4;             // padding records per column of the sea
 constexpr int MAX_CELLS_PER_BOX = 17424;
 constexpr int GRAPH_CHUNK = 50;         // default steps per captured graph
 constexpr int MAX_GROUPS = 4;           // overlapped box groups of a captured step
+// Default groups, by work blocks.  Below four blocks per CU the two launches
+// of a group leave each other little to overlap and split the chip's tail:
+// 166k particles with stress components 1290 us in one group, 1473 in two
+// (plain forces 1264 and 1263); 311k plain 1530 and 1457.  Three pay from about
+// 930k particles: 2984 us in two, 2836 in three (681k: 2360 and 2402).
+constexpr int GROUP2_BLOCKS = 1024;
+constexpr int GROUP3_BLOCKS = 3584;
 constexpr int MAX_WINDOW = 50;          // steps whose partial sums are kept before a flush
 constexpr size_t PART_BYTES = size_t(64) << 20;  // their memory, where more than one step would take more
 constexpr int ACC = 36;                 // per-box stress sums: kinetic, pair, FENE, C, D, R (6 each)
@@ -2403,9 +2410,9 @@ Lists fill_lists(const lhmm_micro* m, const int* boxes, int n_sel, int* out) {
 
 // Partition the boxes into G groups of about equal particle counts and mixed
 // sizes (largest first, each to the least loaded group), with their lists:
-// groups that take equally long overlap to the chunk's end (batch of 256, 20
-// steps: 4800 us; 5046 with the largest boxes, two thirds of the particles, in
-// one group, which ran alone after the other; one group 5240).
+// groups that take equally long overlap to the chunk's end (with the largest
+// boxes, two thirds of the particles, in one group, that one ran alone after
+// the other: batch of 256, 20 steps, 5046 us against 4800).
 int prepare_groups(lhmm_micro* m, int G) {
     HIPCHK(hipStreamSynchronize(m->stream));
     for (auto& gr : m->groups)
@@ -2532,7 +2539,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     m->cfg.graph_chunk = GRAPH_CHUNK;
     m->cfg.prune = 0;
     m->cfg.fuse_bin = 1;
-    m->cfg.groups = 2;
+    m->cfg.groups = 1;  // by size, below
     m->cfg.bin_split = 0;
     m->real_size = p->precision == LHMM_FP64 ? sizeof(double) : sizeof(float);
     m->user_stream = (hipStream_t)stream;
@@ -2720,6 +2727,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     C.inv_R02 = 1.0 / (p->R0 * p->R0);
     C.key0 = (unsigned)(p->seed & 0xFFFFFFFFull);
     C.key1 = (unsigned)(p->seed >> 32);
+    m->cfg.groups = m->n_blocks < GROUP2_BLOCKS ? 1 : (m->n_blocks < GROUP3_BLOCKS ? 2 : 3);
     rc = build_slabs(m);
     if (rc == LHMM_OK) rc = prepare_groups(m, m->cfg.groups);
     if (rc != LHMM_OK) {
