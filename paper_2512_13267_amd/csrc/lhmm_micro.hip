@@ -956,19 +956,27 @@ __global__ __launch_bounds__(T) void k_bin(Ctx C, Step A, int n_cell, int lds_ce
     const float inv_n2 = 1.0f / (float)n2;
     const int* key = C.key + B.off;
     int before = 0, img = 0;
-    for (int k0 = tid; k0 - tid < B.n; k0 += 4 * T) {  // four keys in flight
+    int next[4];  // the keys after the four at hand
+#pragma unroll
+    for (int u = 0; u < 4; ++u) next[u] = key[min(tid + u * T, B.n - 1)];
+    for (int k0 = tid; k0 - tid < B.n; k0 += 4 * T) {
         int cell[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) cell[u] = key[min(k0 + u * T, B.n - 1)];
+        for (int u = 0; u < 4; ++u) {
+            cell[u] = k0 + u * T < B.n ? next[u] : s1;
+            next[u] = key[min(k0 + (4 + u) * T, B.n - 1)];
+        }
         unsigned long long mine[4];
         int found = 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const bool on = k0 + u * T < B.n, early = on && cell[u] < s0;
-            const int z = cell[u] - div_small(cell[u], inv_n2) * n2;
-            before += __popcll(__ballot(early));
-            img += __popcll(__ballot(early && z < zs)) + __popcll(__ballot(early && z >= n2 - zs));
-            mine[u] = __ballot(on && cell[u] >= s0 && cell[u] < s1);
+            const unsigned long long early = __ballot(cell[u] < s0);
+            if (early) {  // the keys are nearly sorted: most waves have none, or only these
+                const int z = cell[u] - div_small(cell[u], inv_n2) * n2;
+                before += __popcll(early);
+                img += __popcll(early & __ballot(z < zs)) + __popcll(early & __ballot(z >= n2 - zs));
+            }
+            mine[u] = __ballot(cell[u] < s1) & ~early;
             found += __popcll(mine[u]);
         }
         if (found == 0) continue;  // wave-uniform
