@@ -897,9 +897,10 @@ __device__ __forceinline__ void block_scan(int n, int* wsum /* BT / 64 */, Val v
 // in the search layout, once more for the images of the bottom and top cells.
 //
 // One workgroup per box (the earlier form) took 19 us for 3000 particles,
-// 67 us for a batch with boxes of 1.5k to 12k and 160 us for 23k, which did
-// not fit its LDS; the largest box set the time.  See the table of the design
-// notes for the present times.
+// 67 us for a batch with boxes of 1.5k to 12k and 160 us for eight of 23k,
+// which did not fit its LDS; the largest box set the time.  Now 8.3, 31 and
+// 19 us: one chain of loads, scans and barriers for small launches, and for
+// large boxes the reading of all keys by every slab.
 //
 // A slab holding more than SLAB_CAP particles (a very uneven density) orders
 // its cells in global memory instead; the result is the same.
@@ -1613,7 +1614,10 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ?
 // the bit.  A workgroup takes the sixteen particles l = r + 4 j of a wave's 64
 // (r = 0 .. 3): their partial sums are a subtree of k_forces's wave sum.
 // Slower per particle (four particles per wave), so only for at most
-// WIDE_BLOCKS work blocks; the design notes have both kernels' times.
+// WIDE_BLOCKS work blocks.  FP32 boxes of 3072 particles, us a step with the
+// wide kernel and with k_forces: 12 blocks 18.9 and 41.3, 96 blocks 25.9 and
+// 36.3, 192 blocks 35.7 and 37.1, 252 blocks 41.5 and 40.8, 312 blocks 46.9
+// and 43.1.
 constexpr int WIDE_UNITS = 16;    // workgroups per work block
 constexpr int WIDE_BLOCKS = 256;  // largest launch, in work blocks
 constexpr int WIDE_ROW = 12;      // accepted neighbours per row that LDS holds
