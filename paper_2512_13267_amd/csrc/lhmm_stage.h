@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 
 struct HostStage {
     static constexpr size_t HALF = 512 * 1024;
@@ -27,6 +28,7 @@ struct HostStage {
     template <class Fill, class Take>
     hipError_t run(hipStream_t st, size_t total, Fill fill, Take take) {
         if (total == 0) return hipSuccess;
+        std::lock_guard<std::mutex> lock(busy);  // threads that read one engine take turns
         hipError_t e = reserve(total);
         for (size_t o = 0; e == hipSuccess && o < total + HALF; o += HALF) {
             if (o < total) {
@@ -116,6 +118,7 @@ struct HostStage {
 private:
     static size_t round16(size_t b) { return (b + 15) / 16 * 16; }
     char* half(size_t o) const { return host + o / HALF % 2 * HALF; }
+    std::mutex busy;
     char* host = nullptr;
     size_t cap = 0;
     hipEvent_t done[2] = {};
