@@ -630,7 +630,7 @@ struct lhmm_sph {
     hipStream_t stream = nullptr;
     double* d_sigma = nullptr;  // n x 6, micro stresses of the last interval (zero at start)
     double* d_gradL = nullptr;  // n x 9
-    void* bufs[16] = {};
+    void* arena = nullptr;  // every device array
     HostStage stage;
 };
 
@@ -638,8 +638,7 @@ namespace {
 
 void sph_release(lhmm_sph* s) {
     if (s->stream) (void)hipStreamSynchronize(s->stream);
-    for (void* b : s->bufs)
-        if (b) (void)hipFree(b);
+    if (s->arena) (void)hipFree(s->arena);
     s->stage.release();
 }
 
@@ -744,38 +743,46 @@ int lhmm_sph_create(const lhmm_sph_params* p, int32_t n, const double* r0, const
             S.tiles = (gy + S.rows - 1) / S.rows;
         }
     }
-    if (S.ncx > 0 && hipFuncSetAttribute((const void*)&k_tile, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS * 16384) != hipSuccess) {
+    // beyond 64 KiB with k_tile's static LDS (13 KiB)
+    if (S.ncx > 0 && TILE_LDS * n > 48 * 1024 &&
+        hipFuncSetAttribute((const void*)&k_tile, hipFuncAttributeMaxDynamicSharedMemorySize, TILE_LDS * 16384) != hipSuccess) {
         delete s;
         return lhmm_fail(LHMM_ERR_HIP, "cell tiles: LDS of 144 KiB refused");
     }
     const size_t m = (size_t)n;
     const size_t sizes[16] = {2 * m, 2 * m, m, m, 2 * m, 6 * m, 9 * m, (size_t)S.ncx * S.ncy + 1, m, m, 2 * m, 2 * m, m, m,
                               3 * m, m};
-    for (int k = 0; k < 16; ++k) {
-        if (hipMalloc(&s->bufs[k], sizes[k] * sizeof(double)) != hipSuccess) {
-            sph_release(s);
-            delete s;
-            return lhmm_fail(LHMM_ERR_OOM, "hipMalloc failed");
-        }
+    // one allocation, its arrays on 256-byte boundaries
+    size_t total = 0;
+    for (size_t k : sizes) total += (k * sizeof(double) + 255) / 256 * 256;
+    if (hipMalloc(&s->arena, total) != hipSuccess) {
+        sph_release(s);
+        delete s;
+        return lhmm_fail(LHMM_ERR_OOM, "hipMalloc failed");
     }
-    S.r = (double*)s->bufs[0];
-    S.v = (double*)s->bufs[1];
-    S.d = (double*)s->bufs[2];
-    S.p = (double*)s->bufs[3];
-    S.acc = (double*)s->bufs[4];
-    s->d_sigma = (double*)s->bufs[5];
-    s->d_gradL = (double*)s->bufs[6];
-    S.cstart = (int*)s->bufs[7];
-    S.cidx = (int*)s->bufs[8];
-    S.key = (unsigned*)s->bufs[9];
-    S.rs = (double2*)s->bufs[10];
-    S.vs = (double2*)s->bufs[11];
-    S.ids = (double*)s->bufs[12];
-    S.p2s = (double*)s->bufs[13];
-    S.s2s = (double*)s->bufs[14];
-    S.cell = (unsigned*)s->bufs[15];
+    void* bufs[16];
+    char* at = (char*)s->arena;
+    for (int k = 0; k < 16; ++k) {
+        bufs[k] = at;
+        at += (sizes[k] * sizeof(double) + 255) / 256 * 256;
+    }
+    S.r = (double*)bufs[0];
+    S.v = (double*)bufs[1];
+    S.d = (double*)bufs[2];
+    S.p = (double*)bufs[3];
+    S.acc = (double*)bufs[4];
+    s->d_sigma = (double*)bufs[5];
+    s->d_gradL = (double*)bufs[6];
+    S.cstart = (int*)bufs[7];
+    S.cidx = (int*)bufs[8];
+    S.key = (unsigned*)bufs[9];
+    S.rs = (double2*)bufs[10];
+    S.vs = (double2*)bufs[11];
+    S.ids = (double*)bufs[12];
+    S.p2s = (double*)bufs[13];
+    S.s2s = (double*)bufs[14];
+    S.cell = (unsigned*)bufs[15];
     auto init = [&]() -> int {
-        LHMM_HIPCHK(s->stage.reserve(15 * m * sizeof(double)));
         LHMM_HIPCHK(hipMemcpy(S.r, r0, 2 * (size_t)n * sizeof(double), hipMemcpyHostToDevice));
         LHMM_HIPCHK(hipMemcpy(S.v, v0, 2 * (size_t)n * sizeof(double), hipMemcpyHostToDevice));
         LHMM_HIPCHK(hipMemset(s->d_sigma, 0, 6 * (size_t)n * sizeof(double)));
@@ -783,7 +790,6 @@ int lhmm_sph_create(const lhmm_sph_params* p, int32_t n, const double* r0, const
         if (S.ncx > 0) {
             k_keys<<<(n + TPB - 1) / TPB, TPB, 0, s->stream>>>(S);
             LHMM_HIPCHK(hipGetLastError());
-            LHMM_HIPCHK(hipStreamSynchronize(s->stream));
         }
         return LHMM_OK;
     };

@@ -99,7 +99,7 @@ struct HostStage {
     }
 
     // Pinned memory for read-backs of `total` bytes; run() does it as well, an
-    // engine's create does it ahead of the first one.
+    // engine whose create takes much longer does it ahead of the first one.
     hipError_t reserve(size_t total) {
         const size_t need = std::min(round16(total), 2 * HALF);
         for (hipEvent_t& d : done) {
