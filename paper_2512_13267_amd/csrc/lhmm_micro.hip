@@ -1489,13 +1489,13 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ?
     // Up to SREC_PAD records past a range's end are the column's next z cells, at
     // least the cutoff away along z while zsub cells span it, or the column's
     // padding: they need no test of their own, and a lane whose range has ended
-    // stays at its end.  A box too flat for
-    // that (flagged) scans one record per iteration; a lane that scans nothing
-    // (no particle, a pruned row) tests from far away.
+    // stays at its end.  In a box too flat for that (flagged) they may lie within
+    // it: one record per iteration, none at the end of the range (it would be
+    // queued again for as long as another lane of the wave scans).  A lane that
+    // scans nothing (no particle, a pruned row) tests from far away.
     int row = 0;
     unsigned q = 0, qe = 0;
     const bool spans = D.h[8] * zs >= C.rc * n2;
-    const unsigned step = (spans ? SU : 1) * (unsigned)sizeof(V4);
     const real far = far_away<real>(C, D);
     auto set_range = [&]() {
         const int d0 = row / 3 - 1, d1 = row % 3 - 1;
@@ -1550,15 +1550,17 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ?
             // SU records per lane per iteration, all loads issued before the
             // first test, addressed by one 32-bit byte offset from the box's
             // records
-            V4 cand[SU];
+            if (__builtin_expect(spans, 1)) {
+                V4 cand[SU];
 #pragma unroll
-            for (int u = 0; u < SU; ++u) cand[u] = load_rec<real>(srsrc, sbase, q + u * (unsigned)sizeof(V4));
-            push(cand[0]);
-            if (spans) {
+                for (int u = 0; u < SU; ++u) cand[u] = load_rec<real>(srsrc, sbase, q + u * (unsigned)sizeof(V4));
 #pragma unroll
-                for (int u = 1; u < SU; ++u) push(cand[u]);
+                for (int u = 0; u < SU; ++u) push(cand[u]);
+                q = min(q + SU * (unsigned)sizeof(V4), qe);
+            } else if (q < qe) {
+                push(load_rec<real>(srsrc, sbase, q));
+                q += (unsigned)sizeof(V4);
             }
-            q = min(q + step, qe);
             // evaluate when a queue may not take SU more, or when enough
             // lanes hold a neighbour for a well-filled round
             if (__ballot(qt > qfull) != 0ull) break;
