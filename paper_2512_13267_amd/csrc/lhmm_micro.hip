@@ -52,6 +52,7 @@
 
 #include "lhmm.h"
 #include "lhmm_internal.h"
+#include "lhmm_grid.h"
 #include "lhmm_stage.h"
 
 namespace {
@@ -374,11 +375,6 @@ __host__ __device__ inline void m3_mul(const double* A, const double* B, double*
     for (int k = 0; k < 9; ++k) C[k] = T[k];
 }
 
-__host__ __device__ inline double m3_det(const double* A) {
-    return A[0] * (A[4] * A[8] - A[5] * A[7]) - A[1] * (A[3] * A[8] - A[5] * A[6]) +
-           A[2] * (A[3] * A[7] - A[4] * A[6]);
-}
-
 __host__ __device__ inline void m3_inv(const double* A, double* B) {
     const double id = 1.0 / m3_det(A);
     double T[9];
@@ -392,18 +388,6 @@ __host__ __device__ inline void m3_inv(const double* A, double* B) {
     T[7] = (A[1] * A[6] - A[0] * A[7]) * id;
     T[8] = (A[0] * A[4] - A[1] * A[3]) * id;
     for (int k = 0; k < 9; ++k) B[k] = T[k];
-}
-
-// perpendicular widths w_a = V / |h_b x h_c|
-__host__ __device__ inline void m3_widths(const double* h, double* w) {
-    const double V = fabs(m3_det(h));
-    for (int a = 0; a < 3; ++a) {
-        const int b = (a + 1) % 3, c = (a + 2) % 3;
-        const double ux = h[b], uy = h[3 + b], uz = h[6 + b];
-        const double vx = h[c], vy = h[3 + c], vz = h[6 + c];
-        const double x = uy * vz - uz * vy, y = uz * vx - ux * vz, z = ux * vy - uy * vx;
-        w[a] = V / sqrt(x * x + y * y + z * z);
-    }
 }
 
 // Is L finite, in-plane and traceless?
@@ -635,15 +619,8 @@ __device__ void cell_step_box(const Ctx& C, int b, const BoxDyn& S, BoxDyn& D, i
     double w[3];
     m3_widths(h, w);
     int nc[3];
-    bool narrow = false;
     const int zsub = C.box[b].zsub, zmin = 2 * zsub + 1;
-    for (int a = 0; a < 3; ++a) {
-        const int sub = a == 2 ? zsub : 1;
-        int n = (int)floor(sub * w[a] / C.rc);
-        if (!(w[a] >= 3.0 * C.rc)) narrow = true;
-        if (n < 2 * sub + 1) n = 2 * sub + 1;
-        nc[a] = n;
-    }
+    const bool narrow = cell_counts(w, C.rc, zsub, nc);
     const int cap = C.box[b].cell_cap;
     while ((long long)nc[0] * nc[1] * nc[2] > cap) {  // only reachable for a flagged (narrow) cell
         int a = nc[0] >= nc[1] ? 0 : 1;
@@ -1495,7 +1472,7 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ?
     // scans nothing (no particle, a pruned row) tests from far away.
     int row = 0;
     unsigned q = 0, qe = 0;
-    const bool spans = D.h[8] * zs >= C.rc * n2;
+    const bool spans = z_cells_span(D.h[8], zs, n2, C.rc);
     const real far = far_away<real>(C, D);
     auto set_range = [&]() {
         const int d0 = row / 3 - 1, d1 = row % 3 - 1;

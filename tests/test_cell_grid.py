@@ -1,0 +1,80 @@
+"""The cell-grid rules of the micro engine (csrc/lhmm_grid.h, host code of the
+same header): zsub cells along z span the cutoff in every deformed cell that
+is not flagged narrow, whatever the last digit of its edge (boxes of n
+particles at density 3 have edges of (n / 3)^(1/3), often an ulp below a whole
+number of cutoffs), and do not in a cell too flat for its stencil."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#define __host__
+#define __device__
+#include <cstdio>
+#include "lhmm_grid.h"
+int main() {
+    double h[9], rc;
+    int zsub;
+    while (scanf("%la %d", &rc, &zsub) == 2) {
+        for (double& x : h)
+            if (scanf("%la", &x) != 1) return 1;
+        double w[3];
+        int nc[3];
+        m3_widths(h, w);
+        const bool narrow = cell_counts(w, rc, zsub, nc);
+        printf("%d %d %d %d %d\n", nc[0], nc[1], nc[2], narrow, z_cells_span(h[8], zsub, nc[2], rc));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def grid(tmp_path_factory):
+    d = tmp_path_factory.mktemp("grid")
+    src, exe = d / "grid.cpp", d / "grid"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2512_13267_amd", "csrc"), "-o", str(exe),
+                    str(src)], check=True)
+
+    def run(cells):
+        text = "\n".join(" ".join([float(rc).hex(), str(z)] + [float(x).hex() for x in np.ravel(h)]) for rc, z, h in cells)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        return np.array([[int(x) for x in line.split()] for line in out.splitlines()])
+
+    return run
+
+
+def _sheared(rng, edge, hz):
+    """A cell of in-plane area edge^2, rotated and deformed."""
+    t, g, k = rng.uniform(0, 2 * np.pi), rng.uniform(-0.5, 0.5), rng.uniform(-0.3, 0.3)
+    R = np.array([[np.cos(t), -np.sin(t)], [np.sin(t), np.cos(t)]])
+    h = np.zeros((3, 3))
+    h[:2, :2] = R @ np.array([[np.exp(k), g], [0.0, np.exp(-k)]]) * edge
+    h[2, 2] = hz
+    return h
+
+
+@pytest.mark.parametrize("n", [192, 375, 648, 1029, 1536, 2187, 3000, 5184, 12288])
+@pytest.mark.parametrize("rc", [1.0, 0.7, 1.3])
+@pytest.mark.parametrize("zsub", [1, 2])
+def test_cells_span_the_cutoff_at_any_rounding_of_the_edge(grid, n, rc, zsub):
+    rng = np.random.default_rng(n)
+    edge = (n / 3.0) ** (1.0 / 3.0) * rc
+    cells = [(rc, zsub, _sheared(rng, edge, np.nextafter(edge, 0.0 if k % 3 == 0 else 9e9) if k % 3 else edge))
+             for k in range(3000)]
+    out = grid(cells)
+    assert len(out) == len(cells)
+    assert out[:, 4].all(), f"{(out[:, 4] == 0).sum()} of {len(out)} cells are taken for flat"
+    assert (np.abs(out[:, 2] - zsub * edge / rc) <= 1.0 + 1e-9).all()
+
+
+@pytest.mark.parametrize("zsub,hz,spans", [(2, 2.0, 0), (2, 2.49, 0), (2, 2.5, 1), (2, 2.75, 1), (1, 2.2, 0), (1, 2.99, 0),
+                                           (1, 3.0, 1), (2, 2.5 * (1 - 1e-9), 0)])
+def test_flat_cells_are_told_apart(grid, zsub, hz, spans):
+    rng = np.random.default_rng(7)
+    out = grid([(1.0, zsub, _sheared(rng, 9.0, hz)) for _ in range(300)])
+    assert (out[:, 4] == spans).all()
