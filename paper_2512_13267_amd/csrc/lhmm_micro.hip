@@ -526,18 +526,21 @@ __device__ __forceinline__ int xcd_local_work(int b, int n) {
 // and the rounding of the two-sided single-precision pair forces seeds it.
 // The micro-domain moves with its macro particle, so its mean is zero.  The
 // remaining workgroups, a thread per box, take the box's gradient (device
-// array n_boxes x 9), validate it, form exp(L dt) and exp(L dt/2), and clear
-// the call's sums.  One launch: the two parts touch different data.
+// array n_boxes x 9), validate it, form exp(L dt) and exp(L dt/2), and, where
+// steps follow (clear), zero the call's sums: a force evaluation leaves the last
+// step call's pair counts.  One launch: the two parts touch different data.
 constexpr int CALL_THREADS = 1024;
 
 template <typename real>
-__global__ __launch_bounds__(CALL_THREADS) void k_begin_call(Ctx C, const double* __restrict__ gradL, int n_mean) {
+__global__ __launch_bounds__(CALL_THREADS) void k_begin_call(Ctx C, const double* __restrict__ gradL, int n_mean,
+                                                             int clear) {
     if ((int)blockIdx.x >= n_mean) {
         const int b = (blockIdx.x - n_mean) * 64 + threadIdx.x / 16, sub = threadIdx.x % 16;
         if (b >= C.n_boxes) return;
-        for (int q = sub; q < ACC; q += 16) C.acc[ACC * (size_t)b + q] = 0.0;
+        if (clear)
+            for (int q = sub; q < ACC; q += 16) C.acc[ACC * (size_t)b + q] = 0.0;
         if (sub != 0) return;
-        C.acc_pairs[b] = 0ull;
+        if (clear) C.acc_pairs[b] = 0ull;
         BoxDyn& D = C.dyn[b];
         double L[9];
         for (int k = 0; k < 9; ++k) L[k] = gradL[9 * (size_t)b + k];
@@ -2198,12 +2201,12 @@ void launch_force_eval(lhmm_micro* m) {
         launch_force_eval_t<float>(m);
 }
 
-void launch_begin_call(lhmm_micro* m, const Ctx& C, int n_mean, const double* gradL) {
+void launch_begin_call(lhmm_micro* m, const Ctx& C, int n_mean, const double* gradL, int clear = 1) {
     const int grid = n_mean + (m->n_boxes + 63) / 64;
     if (m->precision == LHMM_FP64)
-        k_begin_call<double><<<grid, CALL_THREADS, 0, m->stream>>>(C, gradL, n_mean);
+        k_begin_call<double><<<grid, CALL_THREADS, 0, m->stream>>>(C, gradL, n_mean, clear);
     else
-        k_begin_call<float><<<grid, CALL_THREADS, 0, m->stream>>>(C, gradL, n_mean);
+        k_begin_call<float><<<grid, CALL_THREADS, 0, m->stream>>>(C, gradL, n_mean, clear);
 }
 
 int get_graph(lhmm_micro* m, int nsteps, hipGraphExec_t* out) {
@@ -3194,7 +3197,7 @@ int lhmm_micro_forces(lhmm_micro* m, const double* gradL, double* f_out, double*
     int rc = sync_engine(m);
     if (rc != LHMM_OK) return rc;
     HIPCHK(hipMemcpy(m->d_gradL, gradL, 9 * m->n_boxes * sizeof(double), hipMemcpyHostToDevice));
-    launch_begin_call(m, m->ctx, 0, m->d_gradL);  // gradients only: the velocities keep their mean
+    launch_begin_call(m, m->ctx, 0, m->d_gradL, 0);  // gradients only: velocities keep their mean, sums stay
     launch_force_eval(m);
     HIPCHK(hipGetLastError());
     rc = sync_engine(m);
