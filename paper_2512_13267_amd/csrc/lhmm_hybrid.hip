@@ -340,8 +340,8 @@ int lhmm_hybrid_mean_stress(lhmm_hybrid* h, double* sigma_mean, int32_t reset) {
     lhmm_clear_error();
     if (!h) return lhmm_fail(LHMM_ERR_ARG, "null argument");
     const size_t n6 = 6 * (size_t)h->n;
+    LHMM_HIPCHK(h->stage.copy(h->stream, {{h->sigma_sum, n6 * sizeof(double)}}, {sigma_mean}));
     if (sigma_mean) {
-        LHMM_HIPCHK(h->stage.copy(h->stream, {{h->sigma_sum, n6 * sizeof(double)}}, {sigma_mean}));
         const double w = h->n_sum > 0 ? 1.0 / (double)h->n_sum : 0.0;
         for (size_t i = 0; i < n6; ++i) sigma_mean[i] *= w;
     }

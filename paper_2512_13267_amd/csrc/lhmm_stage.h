@@ -24,10 +24,11 @@ struct HostStage {
 
     // fill(offset, bytes, pinned) enqueues the bytes [offset, offset + bytes)
     // of `total` on the stream, take(offset, bytes, pinned) receives them;
-    // offsets are multiples of 16.
+    // offsets are multiples of 16.  The work on the stream before it has ended
+    // when it returns, also where there is nothing to read.
     template <class Fill, class Take>
     hipError_t run(hipStream_t st, size_t total, Fill fill, Take take) {
-        if (total == 0) return hipSuccess;
+        if (total == 0) return hipStreamSynchronize(st);
         std::lock_guard<std::mutex> lock(busy);  // threads that read one engine take turns
         hipError_t e = reserve(total);
         for (size_t o = 0; e == hipSuccess && o < total + HALF; o += HALF) {

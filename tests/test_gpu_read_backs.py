@@ -31,3 +31,42 @@ def test_a_force_evaluation_leaves_the_last_calls_pair_counts(n, boxes):
     assert np.array_equal(m.pair_counts(), counts)
     assert np.array_equal(m.pair_total(), total)
     m.close()
+
+
+def test_a_read_of_nothing_waits_for_the_engine():
+    """The reads are synchronous also where every destination is null."""
+    _gpu()
+    from paper_2512_13267_amd import _lib, inputs, lhmm, micro
+
+    L = _lib.lib()
+    mac = inputs.cylinder_array(n=16, force=2.0)
+    nm = mac.r.shape[0] - mac.params["n_fixed"]
+    m = micro.from_workload(inputs.lhmm_boxes(nm, n_particles=300, polymer_fraction=0.0, seed_k=3))
+    G = torch.zeros((nm, 9), dtype=torch.float64, device="cuda")
+    m.step(G, 2)
+    s = lhmm.Sph(mac.params, mac.r, mac.v)
+    h = lhmm.Hybrid(s, m, mode="dpd", k_micro=2)
+    on = np.zeros(nm, dtype=np.uint32)
+    reads = {
+        "sph_get_state": lambda: L.lhmm_sph_get_state(s._h, None, None, None),
+        "sph_coupling_state": lambda: L.lhmm_sph_coupling_state(s._h, None, None),
+        "hybrid_state": lambda: L.lhmm_hybrid_state(h._h, None, on.ctypes.data_as(C.POINTER(C.c_uint32))),
+        "hybrid_mean_stress": lambda: L.lhmm_hybrid_mean_stress(h._h, None, 0),
+        "micro_get_state": lambda: L.lhmm_micro_get_state(m._h, None, None, None, None, None),
+    }
+    x = torch.randn((8192, 8192), device="cuda")
+    y = x @ x
+    torch.cuda.synchronize()
+    for name, read in reads.items():
+        print(f"read of nothing: {name}", flush=True)
+        for _ in range(8):  # some 10 ms each
+            torch.mm(x, x, out=y)
+        done = torch.cuda.Event()
+        done.record()
+        m.step(G, 1)  # the micro engine's stream follows the caller's
+        assert read() == 0
+        assert done.query(), name
+        torch.cuda.synchronize()
+    h.close()
+    s.close()
+    m.close()
