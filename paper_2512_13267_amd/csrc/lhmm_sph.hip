@@ -783,6 +783,7 @@ int lhmm_sph_create(const lhmm_sph_params* p, int32_t n, const double* r0, const
     S.s2s = (double*)bufs[14];
     S.cell = (unsigned*)bufs[15];
     auto init = [&]() -> int {
+        LHMM_HIPCHK(s->stage.reserve(0));
         LHMM_HIPCHK(hipMemcpy(S.r, r0, 2 * (size_t)n * sizeof(double), hipMemcpyHostToDevice));
         LHMM_HIPCHK(hipMemcpy(S.v, v0, 2 * (size_t)n * sizeof(double), hipMemcpyHostToDevice));
         LHMM_HIPCHK(hipMemset(s->d_sigma, 0, 6 * (size_t)n * sizeof(double)));

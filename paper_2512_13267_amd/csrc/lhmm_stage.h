@@ -25,12 +25,16 @@ struct HostStage {
     // fill(offset, bytes, pinned) enqueues the bytes [offset, offset + bytes)
     // of `total` on the stream, take(offset, bytes, pinned) receives them;
     // offsets are multiples of 16.  The work on the stream before it has ended
-    // when it returns, also where there is nothing to read.
+    // when it returns, also where there is nothing to read.  Runs with the
+    // engine's device current, whatever the caller's: the events belong to it,
+    // and so do a null stream and what fill launches.
     template <class Fill, class Take>
     hipError_t run(hipStream_t st, size_t total, Fill fill, Take take) {
+        const OnDevice here(device);
+        if (here.error != hipSuccess) return here.error;
         if (total == 0) return hipStreamSynchronize(st);
         std::lock_guard<std::mutex> lock(busy);  // threads that read one engine take turns
-        hipError_t e = reserve(total);
+        hipError_t e = grow(total);
         for (size_t o = 0; e == hipSuccess && o < total + HALF; o += HALF) {
             if (o < total) {
                 e = fill(o, std::min(HALF, total - o), half(o));
@@ -99,9 +103,35 @@ struct HostStage {
         cap = 0;
     }
 
-    // Pinned memory for read-backs of `total` bytes; run() does it as well, an
-    // engine whose create takes much longer does it ahead of the first one.
+    // Called once by an engine's create, with its device current.  Pinned memory
+    // for read-backs of `total` bytes (0: with the first one, where the
+    // allocation would be most of a short create); run() grows it where needed.
     hipError_t reserve(size_t total) {
+        const hipError_t e = hipGetDevice(&device);
+        return e == hipSuccess ? grow(total) : e;
+    }
+
+private:
+    // makes a device current, and the caller's again at the end
+    struct OnDevice {
+        hipError_t error;
+        int before = -1;
+        explicit OnDevice(int device) {
+            error = hipGetDevice(&before);
+            if (error != hipSuccess || before == device) {
+                before = -1;
+            } else {
+                error = hipSetDevice(device);
+            }
+        }
+        ~OnDevice() {
+            if (before >= 0) (void)hipSetDevice(before);
+        }
+        OnDevice(const OnDevice&) = delete;
+        OnDevice& operator=(const OnDevice&) = delete;
+    };
+
+    hipError_t grow(size_t total) {
         const size_t need = std::min(round16(total), 2 * HALF);
         for (hipEvent_t& d : done) {
             const hipError_t e = d ? hipSuccess : hipEventCreateWithFlags(&d, hipEventDisableTiming);
@@ -116,10 +146,10 @@ struct HostStage {
         return e;
     }
 
-private:
     static size_t round16(size_t b) { return (b + 15) / 16 * 16; }
     char* half(size_t o) const { return host + o / HALF % 2 * HALF; }
     std::mutex busy;
+    int device = 0;
     char* host = nullptr;
     size_t cap = 0;
     hipEvent_t done[2] = {};
