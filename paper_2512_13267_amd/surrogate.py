@@ -30,17 +30,13 @@ def pack(members, n_in, n_hidden, n_out) -> np.ndarray:
 
 
 def unpack(flat: np.ndarray, n_members, n_in, n_hidden, n_out):
-    return [{k: x.copy() for k, x in m.items()} for m in _views(flat, n_members, n_in, n_hidden, n_out)]
-
-
-def _views(flat, n_members, n_in, n_hidden, n_out):
     shapes = layer_shapes(n_in, n_hidden, n_out)
     out, o = [], 0
     for _ in range(n_members):
         m = {}
         for k in LAYERS:
             n = int(np.prod(shapes[k]))
-            m[k] = flat[o:o + n].reshape(shapes[k])
+            m[k] = flat[o:o + n].reshape(shapes[k]).copy()
             o += n
         out.append(m)
     return out
@@ -93,14 +89,14 @@ class Surrogate:
         n = self.E * sum(int(np.prod(s)) for s in layer_shapes(self.n_in, self.n_hidden, self.n_out).values())
         w = np.empty(n, dtype=np.float32)
         check(lib().lhmm_sur_get_weights(self._h, _fptr(w)))
-        return _views(w, self.E, self.n_in, self.n_hidden, self.n_out)
+        return unpack(w, self.E, self.n_in, self.n_hidden, self.n_out)
 
     def get_grads(self):
         """Gradients of the last train_step (per-member dicts, FP32)."""
         n = self.E * sum(int(np.prod(s)) for s in layer_shapes(self.n_in, self.n_hidden, self.n_out).values())
         g = np.empty(n, dtype=np.float32)
         check(lib().lhmm_sur_get_grads(self._h, _fptr(g)))
-        return _views(g, self.E, self.n_in, self.n_hidden, self.n_out)
+        return unpack(g, self.E, self.n_in, self.n_hidden, self.n_out)
 
     def train_step(self, X, T, lr, loss=None):
         """One Adam step of every member on (X, T); loss: optional cuda float32

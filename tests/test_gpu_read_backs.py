@@ -70,3 +70,19 @@ def test_a_read_of_nothing_waits_for_the_engine():
     h.close()
     s.close()
     m.close()
+
+
+def test_weights_and_gradients_are_arrays_of_their_own():
+    """Each tensor that get_weights and get_grads return can be kept, resized
+    or dropped without the others."""
+    _gpu()
+    from paper_2512_13267_amd import surrogate
+
+    E, nin, nh, nout = 2, 33, 64, 3
+    s = surrogate.Surrogate(surrogate.init_members(E, nin, nh, nout, seed=2), nin, nh, nout, max_batch=8)
+    s.train_step(torch.randn((8, nin), device="cuda"), torch.randn((8, nout), device="cuda"), 1e-3)
+    for members in (s.get_weights(), s.get_grads()):
+        for m in members:
+            for k, x in m.items():
+                assert x.base is None and x.flags.owndata and x.flags.c_contiguous, k
+    s.close()
