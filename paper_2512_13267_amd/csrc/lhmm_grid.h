@@ -1,8 +1,9 @@
-// lhmm_grid.h -- the cell grid of a micro-box (not part of the public ABI):
-// plain FP64 arithmetic that the kernels and host code share.
+// lhmm_grid.h -- the cell grids of micro-boxes and of the macro problem (not
+// part of the public ABI): plain host arithmetic, in part shared with the kernels.
 #ifndef LHMM_GRID_H
 #define LHMM_GRID_H
 
+#include <algorithm>
 #include <cmath>
 
 __host__ __device__ inline double m3_det(const double* A) {
@@ -47,6 +48,33 @@ __host__ __device__ inline bool cell_counts(const double* w, double rc, int zsub
 // A pair 1e-12 short of the cutoff has a weight of 1e-12.
 __host__ __device__ inline bool z_cells_span(double hz, int zsub, int n2, double rc) {
     return hz * zsub >= rc * n2 * (1.0 - 1e-12);
+}
+
+// Tiles of the macro problem's gx x gy cells: `rows` cells of a column and the
+// ring around them, a workgroup each.  About as many as CUs; a tile holds 64
+// cells with its ring at most (19 rows), and covers each of a column's cells at
+// most once with it, so the largest grids have up to 1060.  Columns run along y,
+// or along x (turned) where a long grid would have more columns than CUs: each
+// workgroup reads all particles' cells, and of 5000 x 3 cells it takes 15000 in
+// columns along y (308 us a step of 1300 particles) and 792 along x (45 us).
+constexpr int TILES = 256;
+constexpr int TILE_CELLS = 64;
+
+struct CellTiles {
+    bool turned;     // cell columns run along x
+    int ncol, nrow;  // columns, cells of a column
+    int rows, tiles; // cells of a column per tile, tiles per column
+};
+
+inline CellTiles cell_tiles(int gx, int gy) {
+    CellTiles t;
+    t.turned = gx > TILES && gx > gy;
+    t.ncol = t.turned ? gy : gx;
+    t.nrow = t.turned ? gx : gy;
+    const int per_column = std::max(1, TILES / t.ncol);
+    t.rows = std::min({(t.nrow + per_column - 1) / per_column, t.nrow - 2, TILE_CELLS / 3 - 2});
+    t.tiles = (t.nrow + t.rows - 1) / t.rows;
+    return t;
 }
 
 #endif

@@ -25,6 +25,7 @@
 
 #include "lhmm.h"
 #include "lhmm_internal.h"
+#include "lhmm_grid.h"
 #include "lhmm_stage.h"
 
 namespace {
@@ -65,10 +66,11 @@ struct SphCtx {
     int n, n_mobile, force_mode;  // particles n_mobile .. n-1 are frozen walls
     int kernel;                   // LHMM_KERNEL_QUINTIC or LHMM_KERNEL_LUCY
     int micro_dim;                // 3: micro-domains are 3-D boxes; 2: planar cells (no zz stress)
-    int ncx, ncy;                 // cell grid (0: all pairs)
+    int ncx, ncy;                 // cell columns and cells of a column (0: all pairs)
+    int turned;                   // columns run along x instead of y
     int rows, tiles;              // cells of a column per tile, tiles per column (k_tile)
     int* cstart;                  // ncx * ncy + 1 cell offsets
-    unsigned* key;                // each particle's cell, x << 16 | y
+    unsigned* key;                // each particle's cell, column << 16 | row
     // in cell order: particle indices, cells, positions, velocities, 1 / d of
     // the density d, and over d^2 the pressure p and the polymer stress (xx,
     // xy, yy; 0 for walls): what a neighbour brings to a force sum
@@ -138,14 +140,13 @@ __device__ __forceinline__ void min_image(const SphCtx& S, double& dx, double& d
     dy = min_image(dy, S.Ly);
 }
 
-__device__ __forceinline__ int cell_x(const SphCtx& S, double x) {
-    return min(max((int)(x * (double)S.ncx / S.Lx), 0), S.ncx - 1);
-}
-__device__ __forceinline__ int cell_y(const SphCtx& S, double y) {
-    return min(max((int)(y * (double)S.ncy / S.Ly), 0), S.ncy - 1);
+__device__ __forceinline__ int cell_along(double x, int n, double L) {
+    return min(max((int)(x * (double)n / L), 0), n - 1);
 }
 __device__ __forceinline__ unsigned cell_key(const SphCtx& S, double x, double y) {
-    return ((unsigned)cell_x(S, x) << 16) | (unsigned)cell_y(S, y);
+    const unsigned ix = (unsigned)cell_along(x, S.turned ? S.ncy : S.ncx, S.Lx);
+    const unsigned iy = (unsigned)cell_along(y, S.turned ? S.ncx : S.ncy, S.Ly);
+    return S.turned ? (iy << 16) | ix : (ix << 16) | iy;
 }
 
 // Tait pressure of the number density d, with the background pressure
@@ -332,8 +333,8 @@ __global__ __launch_bounds__(TPB) void k_gradL(SphCtx S, double* __restrict__ gr
     store_gradient(S, g, lane, gradL + 9 * I);
 }
 
-// With cells: one workgroup per tile of `rows` cells of a column, as many
-// tiles as the chip has CUs at most.  Every workgroup reads all particles'
+// With cells: one workgroup per tile of `rows` cells of a column (cell_tiles:
+// about as many as the chip has CUs).  Every workgroup reads all particles'
 // cells (4 bytes each), counting those before its tile and collecting those in
 // the 3 x (rows + 2) cells around it, so it needs nothing from another one.
 // It sorts what it collected by cell and index and sums the densities of its
@@ -344,8 +345,6 @@ __global__ __launch_bounds__(TPB) void k_gradL(SphCtx S, double* __restrict__ gr
 // by one as they are collected 10.4 us, the records written by each density
 // wave 10.4 us, sums through ds_bpermute in place of wave_sum's 9.5 us.
 constexpr int TILE_THREADS = 1024;
-constexpr int TILES = 256;
-constexpr int TILE_CELLS = 64;        // cells around a tile at most
 constexpr int TILE_POSITIONS = 512;  // collected positions, own densities held in LDS; beyond, read again
 
 // dynamic LDS of k_tile: the collected particles grouped by cell (index << 16
@@ -733,14 +732,13 @@ int lhmm_sph_create(const lhmm_sph_params* p, int32_t n, const double* r0, const
     {
         const int gx = (int)std::floor(p->Lx / p->h), gy = (int)std::floor(p->Ly / p->h);
         const bool fits = gx >= 3 && gy >= 3 && (long long)gx * gy + n <= (65536 - 64) / 4;
-        S.ncx = fits ? gx : 0;
-        S.ncy = fits ? gy : 0;
         if (fits) {
-            // as many tiles as CUs at most; with its two rows around it, a tile
-            // covers each of a column's cells at most once
-            const int per_column = std::max(1, TILES / gx);
-            S.rows = std::min({(gy + per_column - 1) / per_column, gy - 2, TILE_CELLS / 3 - 2});
-            S.tiles = (gy + S.rows - 1) / S.rows;
+            const CellTiles tiles = cell_tiles(gx, gy);
+            S.turned = tiles.turned;
+            S.ncx = tiles.ncol;
+            S.ncy = tiles.nrow;
+            S.rows = tiles.rows;
+            S.tiles = tiles.tiles;
         }
     }
     // beyond 64 KiB with k_tile's static LDS (13 KiB)

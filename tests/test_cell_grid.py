@@ -1,8 +1,11 @@
-"""The cell-grid rules of the micro engine (csrc/lhmm_grid.h, host code of the
-same header): zsub cells along z span the cutoff in every deformed cell that
-is not flagged narrow, whatever the last digit of its edge (boxes of n
-particles at density 3 have edges of (n / 3)^(1/3), often an ulp below a whole
-number of cutoffs), and do not in a cell too flat for its stencil."""
+"""The cell-grid rules (csrc/lhmm_grid.h, compiled for the host).  Micro-boxes:
+zsub cells along z span the cutoff in every deformed cell that is not flagged
+narrow, whatever the last digit of its edge (boxes of n particles at density 3
+have edges of (n / 3)^(1/3), often an ulp below a whole number of cutoffs), and
+do not in a cell too flat for its stencil.  Macro problem: the tiles of every
+grid that is accepted cover its columns once, fit their workgroup, and are few
+(every workgroup reads all particles' cells): at most 256 columns of tiles of
+19 rows, each column with a rest, 256 + 16368 / 19."""
 import os
 import subprocess
 
@@ -16,7 +19,25 @@ PROGRAM = r"""
 #define __device__
 #include <cstdio>
 #include "lhmm_grid.h"
-int main() {
+// every macro grid of up to 16368 cells: 1 where a rule is broken
+int tiles() {
+    int most = 0;
+    for (int gx = 3; gx <= 5456; ++gx)
+        for (int gy = 3; gx * gy <= 16368; ++gy) {
+            const CellTiles t = cell_tiles(gx, gy);
+            const bool cells = t.turned ? t.ncol == gy && t.nrow == gx : t.ncol == gx && t.nrow == gy;
+            const bool cover = t.rows >= 1 && t.tiles * t.rows >= t.nrow && (t.tiles - 1) * t.rows < t.nrow;
+            if (!cells || !cover || t.rows + 2 > t.nrow || 3 * (t.rows + 2) > TILE_CELLS) {
+                printf("%d x %d\n", gx, gy);
+                return 1;
+            }
+            most = std::max(most, t.tiles * t.ncol);
+        }
+    printf("%d\n", most);
+    return 0;
+}
+int main(int argc, char**) {
+    if (argc > 1) return tiles();
     double h[9], rc;
     int zsub;
     while (scanf("%la %d", &rc, &zsub) == 2) {
@@ -41,6 +62,8 @@ def grid(tmp_path_factory):
                     str(src)], check=True)
 
     def run(cells):
+        if cells is None:
+            return subprocess.run([str(exe), "tiles"], capture_output=True, text=True)
         text = "\n".join(" ".join([float(rc).hex(), str(z)] + [float(x).hex() for x in np.ravel(h)]) for rc, z, h in cells)
         out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
         return np.array([[int(x) for x in line.split()] for line in out.splitlines()])
@@ -78,3 +101,9 @@ def test_flat_cells_are_told_apart(grid, zsub, hz, spans):
     rng = np.random.default_rng(7)
     out = grid([(1.0, zsub, _sheared(rng, 9.0, hz)) for _ in range(300)])
     assert (out[:, 4] == spans).all()
+
+
+def test_tiles_of_every_macro_grid(grid):
+    res = grid(None)
+    assert res.returncode == 0, res.stdout
+    assert int(res.stdout) <= 256 + 16368 // 19
