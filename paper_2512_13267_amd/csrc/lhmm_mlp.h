@@ -58,15 +58,16 @@ struct MlpArgs {
     float* ploss;              // E x Bp / 8: squared errors of eight rows
 };
 
-inline size_t mlp_lds_bytes(int nin_p, int nh) {
-    return sizeof(bf16) * 32 * ((size_t)(nin_p + MLP_PAD) + 2 * (size_t)(nh + MLP_PAD) + 32 + MLP_PAD);
+// features in LDS at a time: xcols
+inline size_t mlp_lds_bytes(int xcols, int nh) {
+    return sizeof(bf16) * 32 * ((size_t)(xcols + MLP_PAD) + 2 * (size_t)(nh + MLP_PAD) + 32 + MLP_PAD);
 }
 
 // Weight fragments in flight per wave, so that a product of 16 k-steps does
 // not wait for L2 at every step.  Inference: 4 (14.3 us for 217 rows, 8 take
 // 15.5: the registers hold fewer waves).  Training keeps GELU' in registers
 // and has two workgroups per CU either way: 8 (64 us for 5 x 4096 rows, 4 take 67).
-constexpr int mlp_pf(bool train) { return train ? 8 : 4; }
+constexpr int mlp_pf(bool train, bool wide) { return train || wide ? 8 : 4; }
 
 template <int PF>
 __device__ __forceinline__ void mlp_preload(bf16x8 (&b)[PF], const bf16* w, int KS, int l) {
@@ -108,10 +109,21 @@ __device__ __forceinline__ void mlp_store_t(bf16* base, int t, int KSB, int R0, 
 // of the 22.6 us) on the 2 or 3 workgroups that share a CU, and in training by
 // 85 MB of transposed operands and FP32 dZ written as well.  GELU' parked in
 // memory instead of registers (three workgroups per CU) took 73 us.
-template <bool TRAIN, int NTW>
+//
+// WIDE (inference, more than MLP_XCOLS features): the features pass through LDS
+// MLP_XCOLS at a time, the next ones on their way while these are multiplied, in
+// the same order.  With all of them in LDS a CU held one workgroup, whose loads
+// waited for one another: 5 x 12000 rows of 1250-128-128-3 193 us layer by
+// layer, 390 with all features in LDS, 106 in pieces; 1700-32-32-3 113, 490 and
+// 112.  Narrow layers gain least (seven of eight waves only load): 400-32-32-3
+// 44, 47 and 53 us, 1000-32-32-3 75, 165 and 83.
+constexpr int MLP_XCOLS = 320;
+
+template <bool TRAIN, int NTW, bool WIDE>
 __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
+    static_assert(!(TRAIN && WIDE), "training reads all features again");
     extern __shared__ __align__(16) unsigned char mlp_lds[];
-    const int ldx = g.nin_p + MLP_PAD, ldh = g.nh + MLP_PAD, ldy = 32 + MLP_PAD;
+    const int ldx = (WIDE ? MLP_XCOLS : g.nin_p) + MLP_PAD, ldh = g.nh + MLP_PAD, ldy = 32 + MLP_PAD;
     bf16* Xs = (bf16*)mlp_lds;
     bf16* Ha = Xs + 32 * ldx;
     bf16* Hb = Ha + 32 * ldh;
@@ -122,13 +134,47 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
     const bf16* W1 = g.W1f + (size_t)e * g.nin_p * g.nh;
     const bf16* W2 = g.W2f + (size_t)e * g.nh * g.nh;
     const bf16* W3 = g.W3f + (size_t)e * 32 * g.nh;
-    bf16x8 b[mlp_pf(TRAIN)];
-    if (wv < nt) mlp_preload(b, W1 + (size_t)wv * KS1 * 512, KS1, l);
-    // the rows, rounded to BF16; rows and columns of the padding are zero
-    for (int r = wv; r < 32; r += MLP_WAVES)
-        for (int c = l; c < g.nin_p; c += 64)
-            Xs[r * ldx + c] = (bf16)((R0 + r < g.B && c < g.nin) ? g.X[(size_t)(R0 + r) * g.nin + c] : 0.0f);
-    __syncthreads();
+    bf16x8 b[mlp_pf(TRAIN, WIDE)];
+    floatx16 acc1[NTW] = {};  // WIDE: the first layer's products
+    if constexpr (WIDE) {
+        float x[4][MLP_XCOLS / 64];  // rows wv, wv + 8, ..
+        auto load = [&](int c0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int k = 0; k < MLP_XCOLS / 64; ++k) {
+                    const int r = wv + MLP_WAVES * q, c = c0 + 64 * k + l;
+                    x[q][k] = (R0 + r < g.B && c < g.nin) ? g.X[(size_t)(R0 + r) * g.nin + c] : 0.0f;
+                }
+        };
+        auto ksteps = [&](int c0) { return min(MLP_XCOLS, g.nin_p - c0) / 16; };
+        auto weights = [&](int j, int c0) { return W1 + ((size_t)(wv + MLP_WAVES * j) * KS1 + c0 / 16) * 512; };
+        load(0);
+        if (wv < nt) mlp_preload(b, weights(0, 0), ksteps(0), l);
+        for (int c0 = 0; c0 < g.nin_p; c0 += MLP_XCOLS) {
+            if (c0 > 0) __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int k = 0; k < MLP_XCOLS / 64; ++k) Xs[(wv + MLP_WAVES * q) * ldx + 64 * k + l] = (bf16)x[q][k];
+            __syncthreads();
+            if (c0 + MLP_XCOLS < g.nin_p) load(c0 + MLP_XCOLS);
+#pragma unroll
+            for (int j = 0; j < NTW; ++j)
+                if (wv + MLP_WAVES * j < nt) {
+                    if (j > 0) mlp_preload(b, weights(j, c0), ksteps(c0), l);
+                    mlp_tile(acc1[j], b, Xs, ldx, weights(j, c0), ksteps(c0), l);
+                }
+            if (wv < nt && c0 + MLP_XCOLS < g.nin_p) mlp_preload(b, weights(0, c0 + MLP_XCOLS), ksteps(c0 + MLP_XCOLS), l);
+        }
+    } else {
+        if (wv < nt) mlp_preload(b, W1 + (size_t)wv * KS1 * 512, KS1, l);
+        // the rows, rounded to BF16; rows and columns of the padding are zero
+        for (int r = wv; r < 32; r += MLP_WAVES)
+            for (int c = l; c < g.nin_p; c += 64)
+                Xs[r * ldx + c] = (bf16)((R0 + r < g.B && c < g.nin) ? g.X[(size_t)(R0 + r) * g.nin + c] : 0.0f);
+        __syncthreads();
+    }
     if (TRAIN && e == 0) {  // X as the weight gradient reads it, once for all members
         for (int q = tid; q < 4 * g.nin_p; q += 64 * MLP_WAVES) {
             const int c = q >> 2, s = q & 3;  // feature, group of eight rows
@@ -139,16 +185,21 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
         }
     }
     floatx16 d1[TRAIN ? NTW : 1], d2[TRAIN ? NTW : 1];  // GELU'(Z1), GELU'(Z2) of the wave's tiles
-    // one hidden layer: As -> Hs (and, training, its transpose and derivative)
+    // one hidden layer: As -> Hs (and, training, its transpose and derivative);
+    // done: its products, where they are there already
     auto hidden = [&](const bf16* As, int lda, const bf16* W, int KS, const float* bias, bf16* Hs, bf16* Ht,
-                      floatx16* d, const bf16* Wnext, int KSn, int ntn) {
+                      floatx16* d, const bf16* Wnext, int KSn, int ntn, const floatx16* done) {
 #pragma unroll
         for (int j = 0; j < NTW; ++j) {
             const int t = wv + MLP_WAVES * j;
             if (t < nt) {
                 floatx16 acc{};
-                if (j > 0) mlp_preload(b, W + (size_t)t * KS * 512, KS, l);
-                mlp_tile(acc, b, As, lda, W + (size_t)t * KS * 512, KS, l);
+                if (done) {
+                    acc = done[j];
+                } else {
+                    if (j > 0) mlp_preload(b, W + (size_t)t * KS * 512, KS, l);
+                    mlp_tile(acc, b, As, lda, W + (size_t)t * KS * 512, KS, l);
+                }
                 // the next product's first fragments travel during the GELU
                 if (j + 1 == NTW || t + MLP_WAVES >= nt)
                     if (wv < ntn) mlp_preload(b, Wnext + (size_t)wv * KSn * 512, KSn, l);
@@ -174,8 +225,8 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
         }
         __syncthreads();
     };
-    hidden(Xs, ldx, W1, KS1, g.b1, Ha, g.H1t, d1, W2, KSH, nt);
-    hidden(Ha, ldh, W2, KSH, g.b2, Hb, g.H2t, d2, W3, KSH, 1);
+    hidden(Xs, ldx, W1, KS1, g.b1, Ha, g.H1t, d1, W2, KSH, nt, WIDE ? acc1 : nullptr);
+    hidden(Ha, ldh, W2, KSH, g.b2, Hb, g.H2t, d2, W3, KSH, 1, nullptr);
     if (wv == 0) {
         floatx16 acc{};
         mlp_tile(acc, b, Hb, ldh, W3, KSH, l);

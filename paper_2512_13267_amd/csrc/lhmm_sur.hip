@@ -578,11 +578,21 @@ long szW3(const lhmm_sur* s) { return (long)s->nh * s->nout_p; }
 template <bool TRAIN>
 void launch_rows(lhmm_sur* s, const MlpArgs& a) {
     const dim3 grid(a.Bp / 32, s->E);
-    const size_t lds = mlp_lds_bytes(s->nin_p, s->nh);
-    if (s->nh <= 32 * MLP_WAVES)
-        k_mlp_rows<TRAIN, 1><<<grid, 64 * MLP_WAVES, lds, s->stream>>>(a);
+    const bool wide = !TRAIN && s->nin_p > MLP_XCOLS, two = s->nh > 32 * MLP_WAVES;
+    const size_t lds = mlp_lds_bytes(wide ? MLP_XCOLS : s->nin_p, s->nh);
+    const int T = 64 * MLP_WAVES;
+    if constexpr (!TRAIN)
+        if (wide) {
+            if (two)
+                k_mlp_rows<false, 2, true><<<grid, T, lds, s->stream>>>(a);
+            else
+                k_mlp_rows<false, 1, true><<<grid, T, lds, s->stream>>>(a);
+            return;
+        }
+    if (two)
+        k_mlp_rows<TRAIN, 2, false><<<grid, T, lds, s->stream>>>(a);
     else
-        k_mlp_rows<TRAIN, 2><<<grid, 64 * MLP_WAVES, lds, s->stream>>>(a);
+        k_mlp_rows<TRAIN, 1, false><<<grid, T, lds, s->stream>>>(a);
 }
 
 MlpArgs rows_args(const lhmm_sur* s, const float* X, int B) {
@@ -779,8 +789,9 @@ int lhmm_sur_create(const lhmm_sur_params* p, const float* weights, void* stream
     const size_t lds = mlp_lds_bytes(s->nin_p, s->nh);
     s->fused = s->nh <= MLP_MAX_NH && lds <= MLP_LDS_MAX;
     if (s->fused)
-        for (const void* k : {(const void*)&k_mlp_rows<false, 1>, (const void*)&k_mlp_rows<false, 2>,
-                              (const void*)&k_mlp_rows<true, 1>, (const void*)&k_mlp_rows<true, 2>})
+        for (const void* k : {(const void*)&k_mlp_rows<false, 1, false>, (const void*)&k_mlp_rows<false, 2, false>,
+                              (const void*)&k_mlp_rows<false, 1, true>, (const void*)&k_mlp_rows<false, 2, true>,
+                              (const void*)&k_mlp_rows<true, 1, false>, (const void*)&k_mlp_rows<true, 2, false>})
             if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MLP_LDS_MAX) != hipSuccess) {
                 delete s;
                 return lhmm_fail(LHMM_ERR_HIP, "fused layers: LDS of %zu bytes refused", lds);
