@@ -38,7 +38,15 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
     return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * expf(-0.5f * z * z);
 }
 
-constexpr int MLP_WAVES = 8;    // waves of a k_mlp_rows workgroup, one 32-column tile each at a time
+// Waves of a k_mlp_rows workgroup, one 32-column tile each at a time.  In layers
+// of one or two tiles the others only load: two waves do there, from more
+// workgroups than the chip takes at once with eight (four a CU), 5 x 30000 rows
+// of 129-32-32-32 64 us with eight waves and 46 with two (layer by layer 59),
+// their training step 317 and 198; 5 x 700 rows 12.0 and 13.5.  Training
+// transposes the features as well, with eight waves where they are many (3000
+// rows of 1700-32-32-3: 153 us and 208).
+constexpr int MLP_WAVES = 8, MLP_NARROW_WAVES = 2;
+inline bool mlp_few_waves(bool train, int workgroups, int nin_p) { return workgroups > 1024 && (!train || nin_p <= 320); }
 constexpr int MLP_MAX_NH = 64 * MLP_WAVES;  // two tiles per wave
 constexpr int MLP_PAD = 8;      // bf16 of padding per LDS row (16-byte reads of 32 rows spread over the banks)
 constexpr size_t MLP_LDS_MAX = 150 * 1024;
@@ -103,27 +111,27 @@ __device__ __forceinline__ void mlp_store_t(bf16* base, int t, int KSB, int R0, 
 
 // One workgroup per (32 rows, member), 32 the smallest tile of the matrix
 // instruction.  NTW: 32-column tiles per wave and hidden layer.  Measured (5
-// members 129-256-256-3): inference of 3572 rows 22.6 us against 57.7 layer by
-// layer, 217 rows 14.3 against 37.6; the rows of a 4096-row training step 64 us
-// against 200.  Bound by the GELU (about 40 vector instructions an element, 10
-// of the 22.6 us) on the 2 or 3 workgroups that share a CU, and in training by
-// 85 MB of transposed operands and FP32 dZ written as well.  GELU' parked in
+// members 129-256-256-3): inference of 3572 rows 21.4 us against 57.7 layer by
+// layer, 217 rows 13.4 against 37.6 (22.6 and 14.3 with features loaded one
+// by one); the rows of a 4096-row training step 61 us against 200.  Bound by the
+// GELU on the 2 or 3 workgroups that share a CU, and in training by 85 MB of
+// transposed operands and FP32 dZ written as well.  GELU' parked in
 // memory instead of registers (three workgroups per CU) took 73 us.
 //
-// WIDE (inference, more than MLP_XCOLS features): the features pass through LDS
-// MLP_XCOLS at a time, the next ones on their way while these are multiplied, in
+// WIDE (inference, more than mlp_xcols features): they pass through LDS that many
+// at a time, the next ones on their way while these are multiplied, in
 // the same order.  With all of them in LDS a CU held one workgroup, whose loads
 // waited for one another: 5 x 12000 rows of 1250-128-128-3 193 us layer by
-// layer, 390 with all features in LDS, 106 in pieces; 1700-32-32-3 113, 490 and
-// 112.  Narrow layers gain least (seven of eight waves only load): 400-32-32-3
-// 44, 47 and 53 us, 1000-32-32-3 75, 165 and 83.
-constexpr int MLP_XCOLS = 320;
+// layer, 390 with all features in LDS, 113 in pieces; 1700-32-32-3 113, 490 and
+// 92; 400-32-32-3 44, 47 and 36.
+constexpr int mlp_xcols(int waves) { return waves == MLP_NARROW_WAVES ? 192 : 320; }
 
-template <bool TRAIN, int NTW, bool WIDE>
-__global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
+template <bool TRAIN, int NTW, bool WIDE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_mlp_rows(MlpArgs g) {
     static_assert(!(TRAIN && WIDE), "training reads all features again");
+    constexpr int XC = mlp_xcols(WAVES), RW = 32 / WAVES;  // features loaded at a time; rows of a wave
     extern __shared__ __align__(16) unsigned char mlp_lds[];
-    const int ldx = (WIDE ? MLP_XCOLS : g.nin_p) + MLP_PAD, ldh = g.nh + MLP_PAD, ldy = 32 + MLP_PAD;
+    const int ldx = (WIDE ? XC : g.nin_p) + MLP_PAD, ldh = g.nh + MLP_PAD, ldy = 32 + MLP_PAD;
     bf16* Xs = (bf16*)mlp_lds;
     bf16* Ha = Xs + 32 * ldx;
     bf16* Hb = Ha + 32 * ldh;
@@ -135,48 +143,55 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
     const bf16* W2 = g.W2f + (size_t)e * g.nh * g.nh;
     const bf16* W3 = g.W3f + (size_t)e * 32 * g.nh;
     bf16x8 b[mlp_pf(TRAIN, WIDE)];
-    floatx16 acc1[NTW] = {};  // WIDE: the first layer's products
-    if constexpr (WIDE) {
-        float x[4][MLP_XCOLS / 64];  // rows wv, wv + 8, ..
-        auto load = [&](int c0) {
+    // the rows, rounded to BF16, XC features in flight; rows and columns of the
+    // padding are zero
+    float x[RW][XC / 64];  // rows wv, wv + WAVES, ..
+    auto load = [&](int c0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+        for (int k = 0; k < XC / 64; ++k)
+            if (c0 + 64 * k < g.nin_p)
 #pragma unroll
-                for (int k = 0; k < MLP_XCOLS / 64; ++k) {
-                    const int r = wv + MLP_WAVES * q, c = c0 + 64 * k + l;
+                for (int q = 0; q < RW; ++q) {
+                    const int r = wv + WAVES * q, c = c0 + 64 * k + l;
                     x[q][k] = (R0 + r < g.B && c < g.nin) ? g.X[(size_t)(R0 + r) * g.nin + c] : 0.0f;
                 }
-        };
-        auto ksteps = [&](int c0) { return min(MLP_XCOLS, g.nin_p - c0) / 16; };
-        auto weights = [&](int j, int c0) { return W1 + ((size_t)(wv + MLP_WAVES * j) * KS1 + c0 / 16) * 512; };
-        load(0);
+    };
+    auto keep = [&](int c0, int at) {  // features c0 .. to column at of the LDS rows
+#pragma unroll
+        for (int k = 0; k < XC / 64; ++k)
+            if (c0 + 64 * k + l < g.nin_p)
+#pragma unroll
+                for (int q = 0; q < RW; ++q) Xs[(wv + WAVES * q) * ldx + at + 64 * k + l] = (bf16)x[q][k];
+    };
+    floatx16 acc1[NTW] = {};  // WIDE: the first layer's products
+    load(0);
+    if constexpr (WIDE) {
+        auto ksteps = [&](int c0) { return min(XC, g.nin_p - c0) / 16; };
+        auto weights = [&](int j, int c0) { return W1 + ((size_t)(wv + WAVES * j) * KS1 + c0 / 16) * 512; };
         if (wv < nt) mlp_preload(b, weights(0, 0), ksteps(0), l);
-        for (int c0 = 0; c0 < g.nin_p; c0 += MLP_XCOLS) {
+        for (int c0 = 0; c0 < g.nin_p; c0 += XC) {
             if (c0 > 0) __syncthreads();
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int k = 0; k < MLP_XCOLS / 64; ++k) Xs[(wv + MLP_WAVES * q) * ldx + 64 * k + l] = (bf16)x[q][k];
+            keep(c0, 0);
             __syncthreads();
-            if (c0 + MLP_XCOLS < g.nin_p) load(c0 + MLP_XCOLS);
+            if (c0 + XC < g.nin_p) load(c0 + XC);
 #pragma unroll
             for (int j = 0; j < NTW; ++j)
-                if (wv + MLP_WAVES * j < nt) {
+                if (wv + WAVES * j < nt) {
                     if (j > 0) mlp_preload(b, weights(j, c0), ksteps(c0), l);
                     mlp_tile(acc1[j], b, Xs, ldx, weights(j, c0), ksteps(c0), l);
                 }
-            if (wv < nt && c0 + MLP_XCOLS < g.nin_p) mlp_preload(b, weights(0, c0 + MLP_XCOLS), ksteps(c0 + MLP_XCOLS), l);
+            if (wv < nt && c0 + XC < g.nin_p) mlp_preload(b, weights(0, c0 + XC), ksteps(c0 + XC), l);
         }
     } else {
         if (wv < nt) mlp_preload(b, W1 + (size_t)wv * KS1 * 512, KS1, l);
-        // the rows, rounded to BF16; rows and columns of the padding are zero
-        for (int r = wv; r < 32; r += MLP_WAVES)
-            for (int c = l; c < g.nin_p; c += 64)
-                Xs[r * ldx + c] = (bf16)((R0 + r < g.B && c < g.nin) ? g.X[(size_t)(R0 + r) * g.nin + c] : 0.0f);
+        for (int c0 = 0; c0 < g.nin_p; c0 += XC) {
+            if (c0 > 0) load(c0);
+            keep(c0, c0);
+        }
         __syncthreads();
     }
     if (TRAIN && e == 0) {  // X as the weight gradient reads it, once for all members
-        for (int q = tid; q < 4 * g.nin_p; q += 64 * MLP_WAVES) {
+        for (int q = tid; q < 4 * g.nin_p; q += 64 * WAVES) {
             const int c = q >> 2, s = q & 3;  // feature, group of eight rows
             bf16x8 v;
 #pragma unroll
@@ -191,7 +206,7 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
                       floatx16* d, const bf16* Wnext, int KSn, int ntn, const floatx16* done) {
 #pragma unroll
         for (int j = 0; j < NTW; ++j) {
-            const int t = wv + MLP_WAVES * j;
+            const int t = wv + WAVES * j;
             if (t < nt) {
                 floatx16 acc{};
                 if (done) {
@@ -201,7 +216,7 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
                     mlp_tile(acc, b, As, lda, W + (size_t)t * KS * 512, KS, l);
                 }
                 // the next product's first fragments travel during the GELU
-                if (j + 1 == NTW || t + MLP_WAVES >= nt)
+                if (j + 1 == NTW || t + WAVES >= nt)
                     if (wv < ntn) mlp_preload(b, Wnext + (size_t)wv * KSn * 512, KSn, l);
                 const int col = 32 * t + (l & 31);
                 const float bv = bias[(size_t)e * g.nh + col];
@@ -274,7 +289,7 @@ __global__ __launch_bounds__(64 * MLP_WAVES) void k_mlp_rows(MlpArgs g) {
     auto back = [&](const bf16* As, int lda, const bf16* W, int KS, const floatx16* d, bf16* Zs, bf16* Zt, float* Zf) {
 #pragma unroll
         for (int j = 0; j < NTW; ++j) {
-            const int t = wv + MLP_WAVES * j;
+            const int t = wv + WAVES * j;
             if (t < nt) {
                 floatx16 acc{};
                 if (j > 0) mlp_preload(b, W + (size_t)t * KS * 512, KS, l);

@@ -575,24 +575,23 @@ long szW3(const lhmm_sur* s) { return (long)s->nh * s->nout_p; }
 
 // --- fused engines -----------------------------------------------------------
 
-template <bool TRAIN>
+template <bool TRAIN, int NTW, int WAVES>
 void launch_rows(lhmm_sur* s, const MlpArgs& a) {
     const dim3 grid(a.Bp / 32, s->E);
-    const bool wide = !TRAIN && s->nin_p > MLP_XCOLS, two = s->nh > 32 * MLP_WAVES;
-    const size_t lds = mlp_lds_bytes(wide ? MLP_XCOLS : s->nin_p, s->nh);
-    const int T = 64 * MLP_WAVES;
-    if constexpr (!TRAIN)
-        if (wide) {
-            if (two)
-                k_mlp_rows<false, 2, true><<<grid, T, lds, s->stream>>>(a);
-            else
-                k_mlp_rows<false, 1, true><<<grid, T, lds, s->stream>>>(a);
-            return;
-        }
-    if (two)
-        k_mlp_rows<TRAIN, 2, false><<<grid, T, lds, s->stream>>>(a);
+    if (!TRAIN && s->nin_p > mlp_xcols(WAVES))
+        k_mlp_rows<TRAIN, NTW, !TRAIN, WAVES><<<grid, 64 * WAVES, mlp_lds_bytes(mlp_xcols(WAVES), s->nh), s->stream>>>(a);
     else
-        k_mlp_rows<TRAIN, 1, false><<<grid, T, lds, s->stream>>>(a);
+        k_mlp_rows<TRAIN, NTW, false, WAVES><<<grid, 64 * WAVES, mlp_lds_bytes(s->nin_p, s->nh), s->stream>>>(a);
+}
+
+template <bool TRAIN>
+void launch_rows(lhmm_sur* s, const MlpArgs& a) {
+    if (s->nh <= 32 * MLP_NARROW_WAVES && mlp_few_waves(TRAIN, a.Bp / 32 * s->E, s->nin_p))
+        launch_rows<TRAIN, 1, MLP_NARROW_WAVES>(s, a);
+    else if (s->nh <= 32 * MLP_WAVES)
+        launch_rows<TRAIN, 1, MLP_WAVES>(s, a);
+    else
+        launch_rows<TRAIN, 2, MLP_WAVES>(s, a);
 }
 
 MlpArgs rows_args(const lhmm_sur* s, const float* X, int B) {
@@ -789,9 +788,12 @@ int lhmm_sur_create(const lhmm_sur_params* p, const float* weights, void* stream
     const size_t lds = mlp_lds_bytes(s->nin_p, s->nh);
     s->fused = s->nh <= MLP_MAX_NH && lds <= MLP_LDS_MAX;
     if (s->fused)
-        for (const void* k : {(const void*)&k_mlp_rows<false, 1, false>, (const void*)&k_mlp_rows<false, 2, false>,
-                              (const void*)&k_mlp_rows<false, 1, true>, (const void*)&k_mlp_rows<false, 2, true>,
-                              (const void*)&k_mlp_rows<true, 1, false>, (const void*)&k_mlp_rows<true, 2, false>})
+        for (const void* k : {(const void*)&k_mlp_rows<false, 1, false, MLP_NARROW_WAVES>,
+                              (const void*)&k_mlp_rows<false, 1, true, MLP_NARROW_WAVES>,
+                              (const void*)&k_mlp_rows<true, 1, false, MLP_NARROW_WAVES>,
+                              (const void*)&k_mlp_rows<false, 1, false, MLP_WAVES>, (const void*)&k_mlp_rows<false, 1, true, MLP_WAVES>,
+                              (const void*)&k_mlp_rows<true, 1, false, MLP_WAVES>, (const void*)&k_mlp_rows<false, 2, false, MLP_WAVES>,
+                              (const void*)&k_mlp_rows<false, 2, true, MLP_WAVES>, (const void*)&k_mlp_rows<true, 2, false, MLP_WAVES>})
             if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MLP_LDS_MAX) != hipSuccess) {
                 delete s;
                 return lhmm_fail(LHMM_ERR_HIP, "fused layers: LDS of %zu bytes refused", lds);
