@@ -2249,6 +2249,12 @@ int dalloc(T** p, size_t count) {
     return LHMM_OK;
 }
 
+void drop_groups(lhmm_micro* m) {
+    for (auto& gr : m->groups)
+        if (gr.d_lists) (void)hipFree(gr.d_lists);
+    m->groups.clear();
+}
+
 void release(lhmm_micro* m) {
     if (m->stream) (void)hipStreamSynchronize(m->stream);
     for (auto& kv : m->graphs) (void)hipGraphExecDestroy(kv.second);
@@ -2263,9 +2269,7 @@ void release(lhmm_micro* m) {
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     m->stage.release();
-    for (auto& gr : m->groups)
-        if (gr.d_lists) (void)hipFree(gr.d_lists);
-    m->groups.clear();
+    drop_groups(m);
     for (int g = 0; g < MAX_GROUPS - 1; ++g) {
         if (m->aux[g]) (void)hipStreamDestroy(m->aux[g]);
         if (m->ev_join[g]) (void)hipEventDestroy(m->ev_join[g]);
@@ -2351,27 +2355,32 @@ void bin_lds(lhmm_micro* m) {
 }
 
 // Cut the boxes into slabs for the binning: about SLAB_TARGET particles (or
-// bin_split, where that is smaller) and at most SLAB_CELLS cells each.
-int build_slabs(lhmm_micro* m) {
-    const int target = m->cfg.bin_split > 0 ? std::min(m->cfg.bin_split, SLAB_TARGET) : SLAB_TARGET;
-    m->slab_box.clear();
+// bin_split, where that is smaller) and at most SLAB_CELLS cells each.  Where
+// the allocation fails the slabs stay as they were.
+int build_slabs(lhmm_micro* m, int bin_split) {
+    const int target = bin_split > 0 ? std::min(bin_split, SLAB_TARGET) : SLAB_TARGET;
+    std::vector<BoxInfo> box = m->box;
+    std::vector<int> slab_box;
     for (int b = 0; b < m->n_boxes; ++b) {
-        BoxInfo& B = m->box[b];
-        B.slab_off = (int)m->slab_box.size();
+        BoxInfo& B = box[b];
+        B.slab_off = (int)slab_box.size();
         // every column belongs to one slab, so more slabs than columns (9 at least) would only idle
         B.nslab = std::max((B.n + target - 1) / target, (B.cell_cap + SLAB_CELLS - 1) / SLAB_CELLS);
         B.nslab = std::min(B.nslab, box_cols(B));
-        for (int q = 0; q < B.nslab; ++q) m->slab_box.push_back(b);
+        for (int q = 0; q < B.nslab; ++q) slab_box.push_back(b);
     }
-    m->n_slabs = (int)m->slab_box.size();
-    bin_lds(m);
-    if (m->d_slab_box) HIPCHK(hipFree(m->d_slab_box));
-    m->d_slab_box = nullptr;
-    int rc = dalloc(&m->d_slab_box, (size_t)m->n_slabs);
+    int* d = nullptr;
+    int rc = dalloc(&d, slab_box.size());
     if (rc != LHMM_OK) return rc;
+    std::swap(d, m->d_slab_box);
+    if (d) (void)hipFree(d);
+    m->ctx.slab_box = m->d_slab_box;
+    m->n_slabs = (int)slab_box.size();
+    m->slab_box.swap(slab_box);
+    m->box.swap(box);
+    bin_lds(m);
     HIPCHK(hipMemcpy(m->d_slab_box, m->slab_box.data(), m->n_slabs * sizeof(int), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(m->d_box, m->box.data(), m->n_boxes * sizeof(BoxInfo), hipMemcpyHostToDevice));
-    m->ctx.slab_box = m->d_slab_box;
     return LHMM_OK;
 }
 
@@ -2412,11 +2421,9 @@ Lists fill_lists(const lhmm_micro* m, const int* boxes, int n_sel, int* out) {
 // groups that take equally long overlap to the chunk's end (with the largest
 // boxes, two thirds of the particles, in one group, that one ran alone after
 // the other: batch of 256, 20 steps, 5046 us against 4800).
-int prepare_groups(lhmm_micro* m, int G) {
+int make_groups(lhmm_micro* m, int G) {
     HIPCHK(hipStreamSynchronize(m->stream));
-    for (auto& gr : m->groups)
-        if (gr.d_lists) (void)hipFree(gr.d_lists);
-    m->groups.clear();
+    drop_groups(m);
     if (G <= 1) return LHMM_OK;
     if (!m->ev_fork) {
         HIPCHK(hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming));
@@ -2454,6 +2461,13 @@ int prepare_groups(lhmm_micro* m, int G) {
         HIPCHK(hipMemcpy(gr.d_lists, lists.data(), sizeof(int) * n, hipMemcpyHostToDevice));
     }
     return LHMM_OK;
+}
+
+// Groups that could not all be made would leave boxes out: then there are none.
+int prepare_groups(lhmm_micro* m, int G) {
+    const int rc = make_groups(m, G);
+    if (rc != LHMM_OK) drop_groups(m);
+    return rc;
 }
 
 // Validate a host list of boxes (strictly increasing, in range), upload it
@@ -2727,7 +2741,7 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     C.key0 = (unsigned)(p->seed & 0xFFFFFFFFull);
     C.key1 = (unsigned)(p->seed >> 32);
     m->cfg.groups = m->n_blocks < GROUP2_BLOCKS ? 1 : (m->n_blocks < GROUP3_BLOCKS ? 2 : 3);
-    rc = build_slabs(m);
+    rc = build_slabs(m, m->cfg.bin_split);
     if (rc == LHMM_OK) rc = prepare_groups(m, m->cfg.groups);
     if (rc != LHMM_OK) {
         release(m);
@@ -2895,9 +2909,12 @@ int lhmm_micro_set_config(lhmm_micro* m, const lhmm_micro_config* cfg) {
     HIPCHK(hipStreamSynchronize(m->stream));
     drop_graphs(m);
     const bool reslab = cfg->bin_split != m->cfg.bin_split, regroup = cfg->groups != m->cfg.groups || reslab;
+    int rc = reslab ? build_slabs(m, cfg->bin_split) : LHMM_OK;
+    if (rc != LHMM_OK) return rc;
     m->cfg = *cfg;
-    const int rc = reslab ? build_slabs(m) : LHMM_OK;
-    return rc == LHMM_OK && regroup ? prepare_groups(m, cfg->groups) : rc;
+    if (regroup) rc = prepare_groups(m, cfg->groups);
+    if (rc != LHMM_OK) m->cfg.groups = 1;
+    return rc;
 }
 
 int lhmm_micro_set_afbc(lhmm_micro* m, const double* regions, double zeta) {
