@@ -1308,8 +1308,9 @@ __device__ __forceinline__ void end_step(const Ctx& C, const Step& A, const BoxI
     if (id < B.n_beads) ((V4*)C.sid[ns])[i] = rec;
 }
 
-template <typename real, int QD, bool PRUNE, bool COMP = false, bool AF = false>
-__global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ? 4 : (COMP || AF || PRUNE ? 5 : 8)) : 1) void k_forces(
+// FLAT: some box may be too flat for its stencil (see the scan state).
+template <typename real, int QD, bool PRUNE, bool COMP = false, bool AF = false, bool FLAT = false>
+__global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ? 4 : (COMP || AF || PRUNE || FLAT ? 5 : 8)) : 1) void k_forces(
     Ctx C, Step A, int drain, int busy) {
     constexpr bool prune = PRUNE;
     constexpr int NV = COMP ? 37 : 19;  // block partial sums
@@ -1467,15 +1468,17 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ?
     // the search-layout records from byte q to byte qe (z cells k2 - zsub ..
     // k2 + zsub of the row's column, the periodic images included).
     // Up to SREC_PAD records past a range's end are the column's next z cells, at
-    // least the cutoff away along z while zsub cells span it, or the column's
+    // least the cutoff away along z where zsub cells span it, or the column's
     // padding: they need no test of their own, and a lane whose range has ended
     // stays at its end.  In a box too flat for that (flagged) they may lie within
     // it: one record per iteration, none at the end of the range (it would be
-    // queued again for as long as another lane of the wave scans).  A lane that
-    // scans nothing (no particle, a pruned row) tests from far away.
+    // queued again for as long as another lane of the wave scans).  A variant of
+    // its own: in the common kernel, whose 64 registers are all taken, most forms
+    // of that branch spilled and cost the batch 4 to 9%.  A lane that scans
+    // nothing (no particle, a pruned row) tests from far away.
     int row = 0;
     unsigned q = 0, qe = 0;
-    const bool spans = z_cells_span(D.h[8], zs, n2, C.rc);
+    const bool spans = !FLAT || z_cells_span(D.h[8], zs, n2, C.rc);
     const real far = far_away<real>(C, D);
     auto set_range = [&]() {
         const int d0 = row / 3 - 1, d1 = row % 3 - 1;
@@ -1530,7 +1533,7 @@ __global__ __launch_bounds__(BS, sizeof(real) == 4 ? (QD >= 32 || (COMP && AF) ?
             // SU records per lane per iteration, all loads issued before the
             // first test, addressed by one 32-bit byte offset from the box's
             // records
-            if (__builtin_expect(spans, 1)) {
+            if (spans) {
                 V4 cand[SU];
 #pragma unroll
                 for (int u = 0; u < SU; ++u) cand[u] = load_rec<real>(srsrc, sbase, q + u * (unsigned)sizeof(V4));
@@ -2004,6 +2007,7 @@ struct lhmm_micro {
     bool have_snapshot = false;
     bool have_state = false, forces_valid = false;
     bool afbc = false;  // some box has boundary regions (lhmm_micro_set_afbc)
+    bool flat = false;  // some box has been too flat for its stencil
     std::map<int, hipGraphExec_t> graphs;
     // graphs of subset steps, keyed by (boxes, blocks, slabs, steps): a shape is
     // captured the second time it is asked for (history replays repeat it)
@@ -2063,7 +2067,8 @@ void launch_bin(lhmm_micro* m, const Launch& L, const Step& A) {
 
 template <typename real>
 void launch_forces(lhmm_micro* m, const Launch& L, const Step& A) {
-    const int drain = m->cfg.drain, busy = m->cfg.busy_lanes;
+    int drain = m->cfg.drain;
+    const int busy = m->cfg.busy_lanes;
     const Ctx& C = L.C;
     const bool comp = C.nv > 19;
     if (L.wide) {
@@ -2073,25 +2078,30 @@ void launch_forces(lhmm_micro* m, const Launch& L, const Step& A) {
             k_forces_wide<real, false><<<L.nblk * WIDE_UNITS, BS, 0, L.st>>>(C, A);
         return;
     }
-#define LHMM_FORCES(QD)                                                                      \
-    do {                                                                                     \
-        if (m->afbc && comp)                                                                 \
-            k_forces<real, QD, false, true, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);  \
-        else if (m->afbc)                                                                    \
-            k_forces<real, QD, false, false, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy); \
-        else if (comp)                                                                       \
-            k_forces<real, QD, false, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);        \
-        else if (m->cfg.prune)                                                               \
-            k_forces<real, QD, true><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);               \
-        else                                                                                 \
-            k_forces<real, QD, false><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);              \
+#define LHMM_FORCES(QD, FLAT)                                                                     \
+    do {                                                                                          \
+        if (m->afbc && comp)                                                                      \
+            k_forces<real, QD, false, true, true, FLAT><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy);  \
+        else if (m->afbc)                                                                         \
+            k_forces<real, QD, false, false, true, FLAT><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy); \
+        else if (comp)                                                                            \
+            k_forces<real, QD, false, true, false, FLAT><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy); \
+        else if (m->cfg.prune)                                                                    \
+            k_forces<real, QD, true, false, false, FLAT><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy); \
+        else                                                                                      \
+            k_forces<real, QD, false, false, false, FLAT><<<L.nblk, BS, 0, L.st>>>(C, A, drain, busy); \
     } while (0)
+    if (m->flat) {  // rare, in one queue depth (it changes no result)
+        drain = std::min(drain, 16 - scan_unroll(16));
+        LHMM_FORCES(16, true);
+        return;
+    }
     switch (m->cfg.queue_depth) {
-        case 2: LHMM_FORCES(2); break;
-        case 4: LHMM_FORCES(4); break;
-        case 8: LHMM_FORCES(8); break;
-        case 32: LHMM_FORCES(32); break;
-        default: LHMM_FORCES(16); break;
+        case 2: LHMM_FORCES(2, false); break;
+        case 4: LHMM_FORCES(4, false); break;
+        case 8: LHMM_FORCES(8, false); break;
+        case 32: LHMM_FORCES(32, false); break;
+        default: LHMM_FORCES(16, false); break;
     }
 #undef LHMM_FORCES
 }
@@ -2337,6 +2347,12 @@ int launch_subset_steps(lhmm_micro* m, const Launch& L, int len) {
         launch_steps(m, L, len);
     }
     return LHMM_OK;
+}
+
+// A box of z extent hz is too flat for its stencil where the smallest number of
+// cells does not span the cutoff (more cells come only with more extent).
+bool is_flat(const lhmm_micro* m, int b, double hz) {
+    return !z_cells_span(hz, m->box[b].zsub, 2 * m->box[b].zsub + 1, m->p.rc);
 }
 
 // LDS of the binning for the boxes' present z extents.  The cells of a
@@ -2618,7 +2634,10 @@ int lhmm_micro_create(const lhmm_params* p, const lhmm_box* boxes, int32_t n_box
     m->n_total = off;
     m->n_blocks = blk_off;
     m->hz.resize(n_boxes);
-    for (int b = 0; b < n_boxes; ++b) m->hz[b] = boxes[b].h0[8];
+    for (int b = 0; b < n_boxes; ++b) {
+        m->hz[b] = boxes[b].h0[8];
+        m->flat = m->flat || is_flat(m, b, boxes[b].h0[8]);
+    }
     const size_t N = (size_t)m->n_total;
     int rc = LHMM_OK;
 #define ALLOC(ptr, cnt)                     \
@@ -2792,16 +2811,19 @@ int lhmm_micro_set_state(lhmm_micro* m, const double* s, const double* c, const 
         for (int b = 0; b < m->n_boxes; ++b)
             for (int k = 0; k < 9; ++k) dyn[b].h[k] = h[9 * b + k];
         HIPCHK(hipMemcpy(m->d_dyn, dyn.data(), m->n_boxes * sizeof(BoxDyn), hipMemcpyHostToDevice));
-        bool taller = false;
-        for (int b = 0; b < m->n_boxes; ++b)
+        // captured launches hold the binning's LDS size and the force kernel's
+        // variant; a restored snapshot has extents that were set before
+        bool taller = false, flat = m->flat;
+        for (int b = 0; b < m->n_boxes; ++b) {
             if (h[9 * b + 8] > m->hz[b]) {
                 m->hz[b] = h[9 * b + 8];
                 taller = true;
             }
-        if (taller) {  // captured binning launches hold their LDS size
-            bin_lds(m);
-            drop_graphs(m);
+            flat = flat || is_flat(m, b, h[9 * b + 8]);
         }
+        if (taller) bin_lds(m);
+        if (taller || flat != m->flat) drop_graphs(m);
+        m->flat = flat;
     }
     unsigned long long st = step;
     HIPCHK(hipMemcpy(m->d_step, &st, sizeof st, hipMemcpyHostToDevice));
