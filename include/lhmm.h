@@ -202,7 +202,8 @@ int lhmm_micro_step_subset(lhmm_micro* m, const double* gradL, int32_t n_steps, 
  * every sum keeps its order, so all configurations give bit-identical
  * trajectories.
  *   queue_depth: per-lane neighbour queue of the pair-force kernel
- *                (2, 4, 8, 16, 32 entries of 4 bytes);
+ *                (2, 4, 8, 16, 32 entries of 4 bytes; engines with a box too
+ *                flat for its stencil, LHMM_FLAG_CELL, search with 16);
  *   drain:       evaluation rounds run until every queue holds at most this
  *                many neighbours (0 .. queue_depth - u, where a search
  *                iteration tests u = 4, 2, 1 records per lane for depths

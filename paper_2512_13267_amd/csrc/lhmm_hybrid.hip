@@ -19,7 +19,7 @@
 // host memory, and one readback of the micro flags; the particle lists are
 // built on the host and uploaded once, the mask of step 4 is read from pinned
 // host memory.  With a quiet gate a step is nine launches (five of them the
-// SPH step) and one wait: 72 us of kernels for 3572 particles, 24 us of them
+// SPH step) and one wait: 70 us of kernels for 3572 particles, 23 us of them
 // the forward pass.
 #include <hip/hip_runtime.h>
 

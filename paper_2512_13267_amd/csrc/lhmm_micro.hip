@@ -878,7 +878,7 @@ __device__ __forceinline__ void block_scan(int n, int* wsum /* BT / 64 */, Val v
 //
 // One workgroup per box (the earlier form) took 19 us for 3000 particles,
 // 67 us for a batch with boxes of 1.5k to 12k and 160 us for eight of 23k,
-// which did not fit its LDS; the largest box set the time.  Now 8.3, 31 and
+// which did not fit its LDS; the largest box set the time.  Now 8, 32 and
 // 19 us: one chain of loads, scans and barriers for small launches, and for
 // large boxes the reading of all keys by every slab.
 //
@@ -1141,14 +1141,15 @@ __device__ __forceinline__ double inv_sqrt<double>(double x) { return 1.0 / sqrt
 //   `drain` entries (and while `busy` or more lanes have work), and the
 //   queues are drained at the end.  Deep queues let most lanes hold work in
 //   every round.
-//   What bounds it (256 relaxed boxes, 1.5M particles): a wave makes ~5300
-//   accesses to the vector cache, one per cycle and CU (28 for a search step's
-//   16-byte load, 64 for each of a round's two gathers), and issues ~4400 vector
-//   instructions, both near the limit of the CU, so that what helped last was
-//   waves to overlap them: 64 registers, eight waves per SIMD, 173 us; six
-//   waves 181; the previous form of the loops, six waves, 183.  Evaluating a
-//   round without its branch (idle lanes on a zero force) cost 2 us, loading
-//   only for lanes with records left gained nothing.
+//   What bounds it (256 relaxed boxes, 1.5M particles, 164 us): a wave makes
+//   ~5300 accesses to the vector cache, one per cycle and CU (28 for a search
+//   step's 16-byte load, 64 for each of a round's two gathers), and issues 4235
+//   vector instructions, both near the limit of the CU, so that what helped last
+//   was waves to overlap them (64 registers, eight waves per SIMD, took 173 us
+//   when six took 181): 6% fewer instructions, with the tests of a search step
+//   scheduled apart, are no faster.  Evaluating a round without its branch (idle
+//   lanes on a zero force) cost 2 us, loading only for lanes with records left
+//   gained nothing.
 // records tested per lane and search iteration for a queue of depth QD
 __host__ __device__ constexpr int scan_unroll(int qd) { return qd >= 8 ? 4 : (qd >= 4 ? 2 : 1); }
 

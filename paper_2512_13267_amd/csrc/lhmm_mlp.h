@@ -74,7 +74,8 @@ inline size_t mlp_lds_bytes(int xcols, int nh) {
 // Weight fragments in flight per wave, so that a product of 16 k-steps does
 // not wait for L2 at every step.  Inference: 4 (14.3 us for 217 rows, 8 take
 // 15.5: the registers hold fewer waves).  Training keeps GELU' in registers
-// and has two workgroups per CU either way: 8 (64 us for 5 x 4096 rows, 4 take 67).
+// and has two workgroups per CU either way: 8 (64 us for 5 x 4096 rows, 4 took
+// 67); so does a wide forward pass.
 constexpr int mlp_pf(bool train, bool wide) { return train || wide ? 8 : 4; }
 
 template <int PF>
@@ -113,9 +114,10 @@ __device__ __forceinline__ void mlp_store_t(bf16* base, int t, int KSB, int R0, 
 // instruction.  NTW: 32-column tiles per wave and hidden layer.  Measured (5
 // members 129-256-256-3): inference of 3572 rows 21.4 us against 57.7 layer by
 // layer, 217 rows 13.4 against 37.6 (22.6 and 14.3 with features loaded one
-// by one); the rows of a 4096-row training step 61 us against 200.  Bound by the
-// GELU on the 2 or 3 workgroups that share a CU, and in training by 85 MB of
-// transposed operands and FP32 dZ written as well.  GELU' parked in
+// by one); the rows of a 4096-row training step 58 us against 200.  Bound by the
+// GELU: 52 vector instructions per hidden value and wave, all others included,
+// fill 12 of the 21 us, on the 2 or 3 workgroups that share a CU; in training
+// (33 of 58 us) by 85 MB of transposed operands and FP32 dZ written as well.  GELU' parked in
 // memory instead of registers (three workgroups per CU) took 73 us.
 //
 // WIDE (inference, more than mlp_xcols features): they pass through LDS that many
